@@ -157,9 +157,20 @@ class Operator:
         flags = ((capi.OP_WIDE if wide else 0) | (capi.OP_TILED if self.tiled else 0) |
                  (capi.OP_RECORDS if self.records else 0))
         nbytes = ctypes.c_size_t()
-        capi.check(lib.adlbr_operator_workspace(ctypes.byref(self._grid),
-                                                _dtype_code(self.storage), flags,
-                                                ctypes.byref(nbytes)))
+
+        def size(fl):
+            capi.check(lib.adlbr_operator_workspace(ctypes.byref(self._grid),
+                                                    _dtype_code(self.storage), fl,
+                                                    ctypes.byref(nbytes)))
+            return nbytes.value
+
+        if not self.tiled:
+            # pairs of opposite edges are merged, unless the caller's own
+            # workspace holds no more than the lists without merging
+            if workspace is None or workspace.numel() >= size(flags | capi.OP_MERGED) or \
+                    workspace.numel() < size(flags):
+                flags |= capi.OP_MERGED
+        size(flags)
         if workspace is not None and workspace.numel() >= nbytes.value:
             self.workspace = workspace
         else:

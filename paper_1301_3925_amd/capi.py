@@ -21,6 +21,7 @@ NEUMANN, PERIODIC, REFLECT = 0, 1, 2
 OP_WIDE = 1
 OP_TILED = 2
 OP_RECORDS = 4
+OP_MERGED = 8
 DT_ABS, DT_CFL = 0, 1
 MAP_CED, MAP_EED = 0, 1
 

@@ -268,10 +268,10 @@ extern "C" int adlbr_batch_create(int nprob, adlbr_operator *const *ops, void *c
     b->graph_steps = -1;
     std::map<int, int> idx;
     for (int i = 0; i < nprob; ++i) {
-        const int key = batch_class(ops[i]);
-        auto it = idx.find(key);
+        const int key = batch_class(ops[i]), kern = batch_kernels(ops[i]);
+        auto it = idx.find(kern);
         if (it == idx.end()) {
-            it = idx.emplace(key, (int)b->classes.size()).first;
+            it = idx.emplace(kern, (int)b->classes.size()).first;
             adlbr_batch::Class c;
             c.key = key;
             c.rep = ops[i];

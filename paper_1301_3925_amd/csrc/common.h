@@ -167,40 +167,32 @@ __device__ inline long long strip_block(long long L, const GridInfo &g, int poin
     return (long long)z * bp + j;
 }
 
-// Index of weight q of point z in an operator's weights.  2D (S = 3):
-// point-major [N][3], so that the gather of an incoming edge's weight from
-// its source finds the source's three weights on one line.  3D (S = 6),
-// with ADLBR_W3D_INLINE (the default): slot-major planes [6][N], read
-// coalesced by the own part only, and every incoming entry carries its
-// weight beside it (an 8-byte record in FP32).  Without it the 3D weights
-// are point-major too and gathered from the source, 4 bytes less per
-// incoming edge but slower (256^3 step 709 -> 911 us).
-#ifndef ADLBR_W3D_INLINE
-#define ADLBR_W3D_INLINE 1
-#endif
+// Index of weight q of point z in an operator's weights (as the caller gave
+// them; the apply reads the merged ones).  2D (S = 3): point-major [N][3];
+// 3D (S = 6): slot-major planes [6][N].
 template <int S> __host__ __device__ __forceinline__ long long widx(int q, long long z, long long N) {
-    return S == 3 || !ADLBR_W3D_INLINE ? z * S + q : (long long)q * N + z;
+    return S == 3 ? z * S + q : (long long)q * N + z;
 }
 template <int S> __host__ __device__ __forceinline__ unsigned widx32(int q, int z, int N) {
-    return S == 3 || !ADLBR_W3D_INLINE ? (unsigned)(z * S + q) : (unsigned)(q * N + z);
+    return S == 3 ? (unsigned)(z * S + q) : (unsigned)(q * N + z);
 }
 
-// First point of the calling wave's P consecutive 64-point groups in block
-// blk.  Blocks cover 256 P consecutive points, except on a 2D grid whose
-// rows are whole groups and whose row count is a multiple of 4 (with
-// P = 1): there a block takes a 64 x 4 patch, its four waves one row apart,
-// so that their neighbour gathers share the CU's L1 (2D apply on 2048^2:
-// 124 -> 109 us).  Same block count either way.
-__device__ __forceinline__ long long wave_group(const GridInfo &g, long long blk, int P) {
+// First point of the calling wave's 64 consecutive points (from a multiple of
+// 64) in block blk.  Blocks cover 256 consecutive points, except on a 2D grid
+// whose rows are whole groups and whose row count is a multiple of 4: there a
+// block takes a 64 x 4 patch, its four waves one row apart, so that their
+// neighbour gathers share the CU's L1 (2D apply on 2048^2: 124 -> 109 us).
+// Same block count either way.
+__device__ __forceinline__ long long wave_group(const GridInfo &g, long long blk) {
     const long long wv = threadIdx.x >> 6;
-    if (P == 1 && g.dim == 2 && g.nx % 64 == 0 && g.ny % 4 == 0) {
+    if (g.dim == 2 && g.nx % 64 == 0 && g.ny % 4 == 0) {
         // 32-bit division (blocks < 2^22 for N < 2^28): a 64-bit one by a
         // runtime divisor costs a long scalar sequence in every wave
         const unsigned gpr = (unsigned)g.nx / 64u, b = (unsigned)blk;
         const unsigned by = b / gpr, bx = b - by * gpr;
         return (long long)(by * 4u + (unsigned)wv) * g.nx + (long long)bx * 64;
     }
-    return blk * 256 * P + wv * 64 * P;
+    return blk * 256 + wv * 64;
 }
 
 // Device-resident scalars of a (flexible) conjugate-gradient iteration.
@@ -233,9 +225,8 @@ int net_apply_dots(const adlbr_net *net, const adlbr_operator *op, const float *
                    const CgState *st, hipStream_t s);
 
 // Rows per block of the explicit-step kernels: every wave of a 256-thread
-// block takes kApplyPPT groups of 64 consecutive rows.
-constexpr int kApplyPPT = 1;
-constexpr int kApplyPoints = 256 * kApplyPPT;
+// block takes 64 consecutive rows.
+constexpr int kApplyPoints = 256;
 
 // Device descriptor of one problem of a batch (one operator and its two
 // state buffers); first_block is the problem's first block in the batch's
@@ -245,8 +236,8 @@ constexpr int kApplyPoints = 256 * kApplyPPT;
 struct BatchProb {
     GridInfo g;
     const void *sb;
-    const void *w;
-    const uint8_t *cnt;
+    const void *w;           // tiled layout
+    const void *wp;          // merged edge weights (or w)
     const int32_t *pos;
     const int32_t *ent;
     const void *went;
@@ -265,6 +256,8 @@ long long batch_blocks(const adlbr_operator *op, int *block_points);
 // Class of an operator for batching (dim, offset width, boundary, storage):
 // problems of one class share a kernel instance.
 int batch_class(const adlbr_operator *op);
+// What separates kernel instances: the class, and whether edges are merged.
+int batch_kernels(const adlbr_operator *op);
 // Fill the operator part of a descriptor.
 void batch_describe(const adlbr_operator *op, BatchProb *d);
 // Device bytes one explicit step of op reads or writes (u, its successor and
