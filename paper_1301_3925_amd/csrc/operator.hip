@@ -58,7 +58,7 @@ struct adlbr_operator {
     int32_t *hnear;    // edges with every offset component <= hnear are not listed (tiled)
     double *wmax;      // largest weight (tiled: scale of the diagonal pass)
     double *rpart;     // per-block reach partials (tiled)
-    uint8_t *mask;     // bit q: slot q has a positive weight
+    uint8_t *mask;     // 2D, bit q: slot q has a positive weight
     void *lmask;       // listed edges of every point (lmask_t, k_merge)
     double *dsum;      // merged, 3D: own and merged weights of A_zz
     double *part;      // per-block partials of the assembly
@@ -86,7 +86,7 @@ template <> struct Slots<2, false> {
         o[0][0] = v.x; o[0][1] = v.y; o[1][0] = v.z; o[1][1] = v.w;
         o[2][0] = -o[0][0] - o[1][0]; o[2][1] = -o[0][1] - o[1][1];
     }
-    __device__ static bool pack(const int s[6][3], store_t *p, long long z) {
+    __device__ static bool pack(const int s[6][3], unsigned, store_t *p, long long z) {
         for (int q = 0; q < 2; ++q)
             for (int c = 0; c < 2; ++c)
                 if (s[q][c] > 127 || s[q][c] < -127) {
@@ -105,13 +105,15 @@ template <> struct Slots<2, true> {
         o[0][0] = v.x; o[0][1] = v.y; o[1][0] = v.z; o[1][1] = v.w;
         o[2][0] = -o[0][0] - o[1][0]; o[2][1] = -o[0][1] - o[1][1];
     }
-    __device__ static bool pack(const int s[6][3], store_t *p, long long z) {
+    __device__ static bool pack(const int s[6][3], unsigned, store_t *p, long long z) {
         p[z] = make_short4(s[0][0], s[0][1], s[1][0], s[1][1]);
         return true;
     }
 };
 struct __attribute__((aligned(4))) C3x8 { int8_t v[12]; };
 struct __attribute__((aligned(8))) C3x16 { int16_t v[12]; };
+// 3D: v[9] holds the mask of the slots of positive weight, beside the offsets
+// so that a gather of a neighbour's stencil brings both.
 template <> struct Slots<3, false> {
     typedef C3x8 store_t;
     int o[6][3];
@@ -128,7 +130,7 @@ template <> struct Slots<3, false> {
             o[5][c] = o[1][c] + o[2][c];
         }
     }
-    __device__ static bool pack(const int s[6][3], store_t *p, long long z) {
+    __device__ static bool pack(const int s[6][3], unsigned mask, store_t *p, long long z) {
         C3x8 v;
         for (int q = 0; q < 3; ++q)
             for (int c = 0; c < 3; ++c) {
@@ -139,7 +141,8 @@ template <> struct Slots<3, false> {
                 }
                 v.v[3 * q + c] = (int8_t)s[q][c];
             }
-        v.v[9] = v.v[10] = v.v[11] = 0;
+        v.v[9] = (int8_t)mask;
+        v.v[10] = v.v[11] = 0;
         p[z] = v;
         return true;
     }
@@ -157,11 +160,12 @@ template <> struct Slots<3, true> {
             o[5][c] = o[1][c] + o[2][c];
         }
     }
-    __device__ static bool pack(const int s[6][3], store_t *p, long long z) {
+    __device__ static bool pack(const int s[6][3], unsigned mask, store_t *p, long long z) {
         C3x16 v;
         for (int q = 0; q < 3; ++q)
             for (int c = 0; c < 3; ++c) v.v[3 * q + c] = (int16_t)s[q][c];
-        v.v[9] = v.v[10] = v.v[11] = 0;
+        v.v[9] = (int16_t)mask;
+        v.v[10] = v.v[11] = 0;
         p[z] = v;
         return true;
     }
@@ -242,48 +246,46 @@ __device__ __forceinline__ bool edge_target32(const Coord &p, int i, const int *
 
 // ---------------------------------------------------------------- build --
 
-__global__ void k_fill_i32(int32_t *p, long long n, int32_t v) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-template <typename TW> __device__ __forceinline__ double ld_w(const TW *w, long long i) {
-    return (double)w[i];
+// Start of an assembly: the status word, the near reach (0: every edge may be
+// listed) and the bin counters and cursors (3D, nb of each) in one launch.
+__global__ __launch_bounds__(256) void k_build_init(int32_t *status, int32_t *hnear,
+                                                    uint32_t *cnt, uint32_t *cur, long long nb) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) {
+        status[0] = 0x7fffffff;
+        status[1] = 0;
+        *hnear = 0;
+    }
+    if (i < nb) {
+        cnt[i] = 0u;
+        cur[i] = 0u;
+    }
 }
 
 // 3D assembly of the transpose (incoming lists) without per-edge global
-// atomics.  Targets are grouped into bins of kBin consecutive points; the
-// edges of a wavefront mostly land in one or two bins, so counting and
-// placing them costs one atomic per distinct bin per wavefront (leader lane,
-// ballot of the lanes that share its bin).  Each bin is then built by one
-// block with LDS counters.
+// atomics.  Targets are grouped into bins of kBin consecutive points.  The
+// bins of a block's edge targets lie near the block's own bin (offsets are
+// short against the grid), so blocks count their edges in an LDS window of
+// bins around it: one global atomic per window bin and block.  Targets outside
+// the window go to the global counters directly.  Each bin is then built by
+// one block with LDS counters.  (Counting every edge with a global atomic that
+// also ranks it, in k_merge, took 345 us at 160^3 and 235 us at 2048^2, more
+// than the bins and the 2D tiles.)
 constexpr int kBinShift = 10;
 constexpr int kBin = 1 << kBinShift;
 
-// Wave-aggregated "append to bin": every lane with bin >= 0 gets a slot in
-// its bin; the leader of each group of lanes sharing a bin does one atomic.
-// With count_only the slot is not needed.
-__device__ __forceinline__ unsigned bin_append(int bin, uint32_t *counter, bool count_only) {
-    const int lane = (int)(threadIdx.x & 63u);
-    unsigned long long pending = __ballot(bin >= 0);
-    unsigned slot = 0;
-    while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const int bl = __shfl(bin, leader, 64);
-        const unsigned long long m = __ballot(bin == bl);
-        unsigned base = 0;
-        if (lane == leader) base = atomicAdd(&counter[bl], (unsigned)__popcll(m));
-        if (!count_only) {
-            base = __shfl(base, leader, 64);
-            if (bin == bl) slot = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
-        }
-        pending &= ~m;
+template <int BINS> struct BinWindow {
+    long long b0;  // bin of window index 0 (may be negative)
+    __device__ explicit BinWindow(long long z) { b0 = (z >> kBinShift) - BINS / 2; }
+    // window index of target t's bin, -1 outside
+    __device__ int rel(long long t) const {
+        const long long r = (t >> kBinShift) - b0;
+        return r >= 0 && r < BINS ? (int)r : -1;
     }
-    return slot;
-}
+};
 
 // Pack the slots, convert the weights and record which slots carry a
-// positive weight (mask bit q).
+// positive weight (bit q of mask in 2D, of the packed record in 3D).
 template <int DIM, bool WIDE, typename TWin, typename TS, typename TA>
 __global__ __launch_bounds__(256) void k_compact(
     GridInfo g, const int16_t *__restrict__ off, const TWin *__restrict__ win,
@@ -309,15 +311,16 @@ __global__ __launch_bounds__(256) void k_compact(
     // a point whose slots do not fit the compact format keeps no edge
     // (zero weights, empty mask), so the operator stays symmetric and
     // its diagonal is not inflated by self-edges; the flag reports it
-    const bool packed = Slots<DIM, WIDE>::pack(s, sb, z);
-    if (!packed) st |= ADLBR_ST_RANGE;
+    double wq[S];
     unsigned m = 0;
     for (int q = 0; q < S; ++q) {
-        const double wq = packed ? (double)win[q * N + z] : 0.0;
-        w[widx<S>(q, z, N)] = Conv<TS, TA>::st((TA)wq);
-        if (wq > 0.0) m |= 1u << q;
+        wq[q] = (double)win[q * N + z];
+        if (wq[q] > 0.0) m |= 1u << q;
     }
-    mask[z] = (uint8_t)m;
+    const bool packed = Slots<DIM, WIDE>::pack(s, m, sb, z);
+    if (!packed) st |= ADLBR_ST_RANGE;
+    for (int q = 0; q < S; ++q) w[widx<S>(q, z, N)] = Conv<TS, TA>::st((TA)(packed ? wq[q] : 0.0));
+    if (DIM == 2) mask[z] = packed ? (uint8_t)m : (uint8_t)0;
     report(status, z, st);
 }
 
@@ -439,6 +442,14 @@ template <int DIM, bool WIDE> struct SlotKeys {
 // not merged, within the entries' 22-bit reach).
 template <int DIM> using lmask_t = std::conditional_t<DIM == 2, uint8_t, uint16_t>;
 
+// Slots of positive weight of the point whose packed record is v.
+template <int DIM, bool WIDE>
+__device__ __forceinline__ unsigned slot_mask(const typename Slots<DIM, WIDE>::store_t &v,
+                                              const uint8_t *mask, long long z) {
+    if constexpr (DIM == 2) return mask[z];
+    else return (unsigned)v.v[9];
+}
+
 // Number of merged edges of point z with listed edges lm (for the rare rows
 // whose count of incoming stencils is near its limit).
 template <int DIM, bool WIDE, bool PER>
@@ -447,47 +458,65 @@ __device__ inline int merged_count(const GridInfo &g, long long z, unsigned lm,
                                    const uint8_t *__restrict__ mask) {
     Slots<DIM, WIDE> sl;
     sl.load(sb, z);
+    const unsigned m = slot_mask<DIM, WIDE>(sb[z], mask, z);
     const Coord p = coords(z, g);
     int n = 0;
     for (int k = 0; k < (DIM == 2 ? 6 : 12); ++k) {
+        const int *o = sl.o[k >> 1];
         long long t;
-        if (((mask[z] >> (k >> 1)) & 1u) && !((lm >> k) & 1u) &&
-            edge_target<DIM, PER>(p, z, sl.o[k >> 1], k & 1 ? 1 : -1, g, t) &&
-            z - t < (1ll << 22) && z - t > -(1ll << 22))
+        if (((m >> (k >> 1)) & 1u) && !((lm >> k) & 1u) && (o[0] || o[1] || (DIM == 3 && o[2])) &&
+            edge_target<DIM, PER>(p, z, o, k & 1 ? 1 : -1, g, t) && z - t < (1ll << 22) &&
+            z - t > -(1ll << 22))
             ++n;
     }
     return n;
 }
 
+// Bins in the window of a 256-point block that counts its edges.
+constexpr int kCountBins = 1024;
+
 // Find the merged edges of every point, write the edge weights wm, the
 // listed-edge bits lmask and dsum = the own and partner weights of A_zz in
-// FP64.  An edge merges when its target lies in the grid unfolded, and its
-// offset is, up to sign, the offset of exactly one slot of positive weight at
-// both of its ends: both ends then come to the same decision.  Gathers 12
-// targets' slots a point in 3D (all in flight before any is used), about an
-// apply's worth of loads.  Without MG (no merging) only lmask, which may be
-// mask itself, and dsum where it is not null are written.
+// FP64; in 3D also count the listed edges of every bin of targets.  An edge
+// merges when its target lies in the grid unfolded, and its offset is, up to
+// sign, the offset of exactly one slot of positive weight at both of its ends:
+// both ends then come to the same decision.  The targets' slots are gathered
+// six at a time (half of a 3D point's: all twelve at once took 105 registers);
+// the pass waits for these gathers, then for the partners' weights.  160^3:
+// 297 us with the count of the bins in it (378 + 148 us apart).
+// Without MG (no merging) only lmask, which may be mask itself, and dsum
+// where it is not null are written, and edges whose offset components are all
+// within *hnear are left out of lmask (the near edges of the tiled layout).
 template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA>
 __global__ __launch_bounds__(256) void k_merge(
     GridInfo g, const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
-    const TS *__restrict__ w, const uint8_t *mask, void *__restrict__ wm, lmask_t<DIM> *lmask,
-    double *__restrict__ dsum, int32_t *status) {
-    constexpr int S = DIM == 2 ? 3 : 6;
+    const TS *__restrict__ w, const uint8_t *mask, const int32_t *__restrict__ hnear,
+    void *__restrict__ wm, lmask_t<DIM> *lmask, double *__restrict__ dsum,
+    uint32_t *__restrict__ bincnt, int32_t *status) {
+    constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
+    __shared__ uint32_t hist[DIM == 3 ? kCountBins : 1];
+    if (DIM == 3) {
+        for (int i = threadIdx.x; i < kCountBins; i += 256) hist[i] = 0;
+        __syncthreads();
+    }
     const long long blk = strip_block(xcd_block(blockIdx.x, gridDim.x), g, 256);
-    const long long z = wave_group(g, blk) + (threadIdx.x & 63);
-    const long long N = g.N;
-    if (z >= N) return;
+    const long long z0 = wave_group(g, blk), N = g.N;
+    const bool live = z0 + (threadIdx.x & 63) < N;
+    const long long z = live ? z0 + (threadIdx.x & 63) : 0;
+    typedef typename Slots<DIM, WIDE>::store_t store_t;
+    const store_t mine = sb[z];
     Slots<DIM, WIDE> sl;
-    sl.load(sb, z);
-    const unsigned m = mask[z];
+    sl.load(&mine, 0);
+    const unsigned m = slot_mask<DIM, WIDE>(mine, mask, z);
     TS wo[S];
 #pragma unroll
     for (int q = 0; q < S; ++q) wo[q] = w[widx<S>(q, z, N)];
     const Coord p = coords(z, g);
     const SlotKeys<DIM, WIDE> own(sl);
+    const int h = MG ? 0 : *hnear;
     int st = 0;
     unsigned okm = 0, cand = 0, listed = 0;
-    int tt[2 * S];
+    int tt[E];
 #pragma unroll
     for (int q = 0; q < S; ++q) {
         // the offset's only slot of positive weight (and no zero offset, whose
@@ -496,6 +525,10 @@ __global__ __launch_bounds__(256) void k_merge(
 #pragma unroll
         for (int r = 0; r < S; ++r)
             if (r != q) alone = alone && !(((m >> r) & 1u) && own.a[r] == own.a[q]);
+        int reach = max(abs(sl.o[q][0]), abs(sl.o[q][1]));
+        if (DIM == 3) reach = max(reach, abs(sl.o[q][DIM == 3 ? 2 : 0]));
+        // a 2D list leaves out zero offsets
+        const bool far = reach > h || (DIM == 3 && h == 0);
 #pragma unroll
         for (int k = 2 * q; k < 2 * q + 2; ++k) {
             const int sg = k & 1 ? 1 : -1;
@@ -514,140 +547,86 @@ __global__ __launch_bounds__(256) void k_merge(
             }
             okm |= (ok ? 1u : 0u) << k;
             cand |= (c ? 1u : 0u) << k;
-            listed |= (list ? 1u : 0u) << k;
-            tt[k] = c ? (int)t : (int)z;
+            listed |= (list && far ? 1u : 0u) << k;
+            tt[k] = ok ? (int)t : (int)z;
         }
     }
-    if constexpr (!MG) {
-        lmask[z] = (lmask_t<DIM>)listed;
-        if (dsum) {
-            double d = 0.0;
-#pragma unroll
-            for (int k = 0; k < 2 * S; ++k)
-                if ((okm >> k) & 1u) d += (double)Conv<TS, TA>::ld(wo[k >> 1]);
-            dsum[z] = d;
-        }
-        if (st) report(status, z, st);
-        return;
-    }
-    typename Slots<DIM, WIDE>::store_t raw[2 * S];
-    unsigned mt[2 * S];
-#pragma unroll
-    for (int k = 0; k < 2 * S; ++k) {
-        raw[k] = sb[tt[k]];
-        mt[k] = mask[tt[k]];
-    }
-    TS wp[2 * S];
-    unsigned merged = 0;
-#pragma unroll
-    for (int k = 0; k < 2 * S; ++k) {
-        Slots<DIM, WIDE> ts;
-        ts.load(&raw[k], 0);
-        const SlotKeys<DIM, WIDE> other(ts);
-        int hits = 0, slot = 0;
-#pragma unroll
-        for (int r = 0; r < S; ++r)
-            if (((mt[k] >> r) & 1u) && other.a[r] == own.a[k >> 1]) {
-                ++hits;
-                slot = r;
-            }
-        const bool hit = ((cand >> k) & 1u) && hits == 1;
-        merged |= (hit ? 1u : 0u) << k;
-        wp[k] = w[hit ? widx<S>(slot, tt[k], N) : widx<S>(0, z, N)];
-    }
-    listed &= ~merged;
-    MergedW<DIM, TS> mw;
     double d = 0.0;
+    if constexpr (!MG) {
 #pragma unroll
-    for (int i = 0; i < MergedW<DIM, TS>::BYTES / 4; ++i) mw.v[i] = 0u;
-    if constexpr (MergedW<DIM, TS>::SPLIT) {
+        for (int k = 0; k < E; ++k)
+            if ((okm >> k) & 1u) d += (double)Conv<TS, TA>::ld(wo[k >> 1]);
+    } else {
+        MergedW<DIM, TS> mw;
 #pragma unroll
-        for (int q = 0; q < S; ++q) mw.set(q, wo[q]);
-    }
+        for (int i = 0; i < MergedW<DIM, TS>::BYTES / 4; ++i) mw.v[i] = 0u;
+        if constexpr (MergedW<DIM, TS>::SPLIT) {
 #pragma unroll
-    for (int k = 0; k < 2 * S; ++k) {
-        const bool ok = (okm >> k) & 1u, hit = (merged >> k) & 1u;
-        const double wv = ok ? (double)Conv<TS, TA>::ld(wo[k >> 1]) : 0.0;
-        const double pv = hit ? (double)Conv<TS, TA>::ld(wp[k]) : 0.0;
-        d += wv + pv;
-        if constexpr (MergedW<DIM, TS>::SPLIT)
-            mw.set(S + k, ok ? (hit ? wp[k] : TS{}) : Conv<TS, float>::st(-1.0f));
-        else
-            mw.set(k, (TS)(wv + pv));
-    }
-    mw.store(wm, (int)z);
-    lmask[z] = (lmask_t<DIM>)listed;
-    dsum[z] = d;
-    if (st) report(status, z, st);
-}
-
-// The listed edges of point z, k = 2q + (sign > 0) in order: f(k, target)
-// with target -1 for an edge that is not listed (no bit in lmask, or near in
-// the tiled layout).
-template <int DIM, bool WIDE, bool PER, typename F>
-__device__ __forceinline__ void listed_edges(const GridInfo &g, long long z, bool live,
-                                             const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
-                                             const lmask_t<DIM> *__restrict__ lmask, int hnear, F f) {
-    constexpr int S = DIM == 2 ? 3 : 6;
-    const long long zi = live ? z : 0;
-    Slots<DIM, WIDE> sl;
-    sl.load(sb, zi);
-    const unsigned m = live ? lmask[zi] : 0u;
-    const Coord p = coords(zi, g);
+            for (int q = 0; q < S; ++q) mw.set(q, wo[q]);
+        }
+        unsigned merged = 0;
 #pragma unroll
-    for (int k = 0; k < 2 * S; ++k) {
-        const int q = k >> 1;
-        bool on = (m >> k) & 1u;
-        int reach = max(abs(sl.o[q][0]), abs(sl.o[q][1]));
-        if (DIM == 3) reach = max(reach, abs(sl.o[q][DIM == 3 ? 2 : 0]));
-        if (hnear > 0 && reach <= hnear) on = false;
-        long long t = -1;
-        if (on) on = edge_target<DIM, PER>(p, zi, sl.o[q], k & 1 ? 1 : -1, g, t);
-        f(k, on ? t : -1ll);
+        for (int b = 0; b < E; b += 6) {
+            store_t raw[6];
+            unsigned mt[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                raw[i] = sb[tt[b + i]];
+                mt[i] = DIM == 2 ? mask[tt[b + i]] : 0u;
+            }
+            TS wp[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const int k = b + i;
+                if (DIM == 3) mt[i] = slot_mask<DIM, WIDE>(raw[i], mask, 0);
+                Slots<DIM, WIDE> ts;
+                ts.load(&raw[i], 0);
+                const SlotKeys<DIM, WIDE> other(ts);
+                int hits = 0, slot = 0;
+#pragma unroll
+                for (int r = 0; r < S; ++r)
+                    if (((mt[i] >> r) & 1u) && other.a[r] == own.a[k >> 1]) {
+                        ++hits;
+                        slot = r;
+                    }
+                const bool hit = ((cand >> k) & 1u) && hits == 1;
+                merged |= (hit ? 1u : 0u) << k;
+                wp[i] = w[hit ? widx<S>(slot, tt[k], N) : widx<S>(0, z, N)];
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const int k = b + i;
+                const bool ok = (okm >> k) & 1u, hit = (merged >> k) & 1u;
+                const double wv = ok ? (double)Conv<TS, TA>::ld(wo[k >> 1]) : 0.0;
+                const double pv = hit ? (double)Conv<TS, TA>::ld(wp[i]) : 0.0;
+                d += wv + pv;
+                if constexpr (MergedW<DIM, TS>::SPLIT)
+                    mw.set(S + k, ok ? (hit ? wp[i] : TS{}) : Conv<TS, float>::st(-1.0f));
+                else
+                    mw.set(k, (TS)(wv + pv));
+            }
+        }
+        listed &= ~merged;
+        if (live) mw.store(wm, (int)z);
     }
-}
-
-// The bins of a block's edge targets lie near the block's own bin (offsets
-// are short against the grid), so both binning passes count them first in
-// an LDS window of kWinBins bins centred there: one global atomic per
-// window bin and block instead of one per bin, wavefront and edge slot,
-// which took the global counters of the busy bins out of contention.
-// Targets outside the window go to the global counters directly.
-constexpr int kWinBins = 2048;
-
-struct BinWindow {
-    long long b0;  // bin of window index 0 (may be negative)
-    __device__ explicit BinWindow(unsigned block) {
-        b0 = (((long long)block * kBS) >> kBinShift) - kWinBins / 2;
+    if (live) {
+        lmask[z] = (lmask_t<DIM>)listed;
+        if (MG || dsum) dsum[z] = d;
+        if (st) report(status, z, st);
     }
-    // window index of target t's bin, -1 outside (or no target)
-    __device__ int rel(long long t) const {
-        if (t < 0) return -1;
-        const long long r = (t >> kBinShift) - b0;
-        return r >= 0 && r < kWinBins ? (int)r : -1;
+    if constexpr (DIM == 3) {
+        const BinWindow<kCountBins> win(blk * 256);
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            if (live && ((listed >> k) & 1u)) {
+                const int r = win.rel(tt[k]);
+                if (r >= 0) atomicAdd(&hist[r], 1u);
+                else atomicAdd(&bincnt[tt[k] >> kBinShift], 1u);
+            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < kCountBins; i += 256)
+            if (hist[i]) atomicAdd(&bincnt[win.b0 + i], hist[i]);
     }
-};
-
-// Count the listed edges landing in each bin of targets.
-template <int DIM, bool WIDE, bool PER>
-__global__ __launch_bounds__(256) void k_bin_count(GridInfo g,
-                                                   const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
-                                                   const lmask_t<DIM> *__restrict__ lmask,
-                                                   const int32_t *__restrict__ hnear,
-                                                   uint32_t *__restrict__ bincnt) {
-    __shared__ uint32_t hist[kWinBins];
-    for (int i = threadIdx.x; i < kWinBins; i += 256) hist[i] = 0;
-    __syncthreads();
-    const BinWindow win(blockIdx.x);
-    const long long z = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    listed_edges<DIM, WIDE, PER>(g, z, z < g.N, sb, lmask, *hnear, [&](int, long long t) {
-        const int r = win.rel(t);
-        bin_append(r, hist, true);  // every lane
-        if (t >= 0 && r < 0) atomicAdd(&bincnt[t >> kBinShift], 1u);
-    });
-    __syncthreads();
-    for (int i = threadIdx.x; i < kWinBins; i += 256)
-        if (hist[i]) atomicAdd(&bincnt[win.b0 + i], hist[i]);
 }
 
 // Maximum of v over the wavefront, in every lane (all 64 lanes must call it).
@@ -813,68 +792,111 @@ __device__ inline double sort_row_diag(const GridInfo &g, long long z, int32_t *
     return d;
 }
 
-// Place every listed edge (target, entry) in its bin's region of binbuf
-// (the same edges as k_bin_count): the block counts its window bins in LDS,
-// reserves each bin's range with one global atomic, then places its edges
-// within the ranges by LDS cursors.  The order within a bin depends on
-// timing; k_bin_build sorts every row.
+// Place every listed edge (target, entry) in its bin's region of binbuf: a
+// block of kFillBS points numbers its edges within their window bins by LDS
+// counters, reserves each bin's range with one global atomic, and writes them.
+// The order within a bin depends on timing; k_bin_build sorts every row.
+// Plain LDS atomics, one pass over the edges: 160^3 96 us (343 us with the
+// wavefront's lanes grouped by bin, counted and then numbered in two passes).
+constexpr int kFillBS = 1024, kFillBins = 2048;
+
 template <int DIM, bool WIDE, bool PER>
-__global__ __launch_bounds__(256) void k_bin_fill(GridInfo g, const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
-                           const lmask_t<DIM> *__restrict__ lmask, const int32_t *__restrict__ hnear,
+__global__ __launch_bounds__(kFillBS) void k_bin_fill(GridInfo g, const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
+                           const lmask_t<DIM> *__restrict__ lmask,
                            const uint32_t *__restrict__ binoff, uint32_t *__restrict__ bincur,
                            int2 *__restrict__ binbuf) {
-    __shared__ uint32_t hist[kWinBins];  // counts, then cursors
-    __shared__ uint32_t base[kWinBins];  // the block's range start in each bin
-    for (int i = threadIdx.x; i < kWinBins; i += 256) hist[i] = 0;
+    constexpr int E = DIM == 2 ? 6 : 12;
+    __shared__ uint32_t hist[kFillBins];  // counts, then the block's start in each bin's region
+    for (int i = threadIdx.x; i < kFillBins; i += kFillBS) hist[i] = 0;
     __syncthreads();
-    const BinWindow win(blockIdx.x);
-    const long long z = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int hn = *hnear;
-    listed_edges<DIM, WIDE, PER>(g, z, z < g.N, sb, lmask, hn, [&](int, long long t) {
-        bin_append(win.rel(t), hist, true);  // every lane
-    });
-    __syncthreads();
-    for (int i = threadIdx.x; i < kWinBins; i += 256) {
-        const uint32_t c = hist[i];
-        base[i] = c ? atomicAdd(&bincur[win.b0 + i], c) : 0u;
-        hist[i] = 0;
+    const long long zb = (long long)blockIdx.x * kFillBS;
+    const BinWindow<kFillBins> win(zb);
+    const bool live = zb + threadIdx.x < g.N;
+    const long long z = live ? zb + threadIdx.x : 0;
+    Slots<DIM, WIDE> sl;
+    sl.load(sb, z);
+    const unsigned m = live ? lmask[z] : 0u;
+    const Coord p = coords(z, g);
+    int tt[E];
+    unsigned slot[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        long long t = 0;
+        edge_target<DIM, PER>(p, z, sl.o[k >> 1], k & 1 ? 1 : -1, g, t);
+        tt[k] = (int)t;
+        slot[k] = 0;
+        if ((m >> k) & 1u) {
+            const int r = win.rel(t);
+            slot[k] = r >= 0 ? atomicAdd(&hist[r], 1u) : atomicAdd(&bincur[t >> kBinShift], 1u);
+        }
     }
     __syncthreads();
-    listed_edges<DIM, WIDE, PER>(g, z, z < g.N, sb, lmask, hn, [&](int k, long long t) {
-        const int r = win.rel(t);
-        const int far = t >= 0 && r < 0 ? (int)(t >> kBinShift) : -1;
-        const unsigned near_slot = bin_append(r, hist, false);   // every lane
-        const unsigned far_slot = bin_append(far, bincur, false);  // every lane
-        if (t >= 0) {
-            const long long bin = t >> kBinShift;
-            const unsigned slot = r >= 0 ? base[r] + near_slot : far_slot;
-            const int32_t e = (int32_t)(((z - t) << 9) | ((k >> 1) << 6) | (t & 63));
-            binbuf[(long long)binoff[bin] + slot] = make_int2((int)t, e);
+    for (int i = threadIdx.x; i < kFillBins; i += kFillBS) {
+        const uint32_t c = hist[i];
+        if (c) hist[i] = binoff[win.b0 + i] + atomicAdd(&bincur[win.b0 + i], c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+        if ((m >> k) & 1u) {
+            const int t = tt[k], r = win.rel(t);
+            const uint32_t at = (r >= 0 ? hist[r] : binoff[t >> kBinShift]) + slot[k];
+            binbuf[at] = make_int2(t, (int32_t)((((int)z - t) * 512) | ((k >> 1) << 6) | (t & 63)));
         }
-    });
 }
 
-// One block per bin: per-target counts and offsets in LDS, entries placed at
-// their row, rows sorted by (source, slot), diagonal A_zz = own and merged
-// weights (dsum) + listed weights, and the maximum diagonal.
+// One block per bin: entries ranked in their target's row and counted by LDS
+// counters, rows placed in LDS (in ent where the bin has more than fit),
+// sorted by (source, slot) and stored with their weights; diagonal A_zz = own
+// and merged weights (dsum) + listed weights, and the maximum diagonal.  The
+// bin's entries are read once: each thread keeps its first kKeep with their
+// ranks in registers.  ent is written back only where it is read later (not
+// with FP32's packed records).  Bound by the gathers of the entries' weights
+// and the sorts: 160^3 247 us (385 us with the rows placed in ent).
+constexpr int kStage = 6144;  // entries a bin holds in LDS (24 KB): twice a usual bin's
 template <int DIM, bool WIDE, bool PER, typename TS, typename TA, typename TD>
 __global__ __launch_bounds__(256) void k_bin_build(
     GridInfo g, const uint32_t *__restrict__ bincnt, const uint32_t *__restrict__ binoff,
     const int2 *__restrict__ binbuf, const TS *__restrict__ w, const double *__restrict__ dsum,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const uint8_t *__restrict__ mask,
-    const lmask_t<DIM> *__restrict__ lmask, int32_t *__restrict__ pos, int32_t *__restrict__ ent, EntRec<TS> *__restrict__ went, TD *__restrict__ diag,
+    const lmask_t<DIM> *__restrict__ lmask, int merged, int32_t *__restrict__ pos,
+    int32_t *__restrict__ ent, EntRec<TS> *__restrict__ went, TD *__restrict__ diag,
     double *__restrict__ dpart, int32_t *status) {
+    constexpr int kKeep = 24;  // kStage / 256
     __shared__ int32_t lcnt[kBin];
     __shared__ int32_t loff[kBin];
     __shared__ int32_t scan[256];
+    __shared__ int32_t rows[kStage];
     const long long N = g.N;
     const long long b = blockIdx.x;
     const long long t0 = b << kBinShift;
     const long long base = binoff[b];
     const unsigned E = bincnt[b];
+    const bool staged = E <= (unsigned)kStage;  // block-uniform
     for (int k = threadIdx.x; k < kBin; k += 256) lcnt[k] = 0;
     __syncthreads();
-    for (unsigned e = threadIdx.x; e < E; e += 256) atomicAdd(&lcnt[binbuf[base + e].x - t0], 1);
+    // entry, and (target within the bin, rank in its row) of the first kKeep
+    int32_t key[kKeep];
+    uint32_t at[kKeep];
+#pragma unroll
+    for (int i0 = 0; i0 < kKeep; i0 += 8) {
+        if (256u * i0 >= E) break;  // block-uniform
+        int2 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned e = threadIdx.x + 256u * (i0 + i);
+            v[i] = binbuf[base + (e < E ? e : 0u)];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned e = threadIdx.x + 256u * (i0 + i);
+            const uint32_t tl = (uint32_t)(v[i].x - (int)t0);
+            key[i0 + i] = v[i].y;
+            at[i0 + i] = e < E ? tl | (uint32_t)atomicAdd(&lcnt[tl], 1) << 16 : 0u;
+        }
+    }
+    for (unsigned e = threadIdx.x + 256u * kKeep; e < E; e += 256)
+        atomicAdd(&lcnt[binbuf[base + e].x - t0], 1);
     __syncthreads();
     // exclusive scan of the clamped counts (4 per thread)
     int32_t c4[4], sum = 0;
@@ -899,20 +921,31 @@ __global__ __launch_bounds__(256) void k_bin_build(
         if (t < N) {
             pos[t] = (int32_t)(base + run);
             // every stencil that reaches t counts, listed or merged
-            if (c4[k] > 255 || (c4[k] + 12 > 255 &&
+            if (c4[k] > 255 || (merged && c4[k] + 12 > 255 &&
                                 c4[k] + merged_count<DIM, WIDE, PER>(g, t, lmask[t], sb, mask) > 255))
                 report(status, t, ADLBR_ST_INCOMING);
         }
         run += min(c4[k], 255);
         if (t == N - 1) pos[N] = (int32_t)(base + run);  // total entry count
-        lcnt[tl] = 0;  // becomes the placement cursor
     }
     __syncthreads();
-    for (unsigned e = threadIdx.x; e < E; e += 256) {
-        const int2 v = binbuf[base + e];
-        const int tl = v.x - (int)t0;
-        const int k = atomicAdd(&lcnt[tl], 1);
-        if (k < 255) ent[base + loff[tl] + k] = v.y;
+    if (staged) {
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) {
+            if (256u * i >= E) break;  // block-uniform
+            const uint32_t tl = at[i] & 0xffffu, k = at[i] >> 16;
+            if (threadIdx.x + 256u * i < E && k < 255u) rows[loff[tl] + k] = key[i];
+        }
+    } else {
+        // more entries than LDS holds: ranked again, into ent
+        for (int k = 0; k < 4; ++k) lcnt[threadIdx.x * 4 + k] = 0;
+        __syncthreads();
+        for (unsigned e = threadIdx.x; e < E; e += 256) {
+            const int2 v = binbuf[base + e];
+            const int tl = v.x - (int)t0;
+            const int k = atomicAdd(&lcnt[tl], 1);
+            if (k < 255) ent[base + loff[tl] + k] = v.y;
+        }
     }
     // Rows clamped at 255 entries (flagged above) leave the bin's region
     // [base + clamped total, base + E) unwritten, and the apply reads it as
@@ -932,10 +965,16 @@ __global__ __launch_bounds__(256) void k_bin_build(
         const int c = min(lcnt[tl], 255);  // 0 past the grid
         const int cw = wave_max_i(c);      // all lanes
         if (z >= N) continue;
-        const double d = sort_row_diag<DIM, TS, TA>(g, z, ent + base + loff[tl], c, cw, dsum[z], w,
-                                                    went + base + loff[tl]);
+        const int lo = loff[tl];
+        // two calls, so that the staged one addresses LDS directly
+        const double d = staged ? sort_row_diag<DIM, TS, TA>(g, z, rows + lo, c, cw, dsum[z], w, went + base + lo)
+                                : sort_row_diag<DIM, TS, TA>(g, z, ent + base + lo, c, cw, dsum[z], w, went + base + lo);
         diag[z] = (TD)d;
         dmax = fmax(dmax, d);
+    }
+    if (staged && !kPackedEW<TS>) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < clamped_total; i += 256) ent[base + i] = rows[i];
     }
     block_partial_max(dmax, dpart);
 }
@@ -992,7 +1031,7 @@ template <bool PER> __device__ inline Window window_axis(int t0, int tw, int R, 
 template <bool WIDE, bool PER, typename F>
 __device__ inline void tile_edges(const GridInfo &g, int x0, int y0, int tw, int th, int stride,
                                   int R, const typename Slots<2, WIDE>::store_t *__restrict__ sb,
-                                  const lmask_t<2> *__restrict__ lmask, int hnear, F f) {
+                                  const lmask_t<2> *__restrict__ lmask, F f) {
     const Window wx = window_axis<PER>(x0, tw, R, g.nx);
     const Window wy = window_axis<PER>(y0, th, R, g.ny);
     const long long W = (long long)wx.len * wy.len;
@@ -1010,7 +1049,6 @@ __device__ inline void tile_edges(const GridInfo &g, int x0, int y0, int tw, int
         const Coord p{x, y, 0};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            if (max(abs(sl.o[q][0]), abs(sl.o[q][1])) <= hnear) continue;  // near (tiled)
 #pragma unroll
             for (int sg = -1; sg <= 1; sg += 2) {
                 if (!(m & (1u << (2 * q + (sg > 0))))) continue;
@@ -1031,16 +1069,14 @@ __device__ inline void tile_edges(const GridInfo &g, int x0, int y0, int tw, int
 
 // The listed edges (bits m) of source (x, y) into the rectangle
 // [x0, x0 + tw) x [y0, y0 + th) (Neumann grid): f(local index, target, entry,
-// source, edge index 2q + (sign > 0)).  Edges whose offset components are all
-// <= hnear (near edges of the tiled layout) are left out.
+// source, edge index 2q + (sign > 0)).
 template <bool WIDE, typename F>
 __device__ inline void source_edges_of(const GridInfo &g, int x, int y, const Slots<2, WIDE> &sl,
                                        unsigned m, int x0, int y0, int tw, int th, int stride,
-                                       int hnear, F f) {
+                                       F f) {
     const long long z = x + (long long)g.nx * y;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        if (max(abs(sl.o[q][0]), abs(sl.o[q][1])) <= hnear) continue;
 #pragma unroll
         for (int sg = -1; sg <= 1; sg += 2) {
             if (!(m & (1u << (2 * q + (sg > 0))))) continue;
@@ -1063,7 +1099,7 @@ __device__ inline void brick_pass(const GridInfo &g, int x0, int y0, int tw, int
                                   const int32_t *__restrict__ brmax,
                                   const typename Slots<2, WIDE>::store_t *__restrict__ sb,
                                   const lmask_t<2> *__restrict__ lmask, int32_t *list, int32_t *nlist,
-                                  int hnear, F f) {
+                                  F f) {
     const int nbx = (g.nx + kBrick - 1) / kBrick;
     if (threadIdx.x == 0) *nlist = 0;
     __syncthreads();
@@ -1105,7 +1141,7 @@ __device__ inline void brick_pass(const GridInfo &g, int x0, int y0, int tw, int
 #pragma unroll
         for (int j = 0; j < G; ++j)
             if (m[j])
-                source_edges_of<WIDE>(g, xs[j], ys[j], sl[j], m[j], x0, y0, tw, th, stride, hnear, f);
+                source_edges_of<WIDE>(g, xs[j], ys[j], sl[j], m[j], x0, y0, tw, th, stride, f);
     }
     __syncthreads();
 }
@@ -1123,11 +1159,10 @@ __device__ inline void tile_sources(const GridInfo &g, int x0, int y0, int tw, i
                                     int R, const int32_t *__restrict__ trmax,
                                     const int32_t *__restrict__ brmax,
                                     const typename Slots<2, WIDE>::store_t *__restrict__ sb,
-                                    const lmask_t<2> *__restrict__ lmask, int32_t *list, int hnear,
-                                    F f) {
+                                    const lmask_t<2> *__restrict__ lmask, int32_t *list, F f) {
     static_assert(CAP >= (kTile / kBrick) * (kTile / kBrick), "a tile's bricks fit the list");
     if (PER) {
-        tile_edges<WIDE, PER>(g, x0, y0, tw, th, stride, R, sb, lmask, hnear, f);
+        tile_edges<WIDE, PER>(g, x0, y0, tw, th, stride, R, sb, lmask, f);
         return;
     }
     int32_t *nlist = list + CAP;
@@ -1137,7 +1172,7 @@ __device__ inline void tile_sources(const GridInfo &g, int x0, int y0, int tw, i
         const long long nc = (long long)(bxb - bxa + 1) * (byb - bya + 1);
         if (nc <= CAP) {
             brick_pass<WIDE>(g, x0, y0, tw, th, stride, bxa, bya, bxb - bxa + 1, byb - bya + 1,
-                             brmax, sb, lmask, list, nlist, hnear, f);
+                             brmax, sb, lmask, list, nlist, f);
             return;
         }
     }
@@ -1153,7 +1188,7 @@ __device__ inline void tile_sources(const GridInfo &g, int x0, int y0, int tw, i
             if (ax >= bx || ay >= by) continue;
             const int bxa = ax / kBrick, bya = ay / kBrick;
             brick_pass<WIDE>(g, x0, y0, tw, th, stride, bxa, bya, (bx - 1) / kBrick - bxa + 1,
-                             (by - 1) / kBrick - bya + 1, brmax, sb, lmask, list, nlist, hnear, f);
+                             (by - 1) / kBrick - bya + 1, brmax, sb, lmask, list, nlist, f);
         }
 }
 
@@ -1218,7 +1253,6 @@ __global__ __launch_bounds__(256) void k_tile_count(GridInfo g,
                                                     const int32_t *__restrict__ Rp,
                                                     const int32_t *__restrict__ trmax,
                                                     const int32_t *__restrict__ brmax,
-                                                    const int32_t *__restrict__ hnear,
                                                     uint8_t *__restrict__ cnt,
                                                     uint8_t *__restrict__ rank, int32_t *status) {
     __shared__ int32_t lc[kTile * kTile];
@@ -1231,7 +1265,7 @@ __global__ __launch_bounds__(256) void k_tile_count(GridInfo g,
     __syncthreads();
     const long long N = g.N;
     tile_sources<WIDE, PER, CAP>(g, x0, y0, tw, th, kTile, *Rp, trmax, brmax, sb, lmask, list,
-                                 *hnear, [&](int tl, long long, int32_t, long long z, int k) {
+                                 [&](int tl, long long, int32_t, long long z, int k) {
                                      const int r = atomicAdd(&lc[tl], 1);
                                      rank[k * N + z] = (uint8_t)min(r, 255);
                                  });
@@ -1305,10 +1339,8 @@ __global__ __launch_bounds__(256) void k_place2d(GridInfo g,
                                                  const lmask_t<2> *__restrict__ lmask,
                                                  const uint8_t *__restrict__ rank,
                                                  const int32_t *__restrict__ pos,
-                                                 const int32_t *__restrict__ hnear,
                                                  int32_t *__restrict__ ent) {
     const long long N = g.N;
-    const int h = *hnear;
     const long long z = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (z >= N) return;
     Slots<2, WIDE> sl;
@@ -1330,7 +1362,6 @@ __global__ __launch_bounds__(256) void k_place2d(GridInfo g,
         for (int k = 0; k < 2; ++k) {
             long long t = z;
             bool v = (m >> (2 * q + k)) & 1u;
-            v = v && max(abs(sl.o[q][0]), abs(sl.o[q][1])) > h;  // near edges (tiled) unlisted
             v = v && edge_target<2, PER>(p, z, sl.o[q], k ? 1 : -1, g, t);
             v = v && rk[2 * q + k] != 255;
             ok[2 * q + k] = v;
@@ -1423,16 +1454,10 @@ __global__ __launch_bounds__(256) void k_rows(GridInfo g,
     block_partial_max(dmax, dpart);
 }
 
-__global__ void k_copy_u32(const uint32_t *a, uint32_t *b, long long n) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = a[i];
-}
-
-
-// In-place exclusive scan of bsum[0 .. nb) by one block of 256 threads:
-// 4096 values a round, 16 consecutive ones per thread (one round covers the
-// chunk sums of a 2048^2 grid).
-__global__ __launch_bounds__(256) void k_scan_top(int32_t *bsum, long long nb) {
+// Exclusive scan of in[0 .. nb) into out (which may be in) by one block of
+// 256 threads: 4096 values a round, 16 consecutive ones per thread (one round
+// covers the chunk sums of a 2048^2 grid).
+__global__ __launch_bounds__(256) void k_scan_top(const int32_t *in, int32_t *out, long long nb) {
     constexpr int V = 16;
     __shared__ int32_t lds[256];
     int32_t carry = 0;
@@ -1441,25 +1466,27 @@ __global__ __launch_bounds__(256) void k_scan_top(int32_t *bsum, long long nb) {
         int32_t v[V], sum = 0;
 #pragma unroll
         for (int k = 0; k < V; ++k) {
-            v[k] = i0 + k < nb ? bsum[i0 + k] : 0;
+            v[k] = i0 + k < nb ? in[i0 + k] : 0;
             sum += v[k];
         }
         int32_t total;
         int32_t run = carry + block_excl_scan256(sum, lds, total);
 #pragma unroll
         for (int k = 0; k < V; ++k) {
-            if (i0 + k < nb) bsum[i0 + k] = run;
+            if (i0 + k < nb) out[i0 + k] = run;
             run += v[k];
         }
         carry += total;
     }
 }
 
-// dt_CFL = 1 / max_z A_zz from the per-block maxima.
+// dt_CFL = 1 / max_z A_zz from the per-block maxima; the end of an assembly
+// also settles the status word.
 __global__ __launch_bounds__(256) void k_cfl(const double *dpart, long long nb, double *maxdiag,
-                                             double *dtcfl) {
+                                             double *dtcfl, int32_t *status) {
     const double m = reduce_partials(dpart, nb, true);
     if (threadIdx.x != 0) return;
+    if (status[0] == 0x7fffffff) status[0] = -1;
     *maxdiag = m;
     *dtcfl = m > 0.0 ? 1.0 / m : 0.0;
 }
@@ -2432,26 +2459,16 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
     const unsigned nbb = (unsigned)((nbins + kBS - 1) / kBS);
     TS *w = (TS *)op->w;
     store_t *sb = (store_t *)op->sb;
+    hipLaunchKernelGGL(k_build_init, dim3(DIM == 3 ? nbb : 1), dim3(256), 0, s, status, op->hnear,
+                       op->bincnt, op->bincur, DIM == 3 ? nbins : 0ll);
     if (win_f64)
         hipLaunchKernelGGL((k_compact<DIM, WIDE, double, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
                            off, (const double *)win, sb, w, op->mask, status);
     else
         hipLaunchKernelGGL((k_compact<DIM, WIDE, float, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
                            off, (const float *)win, sb, w, op->mask, status);
-    // the tiled layout keeps every edge apart (its step finds the near ones
-    // from their sources)
-    lmask_t<DIM> *lmask = (lmask_t<DIM> *)op->lmask;
-    if (MG && !op->tiled)
-        hipLaunchKernelGGL((k_merge<DIM, WIDE, PER, MG, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
-                           (const store_t *)sb, (const TS *)w, (const uint8_t *)op->mask, op->wp,
-                           lmask, op->dsum, status);
-    else
-        hipLaunchKernelGGL((k_merge<DIM, WIDE, PER, false, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
-                           (const store_t *)sb, (const TS *)w, (const uint8_t *)op->mask, nullptr,
-                           lmask, op->dsum, status);
-    // the halo of the near edges (tiled layout) or 0
+    // the halo of the near edges (tiled layout; 0 otherwise)
     constexpr bool kTiledOk = !PER && sizeof(TS) <= 4;
-    bool tiled_params = false;
     if constexpr (kTiledOk) {
         if (op->tiled) {
             hipLaunchKernelGGL((k_reach_wmax<DIM, WIDE, TS>), dim3(nb), dim3(256), 0, s, g,
@@ -2459,10 +2476,19 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
             hipLaunchKernelGGL(k_tile_params, dim3(1), dim3(256), 0, s, (const double *)op->rpart,
                                (const double *)op->part, (long long)nb, Tile<DIM>::HMAX,
                                op->hnear, op->wmax);
-            tiled_params = true;
         }
     }
-    if (!tiled_params) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, op->hnear, 1ll, 0);
+    // the tiled layout keeps every edge apart (its step finds the near ones
+    // from their sources)
+    lmask_t<DIM> *lmask = (lmask_t<DIM> *)op->lmask;
+    if (MG && !op->tiled)
+        hipLaunchKernelGGL((k_merge<DIM, WIDE, PER, MG, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
+                           (const store_t *)sb, (const TS *)w, (const uint8_t *)op->mask,
+                           (const int32_t *)op->hnear, op->wp, lmask, op->dsum, op->bincnt, status);
+    else
+        hipLaunchKernelGGL((k_merge<DIM, WIDE, PER, false, TS, TA>), dim3(nb), dim3(kBS), 0, s, g,
+                           (const store_t *)sb, (const TS *)w, (const uint8_t *)op->mask,
+                           (const int32_t *)op->hnear, nullptr, lmask, op->dsum, op->bincnt, status);
     long long nparts;
     if constexpr (DIM == 2) {
         const int ntx = (g.nx + kTile - 1) / kTile, nty = (g.ny + kTile - 1) / kTile;
@@ -2477,17 +2503,18 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
                            (const typename Slots<2, WIDE>::store_t *)op->sb, (const lmask_t<DIM> *)lmask,
                            (const uint8_t *)op->mask, op->merged, (const int32_t *)op->rmax,
                            (const int32_t *)op->trmax, (const int32_t *)op->brmax,
-                           (const int32_t *)op->hnear, op->cnt, op->rank,
+                           op->cnt, op->rank,
                            status);
         hipLaunchKernelGGL(k_chunk_sum, dim3(nchunk), dim3(256), 0, s, (const uint8_t *)op->cnt, N,
                            (int32_t *)op->bincnt);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, (int32_t *)op->bincnt, nbins);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, (const int32_t *)op->bincnt,
+                           (int32_t *)op->bincnt, nbins);
         hipLaunchKernelGGL(k_chunk_pos, dim3(nchunk), dim3(256), 0, s, (const uint8_t *)op->cnt, N,
                            (const int32_t *)op->bincnt, op->pos);
         hipLaunchKernelGGL((k_place2d<WIDE, PER>), dim3(nb), dim3(256), 0, s, g,
                            (const typename Slots<2, WIDE>::store_t *)op->sb,
                            (const lmask_t<DIM> *)lmask, (const uint8_t *)op->rank,
-                           (const int32_t *)op->pos, (const int32_t *)op->hnear, op->ent);
+                           (const int32_t *)op->pos, op->ent);
         if (op->storage == ADLBR_F64)
             hipLaunchKernelGGL((k_rows<DIM, WIDE, PER, MG, TS, TA, double>), dim3(nb), dim3(256), 0, s,
                                g, (const store_t *)sb, (const TS *)w, (const double *)op->dsum, (const uint8_t *)op->cnt,
@@ -2500,27 +2527,24 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
                                op->part);
         nparts = nb;
     } else {
-        hipLaunchKernelGGL(k_fill_i32, dim3(nbb), dim3(kBS), 0, s, (int32_t *)op->bincnt, nbins, 0);
-        hipLaunchKernelGGL(k_fill_i32, dim3(nbb), dim3(kBS), 0, s, (int32_t *)op->bincur, nbins, 0);
-        hipLaunchKernelGGL((k_bin_count<DIM, WIDE, PER>), dim3(nb), dim3(kBS), 0, s, g,
-                           (const store_t *)sb, (const lmask_t<DIM> *)lmask, (const int32_t *)op->hnear,
-                           op->bincnt);
-        hipLaunchKernelGGL(k_copy_u32, dim3(nbb), dim3(kBS), 0, s, op->bincnt, op->binoff, nbins);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, (int32_t *)op->binoff, nbins);
-        hipLaunchKernelGGL((k_bin_fill<DIM, WIDE, PER>), dim3(nb), dim3(kBS), 0, s, g,
-                           (const store_t *)sb, (const lmask_t<DIM> *)lmask, (const int32_t *)op->hnear,
-                           op->binoff, op->bincur, op->binbuf);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, (const int32_t *)op->bincnt,
+                           (int32_t *)op->binoff, nbins);
+        hipLaunchKernelGGL((k_bin_fill<DIM, WIDE, PER>), dim3((unsigned)((N + kFillBS - 1) / kFillBS)),
+                           dim3(kFillBS), 0, s, g, (const store_t *)sb,
+                           (const lmask_t<DIM> *)lmask, op->binoff, op->bincur, op->binbuf);
         if (op->storage == ADLBR_F64)
             hipLaunchKernelGGL((k_bin_build<DIM, WIDE, PER, TS, TA, double>), dim3((unsigned)nbins),
                                dim3(256), 0, s, g, op->bincnt, op->binoff, op->binbuf,
                                (const TS *)w, (const double *)op->dsum, (const store_t *)sb,
-                               (const uint8_t *)op->mask, (const lmask_t<DIM> *)lmask, op->pos, op->ent, (EntRec<TS> *)op->went, (double *)op->diag, op->part,
+                               (const uint8_t *)op->mask, (const lmask_t<DIM> *)lmask, op->merged,
+                               op->pos, op->ent, (EntRec<TS> *)op->went, (double *)op->diag, op->part,
                                status);
         else
             hipLaunchKernelGGL((k_bin_build<DIM, WIDE, PER, TS, TA, float>), dim3((unsigned)nbins),
                                dim3(256), 0, s, g, op->bincnt, op->binoff, op->binbuf,
                                (const TS *)w, (const double *)op->dsum, (const store_t *)sb,
-                               (const uint8_t *)op->mask, (const lmask_t<DIM> *)lmask, op->pos, op->ent, (EntRec<TS> *)op->went, (float *)op->diag, op->part,
+                               (const uint8_t *)op->mask, (const lmask_t<DIM> *)lmask, op->merged,
+                               op->pos, op->ent, (EntRec<TS> *)op->went, (float *)op->diag, op->part,
                                status);
         nparts = nbins;
     }
@@ -2537,7 +2561,7 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
         }
     }
     hipLaunchKernelGGL(k_cfl, dim3(1), dim3(256), 0, s, (const double *)op->part, nparts,
-                       op->maxdiag, op->dtcfl);
+                       op->maxdiag, op->dtcfl, status);
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
 }
@@ -2776,7 +2800,7 @@ Layout layout(const GridInfo &g, int storage, int wide, int merged, int records)
     L.went = o; o += full ? align_up((dtype_size(storage) == 4 ? 8 : dtype_size(storage)) * (size_t)(2 * S) * N) : 0;
     L.diag = o; o += align_up((storage == ADLBR_F64 ? 8 : 4) * (size_t)N);
     L.scal = o; o += 256;
-    L.mask = o; o += align_up((size_t)N + 64);
+    L.mask = o; o += g.dim == 2 ? align_up((size_t)N + 64) : 0;
     // without merging the listed edges of a 2D point replace its mask in place
     L.lmask = full ? o : L.mask;
     o += full ? align_up((g.dim == 2 ? 1 : 2) * (size_t)N) : 0;
@@ -2997,9 +3021,7 @@ extern "C" int adlbr_operator_create(const adlbr_grid *g, const int16_t *offsets
     op->binoff = (uint32_t *)(b + L.binoff);
     op->binbuf = (int2 *)(b + L.binbuf);
     hipStream_t s = as_stream(stream);
-    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(1), 0, s, status);
     rc = dispatch<BuildF>(op, offsets, weights, (int)(w_dtype == ADLBR_F64), status, s);
-    hipLaunchKernelGGL(k_status_final, dim3(1), dim3(1), 0, s, status);
     if (rc) {
         delete op;
         return rc;
@@ -3022,9 +3044,7 @@ extern "C" int adlbr_operator_rebuild(adlbr_operator *op, const int16_t *offsets
         return ADLBR_E_INVALID;
     }
     hipStream_t s = as_stream(stream);
-    hipLaunchKernelGGL(k_status_init, dim3(1), dim3(1), 0, s, status);
     const int rc = dispatch<BuildF>(op, offsets, weights, (int)(w_dtype == ADLBR_F64), status, s);
-    hipLaunchKernelGGL(k_status_final, dim3(1), dim3(1), 0, s, status);
     if (rc) return rc;
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;

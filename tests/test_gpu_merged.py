@@ -112,3 +112,32 @@ def _edge_weights(dims, off, w, periodic=False, reflect=False):
             tgt.append(lin[ok])
             wt.append(w[q][ok])
     return np.concatenate(src), np.concatenate(tgt), np.concatenate(wt)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("spread", [1, 6])
+def test_unpaired_edges_fill_the_bins(dtype, spread):
+    """Every point its own random offsets: nearly nothing merges, and bins of
+    1024 targets receive up to 12 entries a target, more than a block holds in
+    LDS (spread 6) or about as many (spread 1: short offsets often meet)."""
+    import torch
+    import paper_1301_3925_amd as adlbr
+    dims = (40, 16, 8)
+    n = int(np.prod(dims))
+    td = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    rng = np.random.default_rng(spread)
+    a, b, c = rng.integers(-spread, spread + 1, size=(3, n, 3))
+    off = np.stack([a, b, c, -(a + b), a - c, b + c]).transpose(0, 2, 1).astype(np.int16)
+    off = np.ascontiguousarray(off)
+    w = torch.from_numpy(rng.uniform(0.1, 1.0, (6, n)).astype(np.float32)).cuda()
+    u = torch.from_numpy(rng.uniform(-1, 1, n)).to(td).cuda()
+    op = adlbr.Operator(dims, torch.from_numpy(off).cuda(), w, storage=td)
+    held = w.to(td).double().cpu().numpy() * ~(off == 0).all(1)
+    A = oracle.operator_matrix(dims, off, held)
+    uh = u.double().cpu().numpy()
+    ref, mag = A @ uh, abs(A) @ abs(uh)
+    eps = 2.0 ** -53 if dtype == "f64" else 2.0 ** -24
+    out = 2.0 ** -8 if dtype == "bf16" else 0.0
+    tol = 4 * (np.diff(A.indptr) * 2 + 8) * eps * mag * (1 + out) + out * abs(ref)
+    got = op.apply(u).double().cpu().numpy()
+    assert np.all(abs(got - ref) <= tol), float((abs(got - ref) - tol).max())
