@@ -2,9 +2,9 @@
 // N = B^T diag(g2) B, B = C2 diag(g1) C1 (symmetric positive semi-definite):
 // features, gate net, the convolution stack on r, its backward pass, the
 // energy loss and Adam -- everything the network needs to be trained and
-// applied on the GPU.  These are FP32 kernels (one thread per grid point,
-// uniform weight reads); the 2D inference path used inside flexible CG has
-// a fused BF16 MFMA kernel in cnn_mfma.hip.
+// applied on the GPU.  These kernels are FP32 throughout (the convolutions and
+// weight gradients on FP32 matrix instructions); the inference path used
+// inside flexible CG has BF16 MFMA kernels in cnn_mfma.hip.
 //
 // N runs as a plain four-layer gated stack: the gate net writes expanded
 // gates [g1, g2, g1, 1] and adlbr_net_gates expands the weights to
@@ -169,44 +169,197 @@ __global__ void k_features(GridInfo g, const TD *diag, const float *w, const voi
 }
 
 // ------------------------------------------------------- convolutions --
-// out[co] = epi(sum_{t, ci} W[co][ci][t] * in_ci(p + off_t) (+ bias[co]))
-// with in_ci = in[ci] * (in_gate ? in_gate[ci] : 1); epilogue: keep the
-// pre-activation in `pre` (if given), multiply by gate[co] (if given),
-// ReLU (if relu).
-template <int DIM, int CIN, int COUT>
-__global__ __launch_bounds__(kBS) void k_conv(GridInfo g, const float *__restrict__ in,
-                                              const float *__restrict__ in_gate,
-                                              const float *__restrict__ W,
-                                              const float *__restrict__ bias,
-                                              float *__restrict__ out, float *__restrict__ pre,
-                                              const float *__restrict__ gate, int relu) {
-    constexpr int T = DIM == 2 ? 9 : 27;
-    const float *sw = W;  // uniform addresses: read through the scalar cache
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
-    const long long N = g.N;
-    if (i >= N) return;
-    const Pt p = coord_of(i, g);
-    float acc[COUT];
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) acc[co] = bias ? bias[co] : 0.f;
-    for (int t = 0; t < T; ++t) {
-        const long long q = tap_nb<DIM>(p, i, t, g);
-        if (q < 0) continue;
-#pragma unroll 4
-        for (int ci = 0; ci < CIN; ++ci) {
-            float x = in[ci * N + q];
-            if (in_gate) x *= in_gate[ci * N + q];
-#pragma unroll
-            for (int co = 0; co < COUT; ++co) acc[co] += sw[(co * CIN + ci) * T + t] * x;
-        }
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+// Tiles of points of the convolution kernels, and the staged region (tile and
+// a one-point halo): long in x, so that the planes are read and written in
+// whole lines (16 -> 16 channels at 1024^2 with 16 x 16 tiles: 155 us).  CS,
+// the LDS stride of a channel's plane, puts the four k-groups of an operand
+// read on different banks.
+template <int DIM> struct ConvTile;
+template <> struct ConvTile<2> {
+    static constexpr int TX = 64, TY = 4, TZ = 1, HX = 66, HY = 6, HZ = 1;
+    static constexpr int CS = 400;
+};
+template <> struct ConvTile<3> {
+    static constexpr int TX = 32, TY = 4, TZ = 4, HX = 34, HY = 6, HZ = 6;
+    static constexpr int CS = 1232;
+};
+
+template <int DIM> struct TileAt {
+    using C = ConvTile<DIM>;
+    int x0, y0, z0;
+    __device__ __forceinline__ TileAt(const GridInfo &g, int tile) {
+        const int ntx = (g.nx + C::TX - 1) / C::TX, nty = (g.ny + C::TY - 1) / C::TY;
+        x0 = (tile % ntx) * C::TX;
+        y0 = (tile / ntx) % nty * C::TY;
+        z0 = DIM == 3 ? tile / (ntx * nty) * C::TZ : 0;
     }
+};
+
+template <int DIM> long long conv_tiles(const GridInfo &g) {
+    using C = ConvTile<DIM>;
+    return (long long)((g.nx + C::TX - 1) / C::TX) * ((g.ny + C::TY - 1) / C::TY) *
+           (DIM == 3 ? (g.nz + C::TZ - 1) / C::TZ : 1);
+}
+
+// Stage CH channel planes over a tile's halo region (origin x0 - 1, ... of
+// HX x HY x HZ points, 0 outside the grid) in LDS, channel stride `stride`, each
+// value times its gate (if given).  Wave w takes channels w * CW .. + CW, its
+// lanes 64 points at a time; R x CW loads are issued before their stores.
+template <typename C, int CH, int R>
+__device__ __forceinline__ void stage_halo(const GridInfo &g, int x0, int y0, int z0,
+                                           const float *__restrict__ in,
+                                           const float *__restrict__ in_gate, float *sx, int stride) {
+    constexpr int HP = C::HX * C::HY * C::HZ, CW = (CH + 3) / 4, NB = (HP + 63) / 64;
+    const int lane = (int)(threadIdx.x & 63u), c0 = (int)(threadIdx.x >> 6) * CW;
+#pragma unroll 1
+    for (int b0 = 0; b0 < NB; b0 += R) {
+        float v[R][CW], gt[R][CW];
 #pragma unroll
-    for (int co = 0; co < COUT; ++co) {
-        float v = acc[co];
-        if (pre) pre[co * N + i] = v;
-        if (gate) v *= gate[co * N + i];
-        if (relu) v = fmaxf(v, 0.f);
-        out[co * N + i] = v;
+        for (int b = 0; b < R; ++b) {
+            const int q = (b0 + b) * 64 + lane;
+            const int x = x0 - 1 + q % C::HX, y = y0 - 1 + (q / C::HX) % C::HY;
+            const int z = C::HZ > 1 ? z0 - 1 + q / (C::HX * C::HY) : 0;
+            const bool ok = q < HP && (unsigned)x < (unsigned)g.nx && (unsigned)y < (unsigned)g.ny &&
+                            (unsigned)z < (unsigned)g.nz;
+            const int idx = ok ? x + g.nx * (y + g.ny * z) : 0;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const long long k = (c0 + c < CH ? c0 + c : 0) * g.N + idx;
+                v[b][c] = in[k];
+                gt[b][c] = in_gate ? in_gate[k] : 1.f;
+                if (!ok) gt[b][c] = v[b][c] = 0.f;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < R; ++b)
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const int q = (b0 + b) * 64 + lane;
+                if (q < HP && c0 + c < CH) sx[(c0 + c) * stride + q] = v[b][c] * gt[b][c];
+            }
+    }
+}
+
+// 3^d convolution on the matrix cores in FP32 (v_mfma_f32_16x16x4f32), as an
+// implicit GEMM of 16 output channels by 16 points, K = input channels, tap by
+// tap.  Blocks walk tiles: the input on the tile and halo is staged in LDS (all
+// of a thread's loads first), the weights stay in registers as MFMA operands.
+//   forward (ADJ = false): y[co] = sum_{t, ci} W[co][ci][t] in[ci](p + off_t)
+//     (+ bias); pre = y (if given), out = y * gate (if given).
+//   adjoint (ADJ): y[ci] = sum_{t, co} W[co][ci][t] in[co](p - off_t), the
+//     gradient of the layer's input; the previous layer's gates follow at
+//     once: out = y * gate, gsum += y * pre.
+// KIN: channels of `in` (K), MOUT: output channels.  Bound by the matrix cores
+// and the planes: 16 -> 16 at 1024^2 takes 31 us of MFMA and 200 MB.
+template <int DIM, int KIN, int MOUT, bool ADJ>
+__global__ __launch_bounds__(256, DIM == 2 ? (KIN > 8 ? 3 : 4) : 2) void k_conv_mfma(GridInfo g, int ntiles, const float *__restrict__ in,
+                                                   const float *__restrict__ W,
+                                                   const float *__restrict__ bias,
+                                                   float *__restrict__ out,
+                                                   float *__restrict__ pre_out,
+                                                   const float *__restrict__ pre_in,
+                                                   const float *__restrict__ gate,
+                                                   float *__restrict__ gsum) {
+    using C = ConvTile<DIM>;
+    constexpr int T = DIM == 2 ? 9 : 27, KJ = (KIN + 3) / 4;
+    constexpr int HP = C::HX * C::HY * C::HZ, TP = C::TX * C::TY * C::TZ, NG = TP / 64;
+    __shared__ float sx[KJ * 4 * C::CS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = lane & 15, kk = lane >> 4;
+    const long long N = g.N;
+    float a[T][KJ];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const int k = 4 * j + kk;
+            a[t][j] = i < MOUT && k < KIN
+                          ? W[ADJ ? (k * MOUT + i) * T + (T - 1 - t) : (i * KIN + k) * T + t]
+                          : 0.f;
+        }
+    float bv[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) bv[c] = bias && 4 * kk + c < MOUT ? bias[4 * kk + c] : 0.f;
+    // channels past KIN meet zero weights; they must be finite
+    if (KIN % 4) {
+        for (int e = tid; e < (KJ * 4 - KIN) * HP; e += 256) sx[(KIN + e / HP) * C::CS + e % HP] = 0.f;
+    }
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const TileAt<DIM> t0(g, tile);
+        __syncthreads();
+        stage_halo<C, KIN, DIM == 2 ? 7 : 5>(g, t0.x0, t0.y0, t0.z0, in, nullptr, sx, C::CS);
+        __syncthreads();
+        // 16-point groups of a row; a wave takes a row of the tile in 2D, a
+        // plane in 3D (two rows at a time)
+        for (int r = 0; r < NG; r += 4) {
+            f32x4v acc[4];
+            int hb[4];
+            long long pt[4];  // this lane's first output value, -1 past the grid
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                constexpr int RG = C::TX / 16;  // groups of a row
+                const int x = (r + q) % RG * 16 + i;
+                const int y = DIM == 2 ? wave : (r + q) / RG, z = DIM == 2 ? 0 : wave;
+                hb[q] = (z * C::HY + y) * C::HX + x + kk * C::CS;  // tap (-1, -1, -1)
+                const int gx = t0.x0 + x, gy = t0.y0 + y, gz = t0.z0 + z;
+                pt[q] = gx < g.nx && gy < g.ny && gz < g.nz
+                            ? 4 * kk * N + gx + g.nx * (gy + g.ny * gz) : -1;
+                acc[q] = f32x4v{bv[0], bv[1], bv[2], bv[3]};
+            }
+            // what the results meet (from value 0 where there is no result):
+            // requested before the products where the registers allow
+            constexpr bool kEarly = DIM == 3 || !ADJ || KIN <= 8;
+            float ge[4][4], pe[4][4], se[4][4];
+            const auto meet = [&] {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const long long o = pt[q] >= 0 && 4 * kk + c < MOUT ? pt[q] + c * N : 0;
+                        ge[q][c] = gate ? gate[o] : 1.f;
+                        pe[q][c] = ADJ ? pre_in[o] : 0.f;
+                        se[q][c] = ADJ ? gsum[o] : 0.f;
+                    }
+            };
+            if (kEarly) meet();
+            // a tap's operands are read while the one before is multiplied; the
+            // scheduling barriers keep the reads of later taps from moving up
+            // (they filled the registers: 304 instead of 128)
+            float x[2][KJ][4];
+            const auto read = [&](int t) {
+                const int off = ((t / 9) * C::HY + (t / 3) % 3) * C::HX + t % 3;
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x[t & 1][j][q] = sx[hb[q] + off + 4 * j * C::CS];
+            };
+            read(0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if (t + 1 < T) read(t + 1);
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][j], x[t & 1][j][q],
+                                                                      acc[q], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!kEarly) meet();
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (pt[q] < 0 || 4 * kk + c >= MOUT) continue;
+                    const long long o = pt[q] + c * N;
+                    const float v = acc[q][c];
+                    out[o] = v * ge[q][c];
+                    if (ADJ) gsum[o] = se[q][c] + v * pe[q][c];
+                    else if (pre_out) pre_out[o] = v;
+                }
+        }
     }
 }
 
@@ -225,14 +378,29 @@ __global__ __launch_bounds__(kBS) void k_gate_b(long long N, const float *__rest
     float hr[H];
 #pragma unroll
     for (int c = 0; c < H; ++c) hr[c] = fmaxf(h[c * N + i], 0.f);
-    for (int k = 0; k < 2 * W; ++k) {
-        float a = bB[k];
+    static_assert(W % 8 == 0, "whole 16-byte groups of gates");
+#pragma unroll 1
+    for (int k0 = 0; k0 < 2 * W; k0 += 16) {
+        uint32_t q[4] = {0u, 0u, 0u, 0u};  // sixteen gates, one store
 #pragma unroll
-        for (int c = 0; c < H; ++c) a += WB[k * H + c] * hr[c];
-        const float gv = 1.f / (1.f + expf(-a));
-        Gout[k * N + i] = gv;
-        if (G8) G8[i * 2 * W + k] = (uint8_t)__float2int_rn(gv * 255.f);
-        if (k < W) Gout[(2 * W + k) * N + i] = gv;
+        for (int k1 = 0; k1 < 16; ++k1) {
+            const int k = k0 + k1;
+            float a = bB[k];
+#pragma unroll
+            for (int c = 0; c < H; ++c) a += WB[k * H + c] * hr[c];
+            const float gv = 1.f / (1.f + expf(-a));
+            Gout[k * N + i] = gv;
+            q[k1 >> 2] |= (uint32_t)(uint8_t)__float2int_rn(gv * 255.f) << (8 * (k1 & 3));
+            if (k < W) Gout[(2 * W + k) * N + i] = gv;
+        }
+        if (!G8) continue;
+        uint8_t *o = G8 + i * 2 * W + k0;
+        if (((uintptr_t)G8 & 15) == 0) {  // the caller's buffer may start anywhere
+            *(uint4 *)o = make_uint4(q[0], q[1], q[2], q[3]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < 16; ++b) o[b] = (uint8_t)(q[b >> 2] >> (8 * (b & 3)));
+        }
     }
     Gout[(GX - 1) * N + i] = 1.f;
 }
@@ -271,18 +439,6 @@ __global__ void k_fold_weight_grads(const float *__restrict__ gL, float *__restr
     }
 }
 
-// Fold the expanded gate gradients [3W+1][N] onto g1, g2 ([2W][N]):
-// dg1 = dG[0:W] + dG[2W:3W], dg2 = dG[W:2W]; the constant last gate has none.
-__global__ void k_fold_gate_grads(long long N, int W, const float *__restrict__ gx,
-                                  float *__restrict__ gg) {
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
-    if (i >= N) return;
-    for (int k = 0; k < W; ++k) {
-        gg[k * N + i] = gx[k * N + i] + gx[(2 * W + k) * N + i];
-        gg[(W + k) * N + i] = gx[(W + k) * N + i];
-    }
-}
-
 __global__ void k_fill_f32(float *p, long long n, float v) {
     const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
     if (i < n) p[i] = v;
@@ -306,273 +462,85 @@ __global__ void k_gate_grad(long long n, const float *g, const float *gate, cons
     ggate[i] += gv * pre[i];
 }
 
-// gin[ci](p) = sum_{t, co} W[co][ci][t] ga[co](p - off_t)  (transposed conv)
+// Weight gradient of a 3^d layer on the matrix cores, dW[co][ci][t] = sum_p
+// ga[co](p) x_ci(p + off_t) with x_ci = in[ci] (* in_gate[ci]), and the bias
+// gradient db[co] = sum_p ga[co](p): GEMMs D_t[co][ci] += A[co][4 points]
+// B_t[4 points][ci] with v_mfma_f32_16x16x4f32 (FP32 operands and
+// accumulation).  Blocks walk tiles of points (2D 64 x 4, 3D 32 x 4 x 2): ga
+// on the tile and x on the tile plus a one-point halo (0 outside the grid) are
+// staged in LDS (every load of a thread is issued before its stores), then
+// every wave takes a quarter of the tile's four-point steps for all taps.  The
+// four waves' sums are added in LDS in wave order (the x buffer is reused for
+// that once the tiles are done) and written as this block's partials
+// [COUT * CIN * T weights, COUT biases].
+// Bound by latency between the stagings: three blocks a CU, whole lines and
+// unconflicted LDS strides took 16 x 16 at 1024^2 from 385 us (one block a CU,
+// 16 x 16 tiles).
+template <int DIM> struct GradTile;
+template <> struct GradTile<2> {
+    static constexpr int TX = 64, TY = 4, TZ = 1, HX = 66, HY = 6, HZ = 1;
+};
+template <> struct GradTile<3> {
+    static constexpr int TX = 32, TY = 4, TZ = 2, HX = 34, HY = 6, HZ = 4;
+};
+template <int DIM> long long grad_tiles(const GridInfo &g) {
+    using C = GradTile<DIM>;
+    return (long long)((g.nx + C::TX - 1) / C::TX) * ((g.ny + C::TY - 1) / C::TY) *
+           (DIM == 3 ? (g.nz + C::TZ - 1) / C::TZ : 1);
+}
+
 template <int DIM, int CIN, int COUT>
-__global__ __launch_bounds__(kBS) void k_conv_bwd_data(GridInfo g, const float *__restrict__ ga,
-                                                       const float *__restrict__ W,
-                                                       float *__restrict__ gin) {
-    constexpr int T = DIM == 2 ? 9 : 27;
-    const float *sw = W;
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
-    const long long N = g.N;
-    if (i >= N) return;
-    const Pt p = coord_of(i, g);
-    float acc[CIN];
-#pragma unroll
-    for (int ci = 0; ci < CIN; ++ci) acc[ci] = 0.f;
-    for (int t = 0; t < T; ++t) {
-        const long long q = tap_nb<DIM>(p, i, T - 1 - t, g);  // p - off_t
-        if (q < 0) continue;
-        for (int co = 0; co < COUT; ++co) {
-            const float y = ga[co * N + q];
-#pragma unroll
-            for (int ci = 0; ci < CIN; ++ci) acc[ci] += sw[(co * CIN + ci) * T + t] * y;
-        }
-    }
-#pragma unroll
-    for (int ci = 0; ci < CIN; ++ci) gin[ci * N + i] = acc[ci];
-}
-
-// Weight gradient dW[co][ci][t] = sum_p ga[co](p) x_ci(p + off_t), with
-// x_ci = in[ci] (* in_gate[ci]) (ReLU'd if relu_in), and the bias gradient
-// db[co] = sum_p ga[co](p).  Each block walks a set of 256-point chunks and
-// writes partials[block][COUT*CIN*T + COUT]; k_reduce_partials finishes.
-template <int DIM, int CIN, int COUT, int PPT>
-__global__ __launch_bounds__(kBS) void k_conv_bwd_w(GridInfo g, const float *__restrict__ in,
-                                                    const float *__restrict__ in_gate, int relu_in,
+__global__ __launch_bounds__(256, DIM == 2 ? 3 : 2) void k_conv_bwd_w(GridInfo g, int ntiles, const float *__restrict__ in,
+                                                    const float *__restrict__ in_gate,
                                                     const float *__restrict__ ga,
-                                                    float *__restrict__ partials, int taps) {
-    constexpr int TM = DIM == 2 ? 9 : 27;
-    constexpr int C = 128;  // points per chunk
-    const int T = taps;     // 1 for a 1x1 layer
-    __shared__ float sg[COUT * C];
-    __shared__ float sx[C * CIN];
-    const long long N = g.N;
-    float acc[PPT][TM];
-    float accb = 0.f;
-#pragma unroll
-    for (int k = 0; k < PPT; ++k)
-#pragma unroll
-        for (int t = 0; t < TM; ++t) acc[k][t] = 0.f;
-    const long long nchunk = (N + C - 1) / C;
-    for (long long c = blockIdx.x; c < nchunk; c += gridDim.x) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < COUT * C; e += kBS) {
-            const int co = e / C, j = e % C;
-            const long long i = c * C + j;
-            sg[e] = i < N ? ga[co * N + i] : 0.f;
-        }
-        for (int t = 0; t < T; ++t) {
-            const int tt = T == 1 ? (DIM == 2 ? 4 : 13) : t;  // centre tap for 1x1
-            __syncthreads();
-            for (int e = threadIdx.x; e < C * CIN; e += kBS) {
-                const int j = e / CIN, ci = e % CIN;
-                const long long i = c * C + j;
-                float x = 0.f;
-                if (i < N) {
-                    const long long q = tap_nb<DIM>(coord_of(i, g), i, tt, g);
-                    if (q >= 0) {
-                        x = in[ci * N + q];
-                        if (in_gate) x *= in_gate[ci * N + q];
-                        if (relu_in) x = fmaxf(x, 0.f);
-                    }
-                }
-                sx[e] = x;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                const int pair = threadIdx.x + k * kBS;
-                if (pair < COUT * CIN) {
-                    const int co = pair / CIN, ci = pair % CIN;
-                    float s = 0.f;
-                    for (int j = 0; j < C; ++j) s += sg[co * C + j] * sx[j * CIN + ci];
-#pragma unroll
-                    for (int tq = 0; tq < TM; ++tq)
-                        if (tq == t) acc[k][tq] += s;
-                }
-            }
-        }
-        if ((int)threadIdx.x < COUT) {  // bias: sum of ga over the chunk
-            float s = 0.f;
-            for (int j = 0; j < C; ++j) s += sg[threadIdx.x * C + j];
-            accb += s;
-        }
-    }
-    const int stride = COUT * CIN * T + COUT;
-    float *outp = partials + (long long)blockIdx.x * stride;
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int pair = threadIdx.x + k * kBS;
-        if (pair < COUT * CIN)
-            for (int t = 0; t < T; ++t) outp[pair * T + t] = acc[k][t];
-    }
-    if ((int)threadIdx.x < COUT) outp[COUT * CIN * T + threadIdx.x] = accb;
-}
-
-// 2D weight gradient on the matrix cores: the same sums as k_conv_bwd_w for
-// 3x3 layers, dW[co][ci][t] = sum_p ga[co](p) x_ci(p + off_t), as GEMMs
-// D_t[co][ci] += A[co][4 points] B_t[4 points][ci] with
-// v_mfma_f32_16x16x4f32 (FP32 operands and accumulation).  Each block
-// walks 16x16 tiles of points: ga on the tile and x on the tile plus a
-// one-point halo (0 outside the grid) are staged in LDS, then every wave
-// takes a quarter of the tile's 64 four-point steps for all 9 taps.  The
-// four waves' results are summed in LDS in a fixed order and written as
-// this block's partials (same layout as k_conv_bwd_w).
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv_bwd_w2d_mfma(GridInfo g, const float *__restrict__ in,
-                                                           const float *__restrict__ in_gate,
-                                                           int relu_in,
-                                                           const float *__restrict__ ga,
-                                                           float *__restrict__ partials) {
-    constexpr int TW = 16, HW = TW + 2, T = 9;
-    __shared__ float sx[CIN * HW * HW];
-    __shared__ float sg[COUT * TW * TW];
-    __shared__ float red[4][COUT * CIN * T + COUT];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nx = g.nx, ny = g.ny;
-    const int ntx = (nx + TW - 1) / TW, nty = (ny + TW - 1) / TW;
-    const int i = lane & 15, kk = lane >> 4;  // A row (co) / B column (ci), k
-    f32x4v acc[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) acc[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
-    float accb = 0.f;  // bias: sum of ga[co = i] over this lane's points
-    for (int tile = blockIdx.x; tile < ntx * nty; tile += gridDim.x) {
-        const int x0 = (tile % ntx) * TW, y0 = (tile / ntx) * TW;
-        __syncthreads();
-        for (int e = tid; e < CIN * HW * HW; e += 256) {
-            const int ci = e / (HW * HW), q = e % (HW * HW);
-            const int gx = x0 - 1 + q % HW, gy = y0 - 1 + q / HW;
-            float v = 0.f;
-            if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
-                const long long k = (long long)gy * nx + gx;
-                v = in[ci * g.N + k];
-                if (in_gate) v *= in_gate[ci * g.N + k];
-                if (relu_in) v = fmaxf(v, 0.f);
-            }
-            sx[e] = v;
-        }
-        for (int e = tid; e < COUT * TW * TW; e += 256) {
-            const int co = e / (TW * TW), q = e % (TW * TW);
-            const int gx = x0 + q % TW, gy = y0 + q / TW;
-            sg[e] = (gx < nx && gy < ny) ? ga[co * g.N + (long long)gy * nx + gx] : 0.f;
-        }
-        __syncthreads();
-        for (int ks = wave; ks < TW * TW / 4; ks += 4) {
-            const int p = ks * 4 + kk, py = p / TW, px = p % TW;
-            const float a = i < COUT ? sg[i * TW * TW + p] : 0.f;
-            accb += a;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const float b = i < CIN ? sx[i * HW * HW + (py + t / 3) * HW + (px + t % 3)] : 0.f;
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[t], 0, 0, 0);
-            }
-        }
-    }
-    // D: lane holds D[co = 4 (lane >> 4) + c][ci = lane & 15]
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int co = 4 * kk + c, ci = i;
-            if (co < COUT && ci < CIN) red[wave][(co * CIN + ci) * T + t] = acc[t][c];
-        }
-    // bias: lanes with the same co (i) hold disjoint point sets
-    for (int d = 16; d < 64; d <<= 1) accb += __shfl_xor(accb, d, 64);
-    if (kk == 0 && i < COUT) red[wave][COUT * CIN * T + i] = accb;
-    __syncthreads();
+                                                    float *__restrict__ partials) {
+    using C = GradTile<DIM>;
+    constexpr int T = DIM == 2 ? 9 : 27;
+    constexpr int TP = C::TX * C::TY * C::TZ, HP = C::HX * C::HY * C::HZ;
+    static_assert(TP == 256 && CIN <= 16 && COUT <= 16, "one 16 x 16 MFMA tile");
+    // channel strides of 4 modulo the 64 banks: the sixteen channels of an
+    // operand read, four points each, fall on different banks
+    constexpr int XS = (HP - 4 + 63) / 64 * 64 + 4, GS = TP + 4;
+    static_assert(XS >= HP && XS % 64 == 4 && GS % 64 == 4, "strides");
     constexpr int stride = COUT * CIN * T + COUT;
-    for (int e = tid; e < stride; e += 256)
-        partials[(long long)blockIdx.x * stride + e] =
-            ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
-}
-
-// 3D weight gradient on the matrix cores, for 3x3x3 layers: the sums of
-// k_conv_bwd_w as GEMMs D_t[co][ci] += A[co][4 points] B_t[4 points][ci]
-// with v_mfma_f32_16x16x4f32 (FP32 operands and accumulation), as in 2D.
-// Each block walks 8 x 8 x 4 tiles of points: ga on the tile and x on the
-// tile plus a one-point halo (10 x 10 x 6, 0 outside the grid) are staged
-// in LDS (every load of a thread is issued before its stores), then every
-// wave takes a quarter of the tile's 64 four-point steps for all 27 taps.
-// The four waves' sums are added in LDS in wave order (the x buffer is
-// reused for that once the tiles are done) and written as this block's
-// partials (same layout as k_conv_bwd_w).
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv_bwd_w3d_mfma(GridInfo g, const float *__restrict__ in,
-                                                           const float *__restrict__ in_gate,
-                                                           int relu_in,
-                                                           const float *__restrict__ ga,
-                                                           float *__restrict__ partials) {
-    constexpr int TX = 8, TY = 8, TZ = 4, HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
-    constexpr int TP = TX * TY * TZ, HP = HX * HY * HZ, T = 27;
-    constexpr int stride = COUT * CIN * T + COUT;
-    constexpr int SX = CIN * HP > stride ? CIN * HP : stride;
+    constexpr int SX = CIN * XS > stride ? CIN * XS : stride;
     __shared__ float sx[SX];  // x on the halo region; at the end the wave sums
-    __shared__ float sg[COUT * TP];
-    static_assert(CIN <= 16 && COUT <= 16, "one 16 x 16 MFMA tile");
+    __shared__ float sg[COUT * GS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
-    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY, ntz = (nz + TZ - 1) / TZ;
+    const int ntx = (nx + C::TX - 1) / C::TX, nty = (ny + C::TY - 1) / C::TY;
     const int i = lane & 15, kk = lane >> 4;  // A row (co) / B column (ci), k
     f32x4v acc[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
     float accb = 0.f;  // bias: sum of ga[co = i] over this lane's points
-    const long long ntiles = (long long)ntx * nty * ntz;
-    for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int x0 = (int)(tile % ntx) * TX, y0 = (int)((tile / ntx) % nty) * TY,
-                  z0 = (int)(tile / ((long long)ntx * nty)) * TZ;
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int x0 = tile % ntx * C::TX, y0 = tile / ntx % nty * C::TY,
+                  z0 = DIM == 3 ? tile / (ntx * nty) * C::TZ : 0;
         __syncthreads();
         {
-            constexpr int NB = (CIN * HP + 255) / 256;
-            float v[NB];
+            stage_halo<C, CIN, 4>(g, x0, y0, z0, in, in_gate, sx, XS);
+            // ga: one point of the tile per thread, all channels
+            const int gx = x0 + tid % C::TX, gy = y0 + (tid / C::TX) % C::TY,
+                      gz = DIM == 3 ? z0 + tid / (C::TX * C::TY) : 0;
+            const bool ok = gx < nx && gy < ny && gz < nz;
+            const long long k = ok ? ((long long)gz * ny + gy) * nx + gx : 0;
+            float w[COUT];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int e = b * 256 + tid;
-                v[b] = 0.f;
-                if (e < CIN * HP) {
-                    const int ci = e / HP, q = e % HP;
-                    const int gx = x0 - 1 + q % HX, gy = y0 - 1 + (q / HX) % HY,
-                              gz = z0 - 1 + q / (HX * HY);
-                    if (gx >= 0 && gx < nx && gy >= 0 && gy < ny && gz >= 0 && gz < nz) {
-                        const long long k = ((long long)gz * ny + gy) * nx + gx;
-                        float x = in[ci * g.N + k];
-                        if (in_gate) x *= in_gate[ci * g.N + k];
-                        v[b] = relu_in ? fmaxf(x, 0.f) : x;
-                    }
-                }
-            }
-            constexpr int NG = (COUT * TP + 255) / 256;
-            float w[NG];
+            for (int co = 0; co < COUT; ++co) w[co] = ga[co * g.N + k];
 #pragma unroll
-            for (int b = 0; b < NG; ++b) {
-                const int e = b * 256 + tid;
-                w[b] = 0.f;
-                if (e < COUT * TP) {
-                    const int co = e / TP, q = e % TP;
-                    const int gx = x0 + q % TX, gy = y0 + (q / TX) % TY, gz = z0 + q / (TX * TY);
-                    if (gx < nx && gy < ny && gz < nz)
-                        w[b] = ga[co * g.N + ((long long)gz * ny + gy) * nx + gx];
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                if (b * 256 + tid < CIN * HP) sx[b * 256 + tid] = v[b];
-#pragma unroll
-            for (int b = 0; b < NG; ++b)
-                if (b * 256 + tid < COUT * TP) sg[b * 256 + tid] = w[b];
+            for (int co = 0; co < COUT; ++co) sg[co * GS + tid] = ok ? w[co] : 0.f;
         }
         __syncthreads();
         for (int ks = wave; ks < TP / 4; ks += 4) {
             const int p = ks * 4 + kk;
-            const int px = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
-            const float a = i < COUT ? sg[i * TP + p] : 0.f;
+            const int px = p % C::TX, py = (p / C::TX) % C::TY, pz = p / (C::TX * C::TY);
+            const float a = i < COUT ? sg[(i < COUT ? i : 0) * GS + p] : 0.f;
             accb += a;
-            const int hb = i * HP + (pz * HY + py) * HX + px;  // tap (-1, -1, -1)
+            const int hb = (i < CIN ? i : 0) * XS + (pz * C::HY + py) * C::HX + px;
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int off = ((t / 9) * HY + (t / 3) % 3) * HX + t % 3;
+                const int off = ((t / 9) * C::HY + (t / 3) % 3) * C::HX + t % 3;
                 const float b = i < CIN ? sx[hb + off] : 0.f;
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[t], 0, 0, 0);
             }
@@ -604,41 +572,150 @@ __global__ __launch_bounds__(256) void k_conv_bwd_w3d_mfma(GridInfo g, const flo
     for (int e = tid; e < stride; e += 256) partials[(long long)blockIdx.x * stride + e] = sx[e];
 }
 
-// grad[k] += sum over blocks of partials[b][k] (block order: deterministic);
-// weights go to gW[0 .. nw), biases (the last nb entries) to gb (if given).
-__global__ void k_reduce_partials(const float *partials, int nblocks, int stride, int nw,
-                                  float *gW, float *gb) {
-    const int k = blockIdx.x * kBS + threadIdx.x;
-    if (k >= stride) return;
+// grad[k] += sum over blocks of partials[b][k]; weights go to gW[0 .. nw),
+// biases (the last nb entries) to gb (if given).  64 columns a block, its
+// sixteen wavefronts a sixteenth of the rows each (a chain of rounds of loads:
+// 58 us with all rows in one thread), in FP64 in a fixed order.
+constexpr int kRedWaves = 16;
+__global__ __launch_bounds__(64 * kRedWaves) void k_reduce_partials(
+    const float *__restrict__ partials, int nblocks, int stride, int nw, float *gW, float *gb) {
+    __shared__ double red[kRedWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane, kc = k < stride ? k : 0;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += (double)partials[(long long)b * stride + k];
+    int b = wave;
+    for (; b + 7 * kRedWaves < nblocks; b += 8 * kRedWaves) {  // eight rows in flight
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = partials[(long long)(b + kRedWaves * j) * stride + kc];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += (double)v[j];
+    }
+    for (; b < nblocks; b += kRedWaves) s += (double)partials[(long long)b * stride + kc];
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || k >= stride) return;
+    s = 0.0;
+#pragma unroll
+    for (int j = 0; j < kRedWaves; ++j) s += red[j][lane];
     if (k < nw) gW[k] += (float)s;
     else if (gb) gb[k - nw] += (float)s;
 }
 
-// Gate net backward, point-wise part: gg = dG G (1 - G) (into dG's place),
-// gh = (WB^T gg) * [h > 0].
-template <int H, int G>
-__global__ __launch_bounds__(kBS) void k_gate_b_bwd(long long N, const float *__restrict__ Gv,
-                                                    float *__restrict__ gg,
-                                                    const float *__restrict__ h,
-                                                    const float *__restrict__ WB,
-                                                    float *__restrict__ gh) {
-    const float *sw = WB;
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
-    if (i >= N) return;
-    float acc[H];
+// Gate net backward from the gradients gx of the expanded gates ([3W+1][N]), in
+// one pass over the points: the gates' gradients folded (dg1 = dG[0:W] +
+// dG[2W:3W], dg2 = dG[W:2W]; the constant last gate has none), gg = dg g
+// (1 - g), gh = (WB^T gg) * [h > 0] (written), and the 1x1 layer's weight
+// gradient dWB[k][c] = sum_p gg[k] relu(h[c]), dbB[k] = sum_p gg[k]; the
+// products on the matrix cores (FP32), the wave's 64 points staged in LDS
+// (with WB in scalar registers, 512 of them, the loop spilled: 265 us).  Partials per block:
+// [2W * H weights, 2W biases].  Bound by its planes: 48 + 32 + 16 read, 16
+// written (1024^2: 470 MB).
+template <int H, int W>
+__global__ __launch_bounds__(256, 4) void k_gate_bwd(long long N, const float *__restrict__ gx,
+                                                  const float *__restrict__ Gv,
+                                                  const float *__restrict__ h,
+                                                  const float *__restrict__ WB,
+                                                  float *__restrict__ gh,
+                                                  float *__restrict__ partials) {
+    static_assert(H == 16 && W == 16, "two 16 x 16 MFMA tiles");
+    constexpr int G = 2 * W, S = 68;  // LDS stride of a channel: 4 modulo the 64 banks
+    __shared__ float sg[4][W * S];
+    __shared__ float sh[4][H * S];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = lane & 15, kk = lane >> 4;
+    float *mg = sg[wave], *mh = sh[wave];
+    f32x4v acc[2] = {f32x4v{0.f, 0.f, 0.f, 0.f}, f32x4v{0.f, 0.f, 0.f, 0.f}};
+    float accb[2] = {0.f, 0.f};
+    float wb[2][4];  // WB^T as MFMA operands: row c = i, k = 16 m + 4 j + kk
 #pragma unroll
-    for (int c = 0; c < H; ++c) acc[c] = 0.f;
-    for (int k = 0; k < G; ++k) {
-        const float gv = Gv[k * N + i];
-        const float v = gg[k * N + i] * gv * (1.f - gv);
-        gg[k * N + i] = v;
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int c = 0; c < H; ++c) acc[c] += sw[k * H + c] * v;
+        for (int j = 0; j < 4; ++j) wb[m][j] = WB[(16 * m + 4 * j + kk) * H + i];
+    const long long nchunk = (N + 255) / 256;
+    for (long long ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
+        const long long p = ch * 256 + threadIdx.x;
+        const bool ok = p < N;
+        const long long q = ok ? p : 0;
+        float hv[H];
+#pragma unroll
+        for (int c = 0; c < H; ++c) hv[c] = h[c * N + q];
+        f32x4v a[4];  // gh of the wave's four 16-point groups
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = f32x4v{0.f, 0.f, 0.f, 0.f};
+        // g1's sixteen gates, then g2's: every load of the half first
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            float d[W], e[W], gv[W];
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                d[j] = gx[(m * W + j) * N + q];
+                e[j] = m == 0 ? gx[(2 * W + j) * N + q] : 0.f;
+                gv[j] = Gv[(m * W + j) * N + q];
+            }
+            if (m == 0) {
+#pragma unroll
+                for (int c = 0; c < H; ++c) mh[c * S + lane] = ok ? fmaxf(hv[c], 0.f) : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                mg[j * S + lane] = ok ? (d[j] + e[j]) * gv[j] * (1.f - gv[j]) : 0.f;
+            // LDS serves a wave's reads after its writes; the barriers keep the
+            // compiler from moving them
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const float av = mg[i * S + 4 * s + kk], b = mh[i * S + 4 * s + kk];
+                accb[m] += av;
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b, acc[m], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    a[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        wb[m][j], mg[(4 * j + kk) * S + 16 * r + i], a[r], 0, 0, 0);
+            __builtin_amdgcn_wave_barrier();
+        }
+        // a: lane holds channels 4 kk + c of point 16 r + i of the wave
+        const long long pw = ch * 256 + wave * 64;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const long long pr = pw + 16 * r + i;
+                const bool on = mh[(4 * kk + c) * S + 16 * r + i] > 0.f;
+                if (pr < N) gh[(4 * kk + c) * N + pr] = on ? a[r][c] : 0.f;
+            }
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
-    for (int c = 0; c < H; ++c) gh[c * N + i] = h[c * N + i] > 0.f ? acc[c] : 0.f;
+    for (int m = 0; m < 2; ++m)
+        for (int d = 16; d < 64; d <<= 1) accb[m] += __shfl_xor(accb[m], d, 64);
+    // the waves' sums, in wave order
+    constexpr int stride = G * H + G;
+    static_assert(stride <= 4 * W * S, "the sums fit where the gates were");
+    float *tot = sg[0];
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float &r = tot[(16 * m + 4 * kk + c) * H + i];
+                    r = w == 0 ? acc[m][c] : r + acc[m][c];
+                }
+                if (kk == 0) {
+                    float &r = tot[G * H + 16 * m + i];
+                    r = w == 0 ? accb[m] : r + accb[m];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < stride; e += 256)
+        partials[(long long)blockIdx.x * stride + e] = tot[e];
 }
 
 // ------------------------------------------------------------ loss, Adam --
@@ -699,15 +776,25 @@ __global__ void k_residual_vec(long long N, const T *b, const T *kx, T *r) {
 // ------------------------------------------------------------- drivers --
 unsigned nblk(long long N) { return (unsigned)((N + kBS - 1) / kBS); }
 
+// Blocks of the tile-walking kernels: enough to fill 256 CUs a few times over
+// (LDS and registers leave room for 3 to 6 a CU), fewer where there are fewer
+// tiles.
+constexpr int kWgBlocks = 768;
+
+template <int DIM> unsigned conv_blocks(long long tiles) {
+    constexpr long long most = DIM == 2 ? 768 : 512;
+    return (unsigned)(tiles < most ? tiles : most);
+}
+
 template <int DIM>
-int conv_launch(const GridInfo &g, int cin, int cout, const float *in, const float *in_gate,
-                const float *W, const float *bias, float *out, float *pre, const float *gate,
-                int relu, hipStream_t s) {
-    const unsigned nb = nblk(g.N);
+int conv_launch(const GridInfo &g, int cin, int cout, const float *in, const float *W,
+                const float *bias, float *out, float *pre, const float *gate, hipStream_t s) {
+    const int nt = (int)conv_tiles<DIM>(g);  // N < 2^28
+    const unsigned nb = conv_blocks<DIM>(nt);
 #define ADLBR_CONV(CI, CO)                                                                     \
     if (cin == CI && cout == CO) {                                                             \
-        hipLaunchKernelGGL((k_conv<DIM, CI, CO>), dim3(nb), dim3(kBS), 0, s, g, in, in_gate, W, \
-                           bias, out, pre, gate, relu);                                        \
+        hipLaunchKernelGGL((k_conv_mfma<DIM, CI, CO, false>), dim3(nb), dim3(256), 0, s, g, nt, \
+                           in, W, bias, out, pre, nullptr, gate, nullptr);                     \
         return ADLBR_OK;                                                                       \
     }
     ADLBR_CONV(1, 16)
@@ -720,52 +807,50 @@ int conv_launch(const GridInfo &g, int cin, int cout, const float *in, const flo
     return ADLBR_E_UNSUPPORTED;
 }
 
+// Gradient of a layer's input from ga, then the previous layer's gates: out =
+// gin * gate, ggate += gin * pre.
 template <int DIM>
 int bwd_data_launch(const GridInfo &g, int cin, int cout, const float *ga, const float *W,
-                    float *gin, hipStream_t s) {
-    const unsigned nb = nblk(g.N);
+                    const float *pre, const float *gate, float *out, float *ggate, hipStream_t s) {
+    const int nt = (int)conv_tiles<DIM>(g);
+    const unsigned nb = conv_blocks<DIM>(nt);
     if (cin == 16 && cout == 16) {
-        hipLaunchKernelGGL((k_conv_bwd_data<DIM, 16, 16>), dim3(nb), dim3(kBS), 0, s, g, ga, W, gin);
+        hipLaunchKernelGGL((k_conv_mfma<DIM, 16, 16, true>), dim3(nb), dim3(256), 0, s, g, nt, ga, W,
+                           nullptr, out, nullptr, pre, gate, ggate);
         return ADLBR_OK;
     }
     if (cin == 16 && cout == 1) {
-        hipLaunchKernelGGL((k_conv_bwd_data<DIM, 16, 1>), dim3(nb), dim3(kBS), 0, s, g, ga, W, gin);
+        hipLaunchKernelGGL((k_conv_mfma<DIM, 1, 16, true>), dim3(nb), dim3(256), 0, s, g, nt, ga, W,
+                           nullptr, out, nullptr, pre, gate, ggate);
         return ADLBR_OK;
     }
     set_error("conv backward: unsupported channel counts");
     return ADLBR_E_UNSUPPORTED;
 }
 
-constexpr int kWgBlocks = 240;
+void reduce_launch(const float *partials, int nblocks, int stride, int nw, float *gW, float *gb,
+                   hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce_partials, dim3((stride + 63) / 64), dim3(64 * kRedWaves), 0, s, partials,
+                       nblocks, stride, nw, gW, gb);
+}
 
 template <int DIM>
-int bwd_w_launch(const GridInfo &g, int cin, int cout, int taps, const float *in,
-                 const float *in_gate, int relu_in, const float *ga, float *partials, float *gW,
-                 float *gb, hipStream_t s) {
-#define ADLBR_BW(CI, CO, PPT)                                                                 \
+int bwd_w_launch(const GridInfo &g, int cin, int cout, const float *in, const float *in_gate,
+                 const float *ga, float *partials, float *gW, float *gb, hipStream_t s) {
+    const int nt = (int)grad_tiles<DIM>(g), nb = nt < kWgBlocks ? nt : kWgBlocks;
+    constexpr int T = DIM == 2 ? 9 : 27;
+#define ADLBR_BW(CI, CO)                                                                      \
     if (cin == CI && cout == CO) {                                                            \
-        if (DIM == 2 && taps == 9 && CI <= 16 && CO <= 16)                                    \
-            hipLaunchKernelGGL((k_conv_bwd_w2d_mfma<CI, (CO <= 16 ? CO : 16)>),               \
-                               dim3(kWgBlocks), dim3(kBS), 0, s, g, in, in_gate, relu_in, ga, \
-                               partials);                                                     \
-        else if (DIM == 3 && taps == 27 && CI <= 16 && CO <= 16)                              \
-            hipLaunchKernelGGL((k_conv_bwd_w3d_mfma<CI, (CO <= 16 ? CO : 16)>),               \
-                               dim3(kWgBlocks), dim3(kBS), 0, s, g, in, in_gate, relu_in, ga, \
-                               partials);                                                     \
-        else                                                                                  \
-            hipLaunchKernelGGL((k_conv_bwd_w<DIM, CI, CO, PPT>), dim3(kWgBlocks), dim3(kBS),  \
-                               0, s, g, in, in_gate, relu_in, ga, partials, taps);            \
-        const int stride = CO * CI * taps + CO;                                               \
-        hipLaunchKernelGGL(k_reduce_partials, dim3((stride + kBS - 1) / kBS), dim3(kBS), 0, s,  \
-                           partials, kWgBlocks, stride, CO * CI * taps, gW, gb);              \
+        hipLaunchKernelGGL((k_conv_bwd_w<DIM, CI, CO>), dim3(nb), dim3(256), 0, s, g, nt, in,  \
+                           in_gate, ga, partials);                                            \
+        reduce_launch(partials, nb, CO * CI * T + CO, CO * CI * T, gW, gb, s);                \
         return ADLBR_OK;                                                                      \
     }
-    ADLBR_BW(1, 16, 1)
-    ADLBR_BW(16, 16, 1)
-    ADLBR_BW(16, 1, 1)
-    ADLBR_BW(7, 16, 1)
-    ADLBR_BW(13, 16, 1)
-    ADLBR_BW(16, 32, 2)
+    ADLBR_BW(1, 16)
+    ADLBR_BW(16, 16)
+    ADLBR_BW(16, 1)
+    ADLBR_BW(7, 16)
+    ADLBR_BW(13, 16)
 #undef ADLBR_BW
     set_error("conv weight gradient: unsupported channel counts");
     return ADLBR_E_UNSUPPORTED;
@@ -782,10 +867,10 @@ NetWs net_ws(long long N, const NetDims &d, char *base) {
     const size_t plane = align_up(4 * (size_t)N);
     w.g0 = (float *)(base + o);  o += 16 * plane;
     w.g1 = (float *)(base + o);  o += 16 * plane;
-    w.ga = (float *)(base + o);  o += 49 * plane;
+    w.ga = (float *)(base + o);  o += plane;
     w.gl = (float *)(base + o);  o += align_up(4 * d.lcount);
     w.partials = (float *)(base + o);
-    o += align_up(4 * (size_t)kWgBlocks * (16 * 16 * 27 + 64 + 49 * 16 + 49));
+    o += align_up(4 * (size_t)kWgBlocks * (16 * 16 * d.T + 64));
     w.total = o;
     return w;
 }
@@ -799,16 +884,16 @@ int forward_impl(const adlbr_operator *op, const adlbr_net *net, const NetDims &
     const float *G = net->gates;
     float *pre = saved;
     int rc;
-    rc = conv_launch<DIM>(g, 1, 16, r, nullptr, L + d.l1, nullptr, bufA, pre, G, 0, s);
+    rc = conv_launch<DIM>(g, 1, 16, r, L + d.l1, nullptr, bufA, pre, G, s);
     if (rc) return rc;
-    rc = conv_launch<DIM>(g, 16, 16, bufA, nullptr, L + d.l2, nullptr, bufB,
-                          pre ? pre + 16 * N : nullptr, G + 16 * N, 0, s);
+    rc = conv_launch<DIM>(g, 16, 16, bufA, L + d.l2, nullptr, bufB, pre ? pre + 16 * N : nullptr,
+                          G + 16 * N, s);
     if (rc) return rc;
-    rc = conv_launch<DIM>(g, 16, 16, bufB, nullptr, L + d.l3, nullptr, bufA,
-                          pre ? pre + 32 * N : nullptr, G + 32 * N, 0, s);
+    rc = conv_launch<DIM>(g, 16, 16, bufB, L + d.l3, nullptr, bufA, pre ? pre + 32 * N : nullptr,
+                          G + 32 * N, s);
     if (rc) return rc;
-    rc = conv_launch<DIM>(g, 16, 1, bufA, nullptr, L + d.l4, nullptr, bufB,
-                          pre ? pre + 48 * N : nullptr, G + 48 * N, 0, s);
+    rc = conv_launch<DIM>(g, 16, 1, bufA, L + d.l4, nullptr, bufB, pre ? pre + 48 * N : nullptr,
+                          G + 48 * N, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_precond_out, dim3(nblk(N)), dim3(kBS), 0, s, N, r, net->features, bufB, z);
     return ADLBR_OK;
@@ -945,10 +1030,10 @@ extern "C" int adlbr_net_gates(adlbr_operator *op, adlbr_net *net, void *stream)
     const GridInfo &g = operator_grid(op);
     hipStream_t s = as_stream(stream);
     const float *P = net->params;
-    rc = g.dim == 2 ? conv_launch<2>(g, d.nf, 16, net->features, nullptr, P + d.oWA, P + d.obA,
-                                     net->hidden_act, nullptr, nullptr, 0, s)
-                    : conv_launch<3>(g, d.nf, 16, net->features, nullptr, P + d.oWA, P + d.obA,
-                                     net->hidden_act, nullptr, nullptr, 0, s);
+    rc = g.dim == 2 ? conv_launch<2>(g, d.nf, 16, net->features, P + d.oWA, P + d.obA,
+                                     net->hidden_act, nullptr, nullptr, s)
+                    : conv_launch<3>(g, d.nf, 16, net->features, P + d.oWA, P + d.obA,
+                                     net->hidden_act, nullptr, nullptr, s);
     if (rc) return rc;
     hipLaunchKernelGGL((k_gate_b<16, 16>), dim3(nblk(g.N)), dim3(kBS), 0, s, g.N,
                        (const float *)net->hidden_act, P + d.oWB, P + d.obB, net->gates,
@@ -1016,34 +1101,36 @@ extern "C" int adlbr_net_backward(adlbr_operator *op, const adlbr_net *net, cons
     hipStream_t s = as_stream(stream);
     const float *L = net->layers;
     const float *G = net->gates;
-    const int taps = d.T;
     // gradients of the expanded layers go to w.gl, then fold onto W1, W2
     hipLaunchKernelGGL(k_fill_f32, dim3(nblk((long long)d.lcount)), dim3(kBS), 0, s, w.gl,
                        (long long)d.lcount, 0.f);
     // layer 4: out = pre4 * G[48]; dL/dout = gz
-    const float *gcur = gz;
     const size_t offs[4] = {0, 16, 32, 48};
     const int cins[4] = {1, 16, 16, 16}, couts[4] = {16, 16, 16, 1};
     const size_t oW[4] = {d.l1, d.l2, d.l3, d.l4};
+    // ga: the gradient of a layer's pre-gate output; the last layer's here, the
+    // others' with their gates' gradients as the layer above is passed back
     float *gbuf[2] = {w.g0, w.g1};
+    const float *ga = w.ga;
+    hipLaunchKernelGGL(k_gate_grad, dim3(nblk(N)), dim3(kBS), 0, s, N, gz, G + 48 * N,
+                       saved + 48 * N, w.ga, ggates + 48 * N);
     for (int l = 3; l >= 0; --l) {
-        const long long n = (long long)couts[l] * N;
-        hipLaunchKernelGGL(k_gate_grad, dim3(nblk(n)), dim3(kBS), 0, s, n, gcur, G + offs[l] * N,
-                           saved + offs[l] * N, w.ga, ggates + offs[l] * N);
         // input of layer l: r, or the previous layer's pre-gate output times its gates
         const float *in = l == 0 ? r : saved + offs[l - 1] * N;
         const float *in_gate = l == 0 ? nullptr : G + offs[l - 1] * N;
-        rc = g.dim == 2 ? bwd_w_launch<2>(g, cins[l], couts[l], taps, in, in_gate, 0, w.ga,
-                                          w.partials, w.gl + oW[l], nullptr, s)
-                        : bwd_w_launch<3>(g, cins[l], couts[l], taps, in, in_gate, 0, w.ga,
-                                          w.partials, w.gl + oW[l], nullptr, s);
+        rc = g.dim == 2 ? bwd_w_launch<2>(g, cins[l], couts[l], in, in_gate, ga, w.partials,
+                                          w.gl + oW[l], nullptr, s)
+                        : bwd_w_launch<3>(g, cins[l], couts[l], in, in_gate, ga, w.partials,
+                                          w.gl + oW[l], nullptr, s);
         if (rc) return rc;
         if (l > 0) {
             float *gin = gbuf[l & 1];
-            rc = g.dim == 2 ? bwd_data_launch<2>(g, cins[l], couts[l], w.ga, L + oW[l], gin, s)
-                            : bwd_data_launch<3>(g, cins[l], couts[l], w.ga, L + oW[l], gin, s);
+            rc = g.dim == 2 ? bwd_data_launch<2>(g, cins[l], couts[l], ga, L + oW[l], in, in_gate,
+                                                 gin, ggates + offs[l - 1] * N, s)
+                            : bwd_data_launch<3>(g, cins[l], couts[l], ga, L + oW[l], in, in_gate,
+                                                 gin, ggates + offs[l - 1] * N, s);
             if (rc) return rc;
-            gcur = gin;
+            ga = gin;
         }
     }
     hipLaunchKernelGGL(k_fold_weight_grads, dim3(16), dim3(kBS), 0, s, (const float *)w.gl,
@@ -1072,23 +1159,17 @@ extern "C" int adlbr_net_gates_backward(adlbr_operator *op, const adlbr_net *net
     }
     hipStream_t s = as_stream(stream);
     const float *P = net->params;
-    // fold the expanded gate gradients onto g1, g2 (into w.ga); then
-    // gg = dg g (1 - g) in place (the first 2W expanded gates are g1, g2);
-    // gh (in w.g0) = WB^T gg * [h > 0]
-    hipLaunchKernelGGL(k_fold_gate_grads, dim3(nblk(N)), dim3(kBS), 0, s, N, d.W, ggates, w.ga);
-    hipLaunchKernelGGL((k_gate_b_bwd<16, 32>), dim3(nblk(N)), dim3(kBS), 0, s, N, net->gates, w.ga,
-                       net->hidden_act, P + d.oWB, w.g0);
-    // WB, bB: 1x1 layer, input relu(h)
-    rc = g.dim == 2 ? bwd_w_launch<2>(g, 16, 32, 1, net->hidden_act, nullptr, 1, w.ga, w.partials,
-                                      gparams + d.oWB, gparams + d.obB, s)
-                    : bwd_w_launch<3>(g, 16, 32, 1, net->hidden_act, nullptr, 1, w.ga, w.partials,
-                                      gparams + d.oWB, gparams + d.obB, s);
-    if (rc) return rc;
-    // WA, bA: conv on the features
-    rc = g.dim == 2 ? bwd_w_launch<2>(g, d.nf, 16, d.T, net->features, nullptr, 0, w.g0,
-                                      w.partials, gparams + d.oWA, gparams + d.obA, s)
-                    : bwd_w_launch<3>(g, d.nf, 16, d.T, net->features, nullptr, 0, w.g0,
-                                      w.partials, gparams + d.oWA, gparams + d.obA, s);
+    // gh (in w.g0) and the gradients of WB, bB, then those of WA, bA from gh
+    const long long nchunk = (N + 255) / 256;
+    const int nb = (int)(nchunk < kWgBlocks ? nchunk : kWgBlocks);
+    hipLaunchKernelGGL((k_gate_bwd<16, 16>), dim3(nb), dim3(256), 0, s, N, ggates,
+                       (const float *)net->gates, (const float *)net->hidden_act, P + d.oWB, w.g0,
+                       w.partials);
+    reduce_launch(w.partials, nb, 32 * 16 + 32, 32 * 16, gparams + d.oWB, gparams + d.obB, s);
+    rc = g.dim == 2 ? bwd_w_launch<2>(g, d.nf, 16, net->features, nullptr, w.g0, w.partials,
+                                      gparams + d.oWA, gparams + d.obA, s)
+                    : bwd_w_launch<3>(g, d.nf, 16, net->features, nullptr, w.g0, w.partials,
+                                      gparams + d.oWA, gparams + d.obA, s);
     if (rc) return rc;
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
