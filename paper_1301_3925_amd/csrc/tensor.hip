@@ -58,30 +58,69 @@ __device__ __forceinline__ int mirror(int i, int n) {
     return i < n ? i : p - 1 - i;
 }
 
-// Blur `planes` planes along axis `ax`; blockIdx.y selects the plane.
+// The kBO consecutive outputs along an axis from position p0 of one line (src:
+// its first value, `stride` apart, len values, mirrored past its ends): the
+// line's values are read once, not once per output, and every output sums its
+// taps in the order j = 0 .. 2 r.
+constexpr int kBO = 4;
 template <typename T>
-__global__ void k_blur(GridInfo g, const T *__restrict__ in, T *__restrict__ out, int ax, Taps t) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long N = g.N;
-    if (i >= N) return;
-    const long long off = (long long)blockIdx.y * N;
-    const int nx = g.nx, ny = g.ny;
-    const int x = (int)(i % nx);
-    const long long rest = i / nx;
-    const int y = (int)(rest % ny);
-    const int z = (int)(rest / ny);
-    const int p = ax == 0 ? x : (ax == 1 ? y : z);
-    const int len = ax == 0 ? nx : (ax == 1 ? ny : g.nz);
-    const long long stride = ax == 0 ? 1 : (ax == 1 ? (long long)nx : (long long)nx * ny);
-    const T *src = in + off + i - (long long)p * stride;
-    T acc = (T)0;
-    if (p - t.r >= 0 && p + t.r < len) {
-        for (int k = -t.r; k <= t.r; ++k) acc += tap<T>(t, k + t.r) * src[(long long)(p + k) * stride];
-    } else {
-        for (int k = -t.r; k <= t.r; ++k)
-            acc += tap<T>(t, k + t.r) * src[(long long)mirror(p + k, len) * stride];
+__device__ __forceinline__ void blur_line(const T *__restrict__ src, long long stride, int p0, int len,
+                                          const Taps &t, T (&acc)[kBO]) {
+#pragma unroll
+    for (int o = 0; o < kBO; ++o) acc[o] = (T)0;
+    const int n = 2 * t.r + kBO;  // values p0 - r .. p0 + r + kBO - 1
+    const bool inside = p0 - t.r >= 0 && p0 + t.r + kBO - 1 < len;
+    constexpr int B = 8;
+    for (int k0 = 0; k0 < n; k0 += B) {  // uniform; B loads in flight
+        T v[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int p = p0 - t.r + min(k0 + b, n - 1);
+            v[b] = src[(long long)(inside ? p : mirror(p, len)) * stride];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int o = 0; o < kBO; ++o) {
+                const int j = k0 + b - o;  // uniform
+                if (j >= 0 && j <= 2 * t.r) acc[o] += tap<T>(t, j) * v[b];
+            }
     }
-    out[off + i] = acc;
+}
+
+// Blur planes along axis AX, kBO consecutive outputs of a line per thread;
+// blockIdx.y selects the plane.  Threads run along x, then y, then z of the
+// grid shortened kBO-fold along AX.
+template <typename T, int AX>
+__global__ __launch_bounds__(256) void k_blur(GridInfo g, const T *__restrict__ in,
+                                              T *__restrict__ out, Taps t) {
+    const unsigned cx = AX == 0 ? (unsigned)(g.nx + kBO - 1) / kBO : (unsigned)g.nx;
+    const unsigned cy = AX == 1 ? (unsigned)(g.ny + kBO - 1) / kBO : (unsigned)g.ny;
+    const unsigned cz = AX == 2 ? (unsigned)(g.nz + kBO - 1) / kBO : (unsigned)g.nz;
+    const unsigned i = blockIdx.x * 256u + threadIdx.x;  // N < 2^28
+    const unsigned r = i / cx, x0 = i - r * cx, z0 = r / cy, y0 = r - z0 * cy;
+    if (z0 >= cz) return;
+    const int x = (int)x0 * (AX == 0 ? kBO : 1), y = (int)y0 * (AX == 1 ? kBO : 1);
+    const int z = (int)z0 * (AX == 2 ? kBO : 1);
+    const int p0 = AX == 0 ? x : AX == 1 ? y : z, len = AX == 0 ? g.nx : AX == 1 ? g.ny : g.nz;
+    const long long stride = AX == 0 ? 1 : AX == 1 ? g.nx : (long long)g.nx * g.ny;
+    const long long at = (long long)blockIdx.y * g.N + x + (long long)g.nx * (y + (long long)g.ny * z);
+    T acc[kBO];
+    blur_line<T>(in + at - p0 * stride, stride, p0, len, t, acc);
+#pragma unroll
+    for (int o = 0; o < kBO; ++o)
+        if (p0 + o < len) out[at + o * stride] = acc[o];
+}
+
+template <typename T>
+void launch_blur(const GridInfo &g, int planes, const T *in, T *out, int ax, const Taps &t,
+                 hipStream_t s) {
+    const auto cut = [&](int n, int a) { return (long long)(a == ax ? (n + kBO - 1) / kBO : n); };
+    const long long n = cut(g.nx, 0) * cut(g.ny, 1) * cut(g.nz, 2);
+    const dim3 grid((unsigned)((n + 255) / 256), planes);
+    if (ax == 0) hipLaunchKernelGGL((k_blur<T, 0>), grid, dim3(256), 0, s, g, in, out, t);
+    else if (ax == 1) hipLaunchKernelGGL((k_blur<T, 1>), grid, dim3(256), 0, s, g, in, out, t);
+    else hipLaunchKernelGGL((k_blur<T, 2>), grid, dim3(256), 0, s, g, in, out, t);
 }
 
 // grad u_sigma by central differences (mirror boundary), outer products.
@@ -163,15 +202,13 @@ __global__ void k_eigmap2(long long N, const T *__restrict__ J, T *__restrict__ 
     D[2 * N + i] = l2 + dl * vy * vy;
 }
 
-// 3D eigen map: cyclic Jacobi rotations on the symmetric 3x3 J.
+// 3D eigen map: cyclic Jacobi rotations on the symmetric 3x3 J (xx, xy, xz,
+// yy, yz, zz), each by the smaller angle in its algebraic form (tan from the
+// half-angle's quadratic: no trigonometric functions; errors against FP64 a
+// fifth to a third below those of rotations by cos and sin).
 template <typename T>
-__global__ void k_eigmap3(long long N, const T *__restrict__ J, T *__restrict__ D, T alpha, T C,
-                          int map) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    T A[3][3] = {{J[i], J[N + i], J[2 * N + i]},
-                 {J[N + i], J[3 * N + i], J[4 * N + i]},
-                 {J[2 * N + i], J[4 * N + i], J[5 * N + i]}};
+__device__ __forceinline__ void eigmap3(const T J[6], T D[6], T alpha, T C, int map) {
+    T A[3][3] = {{J[0], J[1], J[2]}, {J[1], J[3], J[4]}, {J[2], J[4], J[5]}};
     T V[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
     const T eps = sizeof(T) == 8 ? (T)1e-15 : (T)1e-7;
     for (int sweep = 0; sweep < 12; ++sweep) {
@@ -181,36 +218,49 @@ __global__ void k_eigmap3(long long N, const T *__restrict__ J, T *__restrict__ 
 #pragma unroll
         for (int pq = 0; pq < 3; ++pq) {
             const int p = pq == 2 ? 1 : 0, q = pq == 0 ? 1 : 2;
-            if (A[p][q] == (T)0) continue;
-            // rotation zeroing A[p][q]: tan 2th = 2 A_pq / (A_qq - A_pp)
-            const T th = (T)0.5 * atan2((T)2 * A[p][q], A[q][q] - A[p][p]);
-            const T cs = cos(th), sn = sin(th);
-            for (int k = 0; k < 3; ++k) {
-                const T akp = A[k][p], akq = A[k][q];
-                A[k][p] = cs * akp - sn * akq;
-                A[k][q] = sn * akp + cs * akq;
-            }
-            for (int k = 0; k < 3; ++k) {
-                const T apk = A[p][k], aqk = A[q][k];
-                A[p][k] = cs * apk - sn * aqk;
-                A[q][k] = sn * apk + cs * aqk;
-            }
+            const T apq = A[p][q];
+            if (apq == (T)0) continue;
+            // t = tan of the angle that zeroes A[p][q], |t| <= 1
+            // (formed from quotients in [-1, 1]: squares of tiny J vanish)
+            const T h0 = A[q][q] - A[p][p], b0 = (T)2 * apq;
+            const T m = fmax(fabs(h0), fabs(b0)), h = h0 / m, b = b0 / m;
+            const T t = b / (h + copysign(sqrt(h * h + b * b), h));
+            // Rutishauser's form of the update: small corrections to the old
+            // values, the zeroed entry exact
+            const T cs = (T)1 / sqrt((T)1 + t * t), sn = t * cs, tau = sn / ((T)1 + cs);
+            const int r = 3 - p - q;
+            A[p][p] -= t * apq;
+            A[q][q] += t * apq;
+            A[p][q] = A[q][p] = (T)0;
+            const T arp = A[r][p], arq = A[r][q];
+            A[r][p] = A[p][r] = arp - sn * (arq + tau * arp);
+            A[r][q] = A[q][r] = arq + sn * (arp - tau * arq);
+#pragma unroll
             for (int k = 0; k < 3; ++k) {
                 const T vkp = V[k][p], vkq = V[k][q];
-                V[k][p] = cs * vkp - sn * vkq;
-                V[k][q] = sn * vkp + cs * vkq;
+                V[k][p] = vkp - sn * (vkq + tau * vkp);
+                V[k][q] = vkq + sn * (vkp - tau * vkq);
             }
         }
     }
-    int o[3] = {0, 1, 2};
+    // eigenpairs by descending eigenvalue (component by component: whole
+    // columns chosen by index would go to scratch memory)
+    T mu[3] = {A[0][0], A[1][1], A[2][2]};
+#pragma unroll
     for (int a = 0; a < 3; ++a)
-        for (int b = a + 1; b < 3; ++b)
-            if (A[o[b]][o[b]] > A[o[a]][o[a]]) {
-                const int t = o[a];
-                o[a] = o[b];
-                o[b] = t;
+#pragma unroll
+        for (int b = a + 1; b < 3; ++b) {
+            const bool sw = mu[b] > mu[a];
+            const T m = mu[a];
+            mu[a] = sw ? mu[b] : m;
+            mu[b] = sw ? m : mu[b];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const T v = V[k][a];
+                V[k][a] = sw ? V[k][b] : v;
+                V[k][b] = sw ? v : V[k][b];
             }
-    const T mu[3] = {A[o[0]][o[0]], A[o[1]][o[1]], A[o[2]][o[2]]};
+        }
     T lam[3];
     if (map == ADLBR_MAP_CED) {
         lam[0] = alpha;
@@ -221,11 +271,40 @@ __global__ void k_eigmap3(long long N, const T *__restrict__ J, T *__restrict__ 
         lam[1] = eed(C, mu[1]);
         lam[2] = (T)1;
     }
-    const int pr[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
+    constexpr int pr[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
+#pragma unroll
     for (int q = 0; q < 6; ++q) {
         T acc = (T)0;
-        for (int k = 0; k < 3; ++k) acc += lam[k] * V[pr[q][0]][o[k]] * V[pr[q][1]][o[k]];
-        D[q * N + i] = acc;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) acc += lam[k] * V[pr[q][0]][k] * V[pr[q][1]][k];
+        D[q] = acc;
+    }
+}
+
+// The last blur of J (along z) with the eigen map behind it: kBO points of a
+// column per thread, so that the blurred J does not cross HBM.  100^3, radius
+// 6: the blurs and the map of a tensor took 244 + 64 us as passes of one
+// output per thread with trigonometric rotations.
+template <typename T>
+__global__ __launch_bounds__(256) void k_blur_eigmap3(GridInfo g, const T *__restrict__ J,
+                                                      T *__restrict__ D, Taps t, T alpha, T C,
+                                                      int map) {
+    const unsigned plane = (unsigned)g.nx * (unsigned)g.ny, i = blockIdx.x * 256u + threadIdx.x;
+    const unsigned zc = i / plane, xy = i - zc * plane;
+    const int z = (int)zc * kBO;
+    if (z >= g.nz) return;
+    T v[6][kBO];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) blur_line<T>(J + c * g.N + xy, plane, z, g.nz, t, v[c]);
+#pragma unroll
+    for (int o = 0; o < kBO; ++o) {
+        if (z + o >= g.nz) break;
+        const T j[6] = {v[0][o], v[1][o], v[2][o], v[3][o], v[4][o], v[5][o]};
+        T d[6];
+        eigmap3<T>(j, d, alpha, C, map);
+        const long long at = (long long)(z + o) * plane + xy;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) D[c * g.N + at] = d[c];
     }
 }
 
@@ -468,28 +547,28 @@ int run_tensor(const GridInfo &g, const T *u, int ncomp, const adlbr_tensor_para
     }
     if (g.dim == 2) {
         for (int c = 0; c < ncomp; ++c) {  // u_sigma of component c, its products
-            hipLaunchKernelGGL(k_blur<T>, dim3(nb, 1), dim3(256), 0, s, g, u + c * N, wb, 0, ts);
-            hipLaunchKernelGGL(k_blur<T>, dim3(nb, 1), dim3(256), 0, s, g, (const T *)wb, wb + N, 1, ts);
+            launch_blur<T>(g, 1, u + c * N, wb, 0, ts, s);
+            launch_blur<T>(g, 1, wb, wb + N, 1, ts, s);
             hipLaunchKernelGGL(k_grad_outer<T>, dim3(nb), dim3(256), 0, s, g, (const T *)(wb + N), wa,
                                c > 0 ? 1 : 0);
         }
-        hipLaunchKernelGGL(k_blur<T>, dim3(nb, nj), dim3(256), 0, s, g, (const T *)wa, wb, 0, tr);
-        hipLaunchKernelGGL(k_blur<T>, dim3(nb, nj), dim3(256), 0, s, g, (const T *)wb, wa, 1, tr);
+        launch_blur<T>(g, nj, wa, wb, 0, tr, s);
+        launch_blur<T>(g, nj, wb, wa, 1, tr, s);
         hipLaunchKernelGGL(k_eigmap2<T>, dim3(nb), dim3(256), 0, s, N, (const T *)wa, D,
                            (T)p->alpha, (T)p->C, p->eig_map);
     } else {
         for (int c = 0; c < ncomp; ++c) {
-            hipLaunchKernelGGL(k_blur<T>, dim3(nb, 1), dim3(256), 0, s, g, u + c * N, wa, 0, ts);
-            hipLaunchKernelGGL(k_blur<T>, dim3(nb, 1), dim3(256), 0, s, g, (const T *)wa, wa + N, 1, ts);
-            hipLaunchKernelGGL(k_blur<T>, dim3(nb, 1), dim3(256), 0, s, g, (const T *)(wa + N), wa, 2, ts);
+            launch_blur<T>(g, 1, u + c * N, wa, 0, ts, s);
+            launch_blur<T>(g, 1, wa, wa + N, 1, ts, s);
+            launch_blur<T>(g, 1, wa + N, wa, 2, ts, s);
             hipLaunchKernelGGL(k_grad_outer<T>, dim3(nb), dim3(256), 0, s, g, (const T *)wa, wb,
                                c > 0 ? 1 : 0);
         }
-        hipLaunchKernelGGL(k_blur<T>, dim3(nb, nj), dim3(256), 0, s, g, (const T *)wb, wa, 0, tr);
-        hipLaunchKernelGGL(k_blur<T>, dim3(nb, nj), dim3(256), 0, s, g, (const T *)wa, wb, 1, tr);
-        hipLaunchKernelGGL(k_blur<T>, dim3(nb, nj), dim3(256), 0, s, g, (const T *)wb, wa, 2, tr);
-        hipLaunchKernelGGL(k_eigmap3<T>, dim3(nb), dim3(256), 0, s, N, (const T *)wa, D,
-                           (T)p->alpha, (T)p->C, p->eig_map);
+        launch_blur<T>(g, nj, wb, wa, 0, tr, s);
+        launch_blur<T>(g, nj, wa, wb, 1, tr, s);
+        const long long nc = (long long)((g.nz + kBO - 1) / kBO) * g.nx * g.ny;
+        hipLaunchKernelGGL(k_blur_eigmap3<T>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, g,
+                           (const T *)wb, D, tr, (T)p->alpha, (T)p->C, p->eig_map);
     }
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
