@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kBS) void k_dot_self(long long N, const float *r, d
     block_partial_sum(v, part);
 }
 
-__global__ __launch_bounds__(kBS) void k_dot_self_fin(LossState *ls, const double *part,
+__global__ __launch_bounds__(kFinish) void k_dot_self_fin(LossState *ls, const double *part,
                                                       long long nb) {
     const double t = reduce_partials(part, nb);
     if (threadIdx.x == 0) ls->rr = t;
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(kBS) void k_loss_grad(long long N, const float *z, 
 }
 
 // loss += sum of the partials
-__global__ __launch_bounds__(kBS) void k_loss_fin(const double *part, long long nb, double *loss) {
+__global__ __launch_bounds__(kFinish) void k_loss_fin(const double *part, long long nb, double *loss) {
     const double t = reduce_partials(part, nb);
     if (threadIdx.x == 0) *loss += t;
 }
@@ -938,8 +938,7 @@ __global__ __launch_bounds__(kBS) void k_dots2(long long N, const float *__restr
         a = zi * (double)r[i];
         if (rp) b = zi * (double)rp[i];
     }
-    block_partial_sum(a, part);
-    block_partial_sum(b, part + gridDim.x);
+    block_partial_sum2(a, b, part, part + gridDim.x);
 }
 }  // namespace
 
@@ -1194,12 +1193,12 @@ extern "C" int adlbr_net_loss_grad(adlbr_operator *op, double dt, const float *r
     double *part = (double *)((char *)workspace + align_up(sizeof(LossState)));
     const long long nb = nblk(N);
     hipLaunchKernelGGL(k_dot_self, dim3(nb), dim3(kBS), 0, s, N, r, part);
-    hipLaunchKernelGGL(k_dot_self_fin, dim3(1), dim3(kBS), 0, s, ls, (const double *)part, nb);
+    hipLaunchKernelGGL(k_dot_self_fin, dim3(1), dim3(kFinish), 0, s, ls, (const double *)part, nb);
     int rc = apply_K(op, z, gz, dt, s);  // gz = K z
     if (rc) return rc;
     hipLaunchKernelGGL(k_loss_grad, dim3(nb), dim3(kBS), 0, s, N, z, r, gz, (const LossState *)ls,
                        part);
-    hipLaunchKernelGGL(k_loss_fin, dim3(1), dim3(kBS), 0, s, (const double *)part, nb, loss);
+    hipLaunchKernelGGL(k_loss_fin, dim3(1), dim3(kFinish), 0, s, (const double *)part, nb, loss);
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
 }

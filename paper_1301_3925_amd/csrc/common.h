@@ -198,18 +198,37 @@ __device__ __forceinline__ long long wave_group(const GridInfo &g, long long blk
 // Device-resident scalars of a (flexible) conjugate-gradient iteration.
 struct CgState {
     double dt;      // K = I + dt A
-    double rz;      // <z_k, r_k>
-    double rz_old;  // <z_{k-1}, r_{k-1}>
-    double zr_prev; // <z_k, r_{k-1}> (flexible CG)
-    double pq;      // <p_k, K p_k>
-    double alpha, beta;
+    double rz[2];   // <z_k, r_k>: Jacobi-PCG alternates the slots, flexible CG keeps to the first
+    double pq;      // <p_k, K p_k>, 1 before the first update
+    double beta;    // flexible CG
     double rr;      // |r_k|^2
     double bb;      // |b|^2
+    double tol2bb;  // tol^2 |b|^2
     int32_t bad;    // non-descent direction or non-finite value
     int32_t iter;
     int32_t done;   // recurrence residual below tolerance: later kernels are no-ops
-    int32_t pad;
+    int32_t halt;   // done or bad, as the update found them (the direction's early way out)
 };
+__device__ inline bool cg_breakdown(double pq) { return !(pq > 0.0) || !isfinite(pq); }
+// Whether a kernel behind an update is a no-op.  The update does not raise
+// bad itself: its own later blocks read the flags, and must all find the same.
+__device__ inline bool cg_stopped(const CgState *st) {
+    return st->bad || st->done || cg_breakdown(st->pq);
+}
+
+// What the Jacobi-PCG direction needs to finish the update before it: the
+// update's nu partials of <z, r> (null: nothing to finish, beta comes from
+// the state) and of |r|^2, the slot of rz that holds the last iteration's
+// value, and the history of |r|^2.
+struct CgTail {
+    const double *prz, *prr;
+    int nu, slot;
+    double *hist;
+    int max_hist;
+};
+// Blocks of the solvers' vector update, at most (two per CU), so partials of
+// each of its dots: few enough that every block of the direction sums them.
+constexpr int kUpdBlocks = 512;
 
 struct adlbr_net_impl;
 // Learned preconditioner z = N(r) for K = I + dt A (defined with the CNN).
@@ -273,10 +292,10 @@ int batch_launch(const adlbr_operator *rep, const BatchProb *probs, const BatchP
                  int nprob, long long nblocks, int parity, int variant, int copy, hipStream_t s);
 
 // Internal entry points shared between translation units.
-// Direction update q = K z + beta q, p = z + beta p and alpha = <z,r>/<p,q>
+// Direction update q = K z + beta q, p = z + beta p and the partials of <p, q>
 // (partial: one double per 256-point block).
 int cg_direction(const adlbr_operator *op, const void *z, void *q, void *p, CgState *st,
-                 double *partial, int first, hipStream_t s);
+                 double *partial, int first, const CgTail &tail, hipStream_t s);
 // |b - (I + dt A) x|^2 for an FP64 iterate x, accumulated in FP64 into
 // *out (deterministic); the residual itself goes to rout (storage dtype) if
 // rout is not null.  partial: one double per 256-point block.
@@ -289,18 +308,20 @@ int true_residual(const adlbr_operator *op, double dt, const void *b, const doub
 // device-scope atomics serialize across the XCDs, so a "last block
 // finishes" ticket costs far more than the extra launch; the fixed order
 // also makes every reduction deterministic.
-// Block sum of v over the block's threads (blockDim.x == 256) into
-// partial[blockIdx.x].  All threads must call it.
-__device__ inline void block_partial_sum(double v, double *partial) {
-    __shared__ double red[256];
-    red[threadIdx.x] = v;
+// Block sum of v over the block's threads (blockDim.x == 256) into *out:
+// butterfly sums within each wave, then the four wave sums in wave order;
+// fixed order, so deterministic.  All threads must call it.
+__device__ inline void block_sum_to(double v, double *out) {
+    __shared__ double red[4];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) *out = ((red[0] + red[1]) + red[2]) + red[3];
     __syncthreads();  // red[] may be reused by a second call
+}
+__device__ inline void block_partial_sum(double v, double *partial) {
+    block_sum_to(v, partial + blockIdx.x);
 }
 
 // Block sums of a and b into pa[blockIdx.x] and pb[blockIdx.x] in one pass
@@ -326,43 +347,48 @@ __device__ inline void block_partial_sum2(double a, double b, double *pa, double
 
 // Block maximum of v into partial[blockIdx.x] (blockDim.x == 256).
 __device__ inline void block_partial_max(double v, double *partial) {
-    __shared__ double red[256];
-    red[threadIdx.x] = v;
+    __shared__ double red[4];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v = fmax(v, __shfl_xor(v, d, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) partial[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
     __syncthreads();
 }
 
-// Sum (or max, when take_max) of partial[0 .. n) by a single block of 256
-// threads in a fixed order; every thread gets the result.
+// Sum (or max, when take_max) of partial[0 .. n) by a single block of
+// kFinish threads in a fixed order; every thread gets the result.  One block
+// runs at the latency of its loads: kFinish threads with eight loads in
+// flight each take 8192 partials (2 M points) in one round trip.
+constexpr int kFinish = 1024;
 __device__ inline double reduce_partials(const double *partial, long long n, bool take_max = false) {
-    __shared__ double red[256];
-    double acc = take_max ? -1.0e308 : 0.0;
-    long long b = threadIdx.x;
-    // eight independent loads in flight, then added in the same order as a
-    // plain strided loop would
-    for (; b + 7 * 256 < n; b += 8 * 256) {
+    __shared__ double red[kFinish / 64];
+    const double none = take_max ? -1.0e308 : 0.0;
+    double acc = none;
+    for (long long b0 = threadIdx.x; b0 - threadIdx.x < n; b0 += 8 * kFinish) {
         double v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = partial[b + 256 * j];
+        for (int j = 0; j < 8; ++j) {
+            const long long b = b0 + kFinish * j;
+            v[j] = partial[b < n ? b : 0];
+        }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc = take_max ? fmax(acc, v[j]) : acc + v[j];
+        for (int j = 0; j < 8; ++j) {
+            const double w = b0 + kFinish * j < n ? v[j] : none;
+            acc = take_max ? fmax(acc, w) : acc + w;
+        }
     }
-    for (; b < n; b += 256) acc = take_max ? fmax(acc, partial[b]) : acc + partial[b];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            red[threadIdx.x] = take_max ? fmax(red[threadIdx.x], red[threadIdx.x + s])
-                                        : red[threadIdx.x] + red[threadIdx.x + s];
-        __syncthreads();
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const double o = __shfl_xor(acc, d, 64);
+        acc = take_max ? fmax(acc, o) : acc + o;
     }
-    const double t = red[0];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
+    double t = red[0];
+#pragma unroll
+    for (int j = 1; j < kFinish / 64; ++j) t = take_max ? fmax(t, red[j]) : t + red[j];
+    __syncthreads();  // red[] may be reused by a second call
     return t;
 }
 

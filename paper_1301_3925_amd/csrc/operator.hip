@@ -1482,7 +1482,7 @@ __global__ __launch_bounds__(256) void k_scan_top(const int32_t *in, int32_t *ou
 
 // dt_CFL = 1 / max_z A_zz from the per-block maxima; the end of an assembly
 // also settles the status word.
-__global__ __launch_bounds__(256) void k_cfl(const double *dpart, long long nb, double *maxdiag,
+__global__ __launch_bounds__(kFinish) void k_cfl(const double *dpart, long long nb, double *maxdiag,
                                              double *dtcfl, int32_t *status) {
     const double m = reduce_partials(dpart, nb, true);
     if (threadIdx.x != 0) return;
@@ -2343,7 +2343,7 @@ __global__ __launch_bounds__(256) void k_reach_wmax(GridInfo g,
 
 // hnear = min(hmax, reach) (0 for the list layout: every edge is listed)
 // and the largest weight.
-__global__ __launch_bounds__(256) void k_tile_params(const double *rpart, const double *wpart,
+__global__ __launch_bounds__(kFinish) void k_tile_params(const double *rpart, const double *wpart,
                                                      long long nb, int hmax, int32_t *hnear,
                                                      double *wmax) {
     const double r = reduce_partials(rpart, nb, true);
@@ -2353,60 +2353,122 @@ __global__ __launch_bounds__(256) void k_tile_params(const double *rpart, const 
     *wmax = wm;
 }
 
+// The scalars of a Jacobi-PCG direction: every block sums the update's
+// partials in the same order, so all come to the same beta and the same
+// decision to stop; one thread of the grid writes them down.  The old <z, r>
+// keeps its slot for the blocks that are still to start; a flag that such a
+// block already sees raised says what its own sums would, and one thread
+// reads it for the whole block.  The loads are issued before the row's, the
+// sums taken while those are in flight.
+struct CgSums {
+    double rz[kUpdBlocks / kBS], rr[kUpdBlocks / kBS], rzo, tol;
+    bool stop;
+    __device__ __forceinline__ void issue(const CgState *st, const CgTail &t) {
+#pragma unroll
+        for (int j = 0; j < kUpdBlocks / kBS; ++j) {
+            const int i = (int)threadIdx.x + kBS * j < t.nu ? (int)threadIdx.x + kBS * j : 0;
+            rz[j] = t.prz[i];
+            rr[j] = t.prr[i];
+        }
+        rzo = st->rz[t.slot];
+        tol = st->tol2bb;
+        stop = cg_stopped(st);
+    }
+    // whether the iteration goes on, and its beta
+    __device__ __forceinline__ bool finish(CgState *st, const CgTail &t, double *beta) const {
+        __shared__ double red[2][kBS / 64];
+        __shared__ int halt;
+        double rzn = 0.0, rrn = 0.0;
+#pragma unroll
+        for (int j = 0; j < kUpdBlocks / kBS; ++j) {
+            const bool in = (int)threadIdx.x + kBS * j < t.nu;
+            rzn += in ? rz[j] : 0.0;
+            rrn += in ? rr[j] : 0.0;
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            rzn += __shfl_xor(rzn, d, 64);
+            rrn += __shfl_xor(rrn, d, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            red[0][threadIdx.x >> 6] = rzn;
+            red[1][threadIdx.x >> 6] = rrn;
+        }
+        if (threadIdx.x == 0) halt = stop;
+        __syncthreads();
+        const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
+        if (halt) {
+            if (writer && !st->done) st->bad = 1;
+            return false;
+        }
+        rzn = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+        rrn = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
+        const bool bad = !isfinite(rzn) || !isfinite(rrn) || !(rzo > 0.0), done = rrn <= tol;
+        if (writer) {
+            st->rz[t.slot ^ 1] = rzn;
+            st->rr = rrn;
+            const int it = st->iter + 1;
+            st->iter = it;
+            if (it < t.max_hist) t.hist[it] = rrn;
+            if (bad) st->bad = 1;
+            if (done) st->done = 1;
+        }
+        *beta = rzn / rzo;
+        return !bad && !done;
+    }
+};
+
 // Conjugate-gradient direction with K = I + dt A (dt from the state):
 //   q = K z + beta q,  p = z + beta p  (beta = 0 on the first iteration),
 // so that q = K p without a second gather.  Each block writes its partial
-// <p, q> in FP64 (partial[blk]); k_cg_alpha sums them in block order and
-// sets alpha = <z, r> / <p, q>.
+// <p, q> in FP64 (partial[blk]); the update sums them for alpha.
+//
+// An iteration is the update and this kernel: each sums the other's partials
+// at its start instead of leaving them to a one-block kernel in between,
+// which costs 5 us and a launch's gap twice an iteration whatever the grid.
+// A solve of 32 iterations on 1024^2 FP32: 1.56 ms with them, 1.39 without;
+// one of 128^3 to 1e-4 (31 iterations): 3.21 and 3.11 ms.
 template <int DIM, bool WIDE, bool PER, bool MG, typename T>
 __global__ __launch_bounds__(kBS) void k_cg_direction(
     GridInfo g, const T *__restrict__ zv, T *__restrict__ q, T *__restrict__ p,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const void *__restrict__ wp,
     const int32_t *__restrict__ pos, const int32_t *__restrict__ ent,
-    const EntRec<T> *__restrict__ went, const CgState *st,
-    double *partial, int first) {
+    const EntRec<T> *__restrict__ went, CgState *st, double *partial, int first, CgTail tail) {
+    // a finished solve: the rest of the batch costs its launches
+    if (tail.prz ? st->halt : cg_stopped(st)) return;
+    CgSums sums;
+    if (tail.prz) sums.issue(st, tail);
     const long long N = g.N;
     // the apply's block order (XCD bands; 3D strips of planes)
     const long long blk = strip_block(xcd_block(blockIdx.x, gridDim.x), g, kApplyPoints);
     const long long z0 = wave_group(g, blk), z = z0 + (threadIdx.x & 63);
     const bool live = z < N;
     double pqz = 0.0;
-    const bool skip = st->bad || st->done;
     const WaveLists L = wave_lists(pos, z, N);
     const T zz = live ? zv[z] : (T)0;
     OwnEdges<DIM, WIDE, PER, MG, T, T> edges;
-    edges.load(g, z, live && !skip, sb, wp);
+    edges.load(g, z, live, sb, wp);
+    double beta64 = first ? 0.0 : st->beta;
+    if (tail.prz && !sums.finish(st, tail, &beta64)) return;
     OwnPart<decltype(edges), T, T> own;
     own.issue(edges, zv);
-    T acc = skip ? (T)0 : wave_incoming<MG, DIM == 2 ? 3 : 6, T, T, T>(L, z0, N, zz, zv, (const T *)wp,
-                                                                       ent, went);
-    if (live && !skip) {
+    // requested with the gathers, so that the row does not wait a second time
+    T qo = (T)0, po = (T)0;
+    if (!first) {
+        qo = q[live ? z : 0];
+        po = p[live ? z : 0];
+    }
+    T acc = wave_incoming<MG, DIM == 2 ? 3 : 6, T, T, T>(L, z0, N, zz, zv, (const T *)wp, ent, went);
+    if (live) {
         acc += own.sum(edges, zz);
-        const T dt = (T)st->dt;
-        const T beta = first ? (T)0 : (T)st->beta;
-        const T qn = zz + dt * acc + (first ? (T)0 : beta * q[z]);
-        const T pn = zz + (first ? (T)0 : beta * p[z]);
+        const T dt = (T)st->dt, beta = (T)beta64;
+        const T qn = zz + dt * acc + (first ? (T)0 : beta * qo);
+        const T pn = zz + (first ? (T)0 : beta * po);
         q[z] = qn;
         p[z] = pn;
         pqz = (double)pn * (double)qn;
     }
-    __shared__ double red[kBS];
-    red[threadIdx.x] = pqz;
-    __syncthreads();
-    for (int s = kBS / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blk] = red[0];
-}
-
-// alpha = <z, r> / <p, q> from the partials (one block of kBS threads).
-__global__ __launch_bounds__(kBS) void k_cg_alpha(CgState *st, const double *partial, long long nb) {
-    const double pq = reduce_partials(partial, nb);
-    if (threadIdx.x != 0 || st->bad || st->done) return;
-    st->pq = pq;
-    if (!(pq > 0.0) || !isfinite(pq)) st->bad = 1;
-    st->alpha = st->bad ? 0.0 : st->rz / pq;
+    block_sum_to(pqz, partial + blk);
 }
 
 // |b - (x + dt A x)|^2 with FP64 arithmetic (weights promoted); block
@@ -2442,7 +2504,7 @@ __global__ __launch_bounds__(kBS) void k_residual(
     block_partial_sum(r2, partial);
 }
 
-__global__ __launch_bounds__(kBS) void k_sum_partials(const double *partial, long long nb,
+__global__ __launch_bounds__(kFinish) void k_sum_partials(const double *partial, long long nb,
                                                       double *out) {
     const double t = reduce_partials(partial, nb);
     if (threadIdx.x == 0) *out = t;
@@ -2473,7 +2535,7 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
         if (op->tiled) {
             hipLaunchKernelGGL((k_reach_wmax<DIM, WIDE, TS>), dim3(nb), dim3(256), 0, s, g,
                                (const store_t *)sb, (const TS *)w, op->rpart, op->part);
-            hipLaunchKernelGGL(k_tile_params, dim3(1), dim3(256), 0, s, (const double *)op->rpart,
+            hipLaunchKernelGGL(k_tile_params, dim3(1), dim3(kFinish), 0, s, (const double *)op->rpart,
                                (const double *)op->part, (long long)nb, Tile<DIM>::HMAX,
                                op->hnear, op->wmax);
         }
@@ -2560,7 +2622,7 @@ int build_impl(adlbr_operator *op, const int16_t *off, const void *win, int win_
             nparts = nt;
         }
     }
-    hipLaunchKernelGGL(k_cfl, dim3(1), dim3(256), 0, s, (const double *)op->part, nparts,
+    hipLaunchKernelGGL(k_cfl, dim3(1), dim3(kFinish), 0, s, (const double *)op->part, nparts,
                        op->maxdiag, op->dtcfl, status);
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
@@ -2715,7 +2777,7 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
 
 template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struct CgDirF {
     static int run(const adlbr_operator *op, const void *z, void *q, void *p, CgState *st,
-                   double *partial, int first, hipStream_t s) {
+                   double *partial, int first, const CgTail &tail, hipStream_t s) {
         typedef typename Slots<DIM, WIDE>::store_t store_t;
         const GridInfo g = op->gi;
         const unsigned nb = (unsigned)((g.N + kBS - 1) / kBS);
@@ -2723,22 +2785,19 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
         hipLaunchKernelGGL((k_cg_direction<DIM, WIDE, PER, MG, TS>), dim3(nb), dim3(kBS), 0, s, g,
                            (const TS *)z, (TS *)q, (TS *)p, (const store_t *)op->sb,
                            op->wp, op->pos, op->ent, (const EntRec<TS> *)op->went,
-                           (const CgState *)st,
-                           partial, first);
-        hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(kBS), 0, s, st, (const double *)partial,
-                           (long long)nb);
+                           st, partial, first, tail);
         return ADLBR_OK;
     }
 };
 template <int DIM, bool WIDE, bool PER, bool MG> struct CgDirF<DIM, WIDE, PER, MG, bf16, float> {
     static int run(const adlbr_operator *, const void *, void *, void *, CgState *, double *, int,
-                   hipStream_t) {
+                   const CgTail &, hipStream_t) {
         return ADLBR_E_UNSUPPORTED;
     }
 };
 template <int DIM, bool WIDE, bool PER, bool MG> struct CgDirF<DIM, WIDE, PER, MG, _Float16, float> {
     static int run(const adlbr_operator *, const void *, void *, void *, CgState *, double *, int,
-                   hipStream_t) {
+                   const CgTail &, hipStream_t) {
         return ADLBR_E_UNSUPPORTED;
     }
 };
@@ -2751,7 +2810,7 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
         const unsigned nb = (unsigned)((g.N + kBS - 1) / kBS);
         hipLaunchKernelGGL((k_residual<DIM, WIDE, PER, MG, TS>), dim3(nb), dim3(kBS), 0, s, g,
                            (const TS *)b, x, (const store_t *)op->sb, op->wp, op->pos, op->ent, (const EntRec<TS> *)op->went, dt, partial, (TS *)rout);
-        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBS), 0, s, (const double *)partial,
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kFinish), 0, s, (const double *)partial,
                            (long long)nb, out);
         return ADLBR_OK;
     }
@@ -2889,9 +2948,9 @@ int batch_launch(const adlbr_operator *rep, const BatchProb *probs, const BatchP
 }
 
 int cg_direction(const adlbr_operator *op, const void *z, void *q, void *p, CgState *st,
-                 double *partial, int first, hipStream_t s) {
+                 double *partial, int first, const CgTail &tail, hipStream_t s) {
     if (op->tiled) return ADLBR_E_UNSUPPORTED;  // the solvers gather over full lists
-    return dispatch<CgDirF>(op, z, q, p, st, partial, first, s);
+    return dispatch<CgDirF>(op, z, q, p, st, partial, first, tail, s);
 }
 
 // out = (I + dt A) u, written as one explicit step with step -dt.

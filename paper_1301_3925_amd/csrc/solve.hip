@@ -1,16 +1,16 @@
 // Implicit step K x = b, K = I + dt A, by preconditioned conjugate gradients.
 //
 // All scalars live on the device (CgState); every reduction is a per-block
-// FP64 partial sum finished by a one-block kernel in block order, so a solve
-// is deterministic and needs no host round trip per iteration.  The update
-// kernel's finisher raises `done` when the recurrence residual drops below
+// FP64 partial sum, finished in a fixed order by the next kernel (every block
+// of it for itself), so a solve is deterministic and needs no host round trip
+// per iteration.  `done` is raised when the recurrence residual drops below
 // tol |b|; later kernels of the same batch are then no-ops, so the iteration
 // count is exact although the host only looks every check_every
 // iterations.  The host confirms convergence with the true residual
 // |b - K x| in FP64.
 //
-// Jacobi-PCG per iteration: update (x, r, z = r / diag K, <r,z>, <r,r>,
-// beta) -> direction (q = K z + beta q, p = z + beta p, <p,q>, alpha).
+// Jacobi-PCG per iteration: update (alpha, x, r, z = r / diag K, <r,z>,
+// <r,r>) -> direction (beta, q = K z + beta q, p = z + beta p, <p,q>).
 // Flexible CG (Section 4 solves the restoration system by CG; the flexible
 // variant admits the learned preconditioner): update (x, r, <r,r>) ->
 // z = N(r) with the dots <z,r>, <z,r_prev> -> scalars (|r|^2 checks, beta)
@@ -25,15 +25,16 @@ namespace adlbr {
 namespace {
 
 constexpr int kBS = 256;
+// The vector update: blocks of kFinish threads, kUpd points a thread at a time.
+constexpr int kUpd = 4;
 
 struct SolveState {
     CgState cg;
-    double tol2bb;  // tol^2 |b|^2
     double rr_true;
 };
 
-template <typename TD> __device__ __forceinline__ double inv_kd(const TD *diag, long long z, double dt) {
-    return 1.0 / (1.0 + dt * (double)diag[z]);
+template <typename TD> __device__ __forceinline__ double inv_kd(TD diag, double dt) {
+    return 1.0 / (1.0 + dt * (double)diag);
 }
 
 // x0 = 0: x64 = 0, r = b; otherwise r = b - K x64 is already in r.
@@ -57,105 +58,137 @@ __global__ __launch_bounds__(kBS) void k_init(long long N, const T *__restrict__
             ri = r[i];
         }
         if (jacobi) {
-            const T zi = (T)((double)ri * inv_kd(diag, i, st->cg.dt));
+            const T zi = (T)((double)ri * inv_kd(diag[i], st->cg.dt));
             z[i] = zi;
             rz = (double)ri * (double)zi;
         }
         bb = (double)bi * (double)bi;
     }
-    block_partial_sum(rz, part);
-    block_partial_sum(bb, part + gridDim.x);
+    block_partial_sum2(rz, bb, part, part + gridDim.x);
 }
 
-__global__ __launch_bounds__(kBS) void k_init_fin(SolveState *st, const double *part, long long nb,
+__global__ __launch_bounds__(kFinish) void k_init_fin(SolveState *st, const double *part, long long nb,
                                                   double tol2) {
     const double rz = reduce_partials(part, nb);
     const double bb = reduce_partials(part + nb, nb);
     if (threadIdx.x != 0) return;
-    st->cg.rz = rz;
+    st->cg.rz[0] = st->cg.rz[1] = rz;
     st->cg.beta = 0.0;
     st->cg.iter = 0;
     st->cg.bad = 0;
     st->cg.done = 0;
     st->cg.bb = bb;
-    st->tol2bb = tol2 * bb;
+    st->cg.tol2bb = tol2 * bb;
     st->cg.rr = bb;
 }
 
-// Jacobi-PCG update: x += alpha p, r -= alpha q, z = r / diag K; partials
-// of <r, z> and <r, r>.
-template <typename T, typename TD>
-__global__ __launch_bounds__(kBS) void k_pcg_update(long long N, double *__restrict__ x,
-                                                    T *__restrict__ r, T *__restrict__ z,
+// CG update: alpha = <z, r> / <p, q> from the direction's nd partials, which
+// every block sums for itself in the same order (one of them writes it
+// down), then x += alpha p, rn = r - alpha q and the partials of |rn|^2; with
+// JAC (Jacobi-PCG, rn and r the same vector) also z = rn / diag K and the
+// partials of <rn, z>.  A block takes one contiguous
+// range; its first loads are in flight while the sum is taken.
+template <typename T, typename TD, bool JAC>
+__global__ __launch_bounds__(kFinish, 8) void k_update(long long N, double *__restrict__ x, const T *r,
+                                                    T *rn, T *__restrict__ z,
                                                     const T *__restrict__ p, const T *__restrict__ q,
-                                                    const TD *__restrict__ diag,
-                                                    const SolveState *st, double *part) {
-    const bool skip = st->cg.done || st->cg.bad;
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
+                                                    const TD *__restrict__ diag, CgState *st, int slot,
+                                                    const double *__restrict__ dpart, long long nd,
+                                                    double *__restrict__ prz, double *__restrict__ prr) {
+    constexpr int U = sizeof(T) == 8 ? kUpd / 2 : kUpd;  // 64 registers: two blocks a CU
+    if (st->done || st->bad) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->halt = 1;
+        return;
+    }
+    const long long per = (N + gridDim.x - 1) / gridDim.x;
+    const long long end = min(N, (blockIdx.x + 1) * per);
+    T ri[U], pi[U], qi[U];
+    TD di[U];
+    double xi[U];
+    auto load = [&](long long i0) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long i = i0 + k * kFinish < end ? i0 + k * kFinish : N - 1;
+            xi[k] = x[i];
+            pi[k] = p[i];
+            ri[k] = r[i];
+            qi[k] = q[i];
+            if (JAC) di[k] = diag[i];
+        }
+    };
+    long long i0 = blockIdx.x * per + threadIdx.x;
+    load(i0);
+    const double pq = reduce_partials(dpart, nd);
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->pq = pq;
+    if (cg_breakdown(pq)) return;
+    const double al = st->rz[slot] / pq, dt = st->dt;
+    const T a = (T)al;
     double rz = 0.0, rr = 0.0;
-    if (i < N && !skip) {
-        const T a = (T)st->cg.alpha;
-        x[i] += st->cg.alpha * (double)p[i];
-        const T ri = r[i] - a * q[i];
-        r[i] = ri;
-        const T zi = (T)((double)ri * inv_kd(diag, i, st->cg.dt));
-        z[i] = zi;
-        rz = (double)ri * (double)zi;
-        rr = (double)ri * (double)ri;
+    for (;;) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long i = i0 + k * kFinish;
+            if (i >= end) break;
+            x[i] = xi[k] + al * (double)pi[k];
+            const T rk = ri[k] - a * qi[k];
+            rn[i] = rk;
+            rr += (double)rk * (double)rk;
+            if (JAC) {
+                const T zi = (T)((double)rk * inv_kd(di[k], dt));
+                z[i] = zi;
+                rz += (double)rk * (double)zi;
+            }
+        }
+        i0 += U * kFinish;
+        if (i0 - threadIdx.x >= end) break;
+        load(i0);
     }
-    block_partial_sum(rz, part);
-    block_partial_sum(rr, part + gridDim.x);
+    __shared__ double red[2][kFinish / 64];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        rz += __shfl_xor(rz, d, 64);
+        rr += __shfl_xor(rr, d, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = rz;
+        red[1][threadIdx.x >> 6] = rr;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int j = 1; j < kFinish / 64; ++j) {
+        rz += red[0][j];
+        rr += red[1][j];
+    }
+    if (JAC) prz[blockIdx.x] = rz;
+    prr[blockIdx.x] = rr;
 }
 
-// Finish a PCG iteration: beta, history, convergence flag.
-__global__ __launch_bounds__(kBS) void k_pcg_scalars(SolveState *st, const double *part,
-                                                     long long nb, double *hist, int max_hist) {
-    const double rzn = reduce_partials(part, nb);
-    const double rr = reduce_partials(part + nb, nb);
-    if (threadIdx.x != 0 || st->cg.done || st->cg.bad) return;
-    if (!isfinite(rzn) || !isfinite(rr) || !(st->cg.rz > 0.0)) st->cg.bad = 1;
-    st->cg.beta = st->cg.bad ? 0.0 : rzn / st->cg.rz;
-    st->cg.rz_old = st->cg.rz;
-    st->cg.rz = rzn;
-    st->cg.rr = rr;
-    const int it = st->cg.iter + 1;
-    st->cg.iter = it;
-    if (it < max_hist) hist[it] = rr;
-    if (rr <= st->tol2bb) st->cg.done = 1;
-}
-
-// Flexible-CG update: x += alpha p, r_new = r - alpha q; partials of <r_new, r_new>.
-template <typename T>
-__global__ __launch_bounds__(kBS) void k_fcg_update(long long N, double *__restrict__ x,
-                                                    const T *__restrict__ r, T *__restrict__ rn,
-                                                    const T *__restrict__ p,
-                                                    const T *__restrict__ q, const SolveState *st,
-                                                    double *prr) {
-    const bool skip = st->cg.done || st->cg.bad;
-    const long long i = (long long)blockIdx.x * kBS + threadIdx.x;
-    double rr = 0.0;
-    if (i < N && !skip) {
-        const T a = (T)st->cg.alpha;
-        x[i] += st->cg.alpha * (double)p[i];
-        const T ri = r[i] - a * q[i];
-        rn[i] = ri;
-        rr = (double)ri * (double)ri;
-    }
-    block_partial_sum(rr, prr);
+// <p, q> of a batch's last direction, so that the host sees its breakdown.
+__global__ __launch_bounds__(kFinish) void k_breakdown(CgState *st, const double *dpart, long long nd) {
+    if (st->done || st->bad) return;
+    const double pq = reduce_partials(dpart, nd);
+    if (threadIdx.x != 0) return;
+    st->pq = pq;
+    if (cg_breakdown(pq)) st->bad = 1;
 }
 
 // Finish a flexible-CG iteration (one block): unless first, the update's
 // |r|^2 from its partials prr (iteration count, history, breakdown and
 // convergence flags); then, from the dot partials part (nparts each),
 // beta = (<z, r> - <z, r_prev>) / <z_prev, r_prev> (first: beta = 0).
-__global__ __launch_bounds__(kBS) void k_fcg_scalars(SolveState *st, const double *part,
+__global__ __launch_bounds__(kFinish) void k_fcg_scalars(SolveState *st, const double *part,
                                                      long long nparts, const double *prr,
                                                      long long nb, double *hist, int max_hist,
                                                      int first) {
+    if (cg_stopped(&st->cg)) {
+        if (threadIdx.x == 0 && !st->cg.done) st->cg.bad = 1;
+        return;
+    }
     const double rr = first ? 0.0 : reduce_partials(prr, nb);
     const double zr = reduce_partials(part, nparts);
     const double zrp = reduce_partials(part + nparts, nparts);
-    if (threadIdx.x != 0 || st->cg.done || st->cg.bad) return;
+    if (threadIdx.x != 0) return;
     if (!first) {
         st->cg.rr = rr;
         const int it = st->cg.iter + 1;
@@ -165,7 +198,7 @@ __global__ __launch_bounds__(kBS) void k_fcg_scalars(SolveState *st, const doubl
             st->cg.bad = 1;
             return;
         }
-        if (rr <= st->tol2bb) {
+        if (rr <= st->cg.tol2bb) {
             st->cg.done = 1;
             return;
         }
@@ -174,9 +207,8 @@ __global__ __launch_bounds__(kBS) void k_fcg_scalars(SolveState *st, const doubl
         st->cg.bad = 1;
         return;
     }
-    st->cg.beta = first ? 0.0 : (zr - zrp) / st->cg.rz;
-    st->cg.rz_old = st->cg.rz;
-    st->cg.rz = zr;
+    st->cg.beta = first ? 0.0 : (zr - zrp) / st->cg.rz[0];
+    st->cg.rz[0] = zr;
 }
 
 // Zero the whole state and set dt; a kernel rather than a host copy so no
@@ -186,7 +218,10 @@ __global__ void k_state_reset(SolveState *st, double dt) {
     constexpr int nw = (int)(sizeof(SolveState) / 4);
     for (int k = threadIdx.x; k < nw; k += blockDim.x) w[k] = 0u;
     __syncthreads();
-    if (threadIdx.x == 0) st->cg.dt = dt;
+    if (threadIdx.x == 0) {
+        st->cg.dt = dt;
+        st->cg.pq = 1.0;
+    }
 }
 
 // Residual replacement: r already holds b - K x (from the true residual);
@@ -200,21 +235,22 @@ __global__ __launch_bounds__(kBS) void k_restart(long long N, const T *__restric
     double rz = 0.0;
     if (i < N && jacobi) {
         const T ri = r[i];
-        const T zi = (T)((double)ri * inv_kd(diag, i, st->cg.dt));
+        const T zi = (T)((double)ri * inv_kd(diag[i], st->cg.dt));
         z[i] = zi;
         rz = (double)ri * (double)zi;
     }
     block_partial_sum(rz, part);
 }
 
-__global__ __launch_bounds__(kBS) void k_restart_fin(SolveState *st, const double *part,
+__global__ __launch_bounds__(kFinish) void k_restart_fin(SolveState *st, const double *part,
                                                      long long nb) {
     const double t = reduce_partials(part, nb);
     if (threadIdx.x != 0) return;
-    st->cg.rz = t;
+    st->cg.rz[0] = st->cg.rz[1] = t;
     st->cg.beta = 0.0;
     st->cg.rr = st->rr_true;
     st->cg.done = 0;
+    st->cg.halt = 0;
 }
 
 template <typename TA, typename TB> __global__ void k_convert(long long N, const TA *a, TB *b) {
@@ -233,6 +269,14 @@ size_t dot_parts(const GridInfo &g) {
     if (g.dim == 3)
         m = std::max(m, (size_t)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * ((g.nz + 3) / 4));
     return m;
+}
+
+// Blocks of the update: one per CU from 1024 points a block, then two once
+// each has a whole step of its threads (1024^2: 11.1 us with one per CU, 13.1
+// with two; 128^3: 17.1 and 15.9).
+unsigned update_blocks(long long N) {
+    const long long a = (N + kFinish - 1) / kFinish, b = (N + kUpd * kFinish - 1) / (kUpd * kFinish);
+    return (unsigned)std::max(std::min<long long>(a, kUpdBlocks / 2), std::min<long long>(b, kUpdBlocks));
 }
 
 struct SolveLayout {
@@ -265,12 +309,16 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
     const GridInfo &g = operator_grid(op);
     const long long N = g.N;
     const unsigned nb = (unsigned)((N + kBS - 1) / kBS);
+    const unsigned nbu = update_blocks(N);
     const SolveLayout L = solve_layout(g, sizeof(T), kMaxHist);
     SolveState *st = (SolveState *)(ws + L.st);
     double *hist = (double *)(ws + L.hist);
     double *part = (double *)(ws + L.part);
     // partials of |r|^2 of the flexible-CG update, after the dot partials
     double *prr = part + 2 * (long long)dot_parts(g);
+    // those of <z, r> of the Jacobi-PCG update, out of the direction's way
+    double *prz = part + (long long)dot_parts(g);
+    static_assert(kUpdBlocks <= kDotParts, "in the second region");
     T *r = (T *)(ws + L.vec[0]);
     T *r2 = (T *)(ws + L.vec[1]);
     T *z = (T *)(ws + L.vec[2]);
@@ -296,12 +344,12 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
     }
     hipLaunchKernelGGL((k_init<T, TD>), dim3(nb), dim3(kBS), 0, s, N, b, x64, r, z, diag,
                        p->x0_zero, (int)!net, (const SolveState *)st, part);
-    hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
+    hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(kFinish), 0, s, st, (const double *)part,
                        (long long)nb, p->tol * p->tol);
     int rc = ADLBR_OK;
     bool use_net = net;
     int fell_back = 0, net_iters = 0, restarts = 0, reason = 0;
-    int first = 1;
+    int first = 1, slot = 0;
     T *rc_ = r, *ro = r2;  // current and previous residual (flexible CG)
     auto start_iteration = [&]() -> int {
         if (use_net) {
@@ -311,10 +359,13 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
                                    first ? nullptr : (const float *)ro, (float *)z, part, &np, cg,
                                    s);
             if (e) return e;
-            hipLaunchKernelGGL(k_fcg_scalars, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
-                               np, (const double *)prr, (long long)nb, hist, kMaxHist, first);
+            hipLaunchKernelGGL(k_fcg_scalars, dim3(1), dim3(kFinish), 0, s, st, (const double *)part,
+                               np, (const double *)prr, (long long)nbu, hist, kMaxHist, first);
         }
-        int e = cg_direction(op, z, q, pv, cg, part, first, s);
+        const CgTail tail = {use_net || first ? nullptr : prz, prr, (int)nbu, slot, hist,
+                             kMaxHist};
+        int e = cg_direction(op, z, q, pv, cg, part, first, tail, s);
+        if (tail.prz) slot ^= 1;  // where the direction has left <z, r>
         first = 0;
         return e;
     };
@@ -331,20 +382,22 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
         const int batch = std::min(check, p->max_iter - issued);
         for (int k = 0; k < batch; ++k) {
             if (use_net) {
-                hipLaunchKernelGGL((k_fcg_update<T>), dim3(nb), dim3(kBS), 0, s, N, x64,
-                                   (const T *)rc_, ro, (const T *)pv, (const T *)q,
-                                   (const SolveState *)st, prr);
+                hipLaunchKernelGGL((k_update<T, TD, false>), dim3(nbu), dim3(kFinish), 0, s, N, x64,
+                                   (const T *)rc_, ro, (T *)nullptr, (const T *)pv, (const T *)q,
+                                   (const TD *)nullptr, cg, slot, (const double *)part,
+                                   (long long)nb, (double *)nullptr, prr);
                 std::swap(rc_, ro);  // ro now holds r_k (previous), rc_ r_{k+1}
             } else {
-                hipLaunchKernelGGL((k_pcg_update<T, TD>), dim3(nb), dim3(kBS), 0, s, N, x64, rc_, z,
-                                   (const T *)pv, (const T *)q, diag, (const SolveState *)st, part);
-                hipLaunchKernelGGL(k_pcg_scalars, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
-                                   (long long)nb, hist, kMaxHist);
+                hipLaunchKernelGGL((k_update<T, TD, true>), dim3(nbu), dim3(kFinish), 0, s, N, x64,
+                                   (const T *)rc_, rc_, z, (const T *)pv, (const T *)q, diag, cg,
+                                   slot, (const double *)part, (long long)nb, prz, prr);
             }
             rc = start_iteration();
             if (rc) return rc;
         }
         issued += batch;
+        hipLaunchKernelGGL(k_breakdown, dim3(1), dim3(kFinish), 0, s, cg, (const double *)part,
+                           (long long)nb);
         ADLBR_CHECK_HIP(hipMemcpyAsync(&h, cg, sizeof h, hipMemcpyDeviceToHost, s));
         ADLBR_CHECK_HIP(hipStreamSynchronize(s));
         if (use_net) {
@@ -369,6 +422,7 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
             if (!use_net) break;  // Jacobi-PCG broke down: report as not converged
             // learned preconditioner failed: restart from x with Jacobi-PCG
             use_net = false;
+            slot = 0;
             fell_back = 1;
             if (!reason) reason = 1;
             first = 1;
@@ -378,7 +432,7 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
             if (rc) return rc;
             hipLaunchKernelGGL((k_init<T, TD>), dim3(nb), dim3(kBS), 0, s, N, b, x64, r, z, diag,
                                0, 1, (const SolveState *)st, part);
-            hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
+            hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(kFinish), 0, s, st, (const double *)part,
                                (long long)nb, p->tol * p->tol);
             rc_ = r;
             ro = r2;
@@ -393,7 +447,7 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
             if (rc) return rc;
             double rt = 0.0, t2 = 0.0;
             ADLBR_CHECK_HIP(hipMemcpyAsync(&rt, &st->rr_true, 8, hipMemcpyDeviceToHost, s));
-            ADLBR_CHECK_HIP(hipMemcpyAsync(&t2, &st->tol2bb, 8, hipMemcpyDeviceToHost, s));
+            ADLBR_CHECK_HIP(hipMemcpyAsync(&t2, &st->cg.tol2bb, 8, hipMemcpyDeviceToHost, s));
             ADLBR_CHECK_HIP(hipStreamSynchronize(s));
             if (rt <= t2) {
                 converged = true;
@@ -405,7 +459,7 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
             if (rc) return rc;
             hipLaunchKernelGGL((k_restart<T, TD>), dim3(nb), dim3(kBS), 0, s, N, (const T *)rc_, z,
                                diag, (int)!use_net, (const SolveState *)st, part);
-            hipLaunchKernelGGL(k_restart_fin, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
+            hipLaunchKernelGGL(k_restart_fin, dim3(1), dim3(kFinish), 0, s, st, (const double *)part,
                                (long long)nb);
             first = 1;
             rc = start_iteration();
