@@ -18,6 +18,8 @@
 // A-operand reads of 16 consecutive pixels bank-conflict free; layer 3
 // writes over layer 1's buffer.  Zero padding: every layer's input is 0
 // outside the grid.
+#include <algorithm>
+
 #include "common.h"
 
 namespace adlbr {
@@ -344,194 +346,314 @@ __global__ void k_pack_mfma(const float *__restrict__ L1, const float *__restric
 
 
 // ------------------------------------------------------------------ 3D --
-// The 3D inference runs layer by layer: the thin layers (1 -> 16, 16 -> 1)
-// on the vector units, k3PPT points per thread; the two 16 -> 16 layers on the
-// matrix cores as implicit GEMMs over 8 x 8 x 8 tiles (27 taps x one
-// v_mfma_f32_16x16x16_bf16 per 16-pixel group, the tile plus a one-point
-// halo staged in LDS).  Activations cross HBM between layers as BF16
-// [N][16] (32 bytes a point), gates as the 8-bit g1, g2 of every point.
-constexpr int k3X = 8, k3Y = 8, k3Z = 8;                 // output tile
-constexpr int k3HX = k3X + 2, k3HY = k3Y + 2, k3HZ = k3Z + 2;
-constexpr int k3Halo = k3HX * k3HY * k3HZ;               // 1000 staged points
-constexpr int k3Pts = k3X * k3Y * k3Z;                   // 512 outputs per block
-constexpr int k3PPT = k3Pts / 256;                       // points per thread (layers 1, 4)
-constexpr int k3GPW = k3Pts / 64;                        // 16-point groups per wave (MFMA)
-static_assert(k3Pts % 256 == 0, "whole points per thread");
+// The 3D inference runs in three kernels: layers 1 and 2 together, layer 3,
+// layer 4.  Activations cross HBM between them as BF16 [N][16] (32 bytes a
+// point), gates as the 8-bit g1, g2 of every point.
+//
+// The 16 -> 16 layers walk the planes of a 16 x 8 column, a wave a row of 16
+// points: an input plane and its halo, double buffered in LDS as 32 bytes a
+// point (16 points of a row are 512 contiguous bytes, read without bank
+// conflicts), feeds the three output planes that it neighbours, whose sums
+// a wave holds, so that five LDS reads serve 15 matrix instructions, the 27
+// taps of a row.  The next plane is on its way meanwhile, the
+// weights stay in registers for the whole column, and only the column's own
+// halo (180 points for 128) is read twice.
+constexpr int k3X = 16, k3Y = 8;                         // output column
+constexpr int k3HX = k3X + 2, k3HY = k3Y + 2, k3Plane = k3HX * k3HY;  // 180 staged points
 constexpr int k3T = 27;
+constexpr int k3BS = 64 * k3Y;                           // a wave per row
 
-__device__ __forceinline__ bool in_grid3(int x, int y, int z, int nx, int ny, int nz) {
-    return x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz;
-}
-
-// The tile of block b (8 x 8 x 8 points) and the origin of its halo.
-struct Tile3 {
-    int x0, y0, z0;  // halo origin = tile origin - 1
+// Column c of the grid: its halo's origin and its planes [z0, z1).
+struct Column {
+    int x0, y0, z0, z1;
+    __device__ __forceinline__ Column(const GridInfo &g, long long b, int chunk) {
+        const int ntx = (g.nx + k3X - 1) / k3X, nty = (g.ny + k3Y - 1) / k3Y;
+        x0 = (int)(b % ntx) * k3X - 1;
+        y0 = (int)((b / ntx) % nty) * k3Y - 1;
+        z0 = (int)(b / ((long long)ntx * nty)) * chunk;
+        z1 = min(z0 + chunk, g.nz);
+    }
+    // in-plane index of a point of the halo grown by R, -1 outside the grid
+    template <int R> __device__ __forceinline__ int at(const GridInfo &g, int h) const {
+        const int x = x0 - R + h % (k3HX + 2 * R), y = y0 - R + h / (k3HX + 2 * R);
+        return x >= 0 && x < g.nx && y >= 0 && y < g.ny ? x + g.nx * y : -1;
+    }
 };
-__device__ __forceinline__ Tile3 tile3(const GridInfo &g, long long b) {
-    const int ntx = (g.nx + k3X - 1) / k3X, nty = (g.ny + k3Y - 1) / k3Y;
-    Tile3 t;
-    t.x0 = (int)(b % ntx) * k3X - 1;
-    t.y0 = (int)((b / ntx) % nty) * k3Y - 1;
-    t.z0 = (int)(b / ((long long)ntx * nty)) * k3Z - 1;
-    return t;
-}
-// LDS index of tile point p's neighbour at tap t in the halo region.
-__device__ __forceinline__ int halo_idx(int p, int t) {
-    const int px = p % k3X, py = (p / k3X) % k3Y, pz = p / (k3X * k3Y);
-    const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-    return (pz + 1 + dz) * (k3HX * k3HY) + (py + 1 + dy) * k3HX + (px + 1 + dx);
+
+// The A operands of a layer, per lane (row co = lane & 15): of each dz, four
+// pairs of (dy, dx) taps (2 q, 2 q + 1) for v_mfma_f32_16x16x32_bf16, whose
+// first 16 k are the first tap's channels, and the ninth tap's for
+// v_mfma_f32_16x16x16_bf16.  A pair gives the bits that its two taps one
+// after the other give, in the time of one.
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+constexpr int k3PackLayer = k3T * 64, k3PackPairs = 3 * 4 * 64 * 2;  // in bf16x4
+struct Weights16 {
+    bf16x8v w2[3][4];
+    const bf16x4 *w1;  // the ninth taps' in LDS, [dz][lane]: layer 1 needs the registers
+    __device__ __forceinline__ void load(const bf16x4 *__restrict__ pk, bf16x4 *lds) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                w2[dz][q] = __builtin_bit_cast(bf16x8v, ((const bf16x8 *)pk)[(4 * dz + q) * 64 + lane]);
+        }
+        if (threadIdx.x < 3 * 64) lds[threadIdx.x] = pk[k3PackPairs + threadIdx.x];
+        w1 = lds + lane;
+    }
+};
+
+// Four gated channels as BF16.
+__device__ __forceinline__ uint2 gated4(f32x4 d, uint32_t g4) {
+    float v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = d[c] * q8((g4 >> (8 * c)) & 0xffu);
+    return make_uint2((uint16_t)bfbits(v[0]) | ((uint32_t)(uint16_t)bfbits(v[1]) << 16),
+                      (uint16_t)bfbits(v[2]) | ((uint32_t)(uint16_t)bfbits(v[3]) << 16));
 }
 
-// Stage a BF16 [N][16] field over the tile's halo into LDS (STRIDE shorts
-// per point, 0 outside the grid), 8 bytes per item: a thread issues kB loads
-// before their LDS stores, so the block waits for one round trip to memory
-// per kB items instead of one per item (all of them at once by default; a
-// kernel short of registers takes fewer).  Needs blockDim.x == 256.
-constexpr int k3StageItems = k3Halo * 4, k3StageIters = (k3StageItems + 255) / 256;
-template <int STRIDE = kStride, int kB = k3StageIters>
-__device__ __forceinline__ void stage3d(const GridInfo &g, const Tile3 &T, const uint2 *__restrict__ in,
-                                        short *sx) {
+// One wave's row of a 16 -> 16 layer along its column.  A lane holds four
+// channels (4 (lane >> 4) + c) of point lane & 15.
+struct Row16 {
+    Weights16 W;
+    f32x4 d0, d1, d2;  // output planes z - 1, z, z + 1 of input plane z
+    int i;           // in-plane index of the lane's point, -1 outside
+    uint32_t gate;   // its gates in plane z - 1
+    __device__ __forceinline__ void init(const GridInfo &g, const Column &C, const bf16x4 *__restrict__ pk,
+                                         bf16x4 *lds) {
+        W.load(pk, lds);
+        d0 = d1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+        gate = 0u;
+        i = C.at<0>(g, (1 + (int)(threadIdx.x >> 6)) * k3HX + 1 + (int)(threadIdx.x & 15));
+    }
+    // requests the gates of plane z, for the next plane's end
+    __device__ __forceinline__ void gates(const GridInfo &g, int z, const uint8_t *__restrict__ G8, int goff) {
+        const long long nxy = (long long)g.nx * g.ny;
+        gate = *(const uint32_t *)(G8 + 32 * (nxy * min(max(z, 0), g.nz - 1) + max(i, 0)) + goff +
+                                   4 * ((threadIdx.x & 63) >> 4));
+    }
+    // input plane z (in sx; skipped outside the grid), its LDS reads all
+    // requested before the first is waited for
+    __device__ __forceinline__ void plane(const GridInfo &g, int z, const short *sx) {
+        const int lane = threadIdx.x & 63, kg = lane >> 4;
+        d2 = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (z >= 0 && z < g.nz) {
+            // a lane's tap of a pair: one point on, or from the end of a
+            // halo row to the start of the next
+            const short *row = sx + ((int)(threadIdx.x >> 6) * k3HX + (lane & 15)) * 16;
+            const short *src = row + 8 * (kg & 1) + (kg & 2 ? 16 : 0);
+            const short *wrap = row + 8 * (kg & 1) + (kg & 2 ? 16 * (k3HX - 2) : 0);
+            bf16x8v x[4];
 #pragma unroll
-    for (int i0 = 0; i0 < k3StageIters; i0 += kB) {
-        uint2 v[kB];
+            for (int q = 0; q < 4; ++q) {
+                const int t = 2 * q, o = (t / 3 * k3HX + t % 3) * 16;
+                x[q] = __builtin_bit_cast(bf16x8v, *(const bf16x8 *)((t % 3 == 2 ? wrap : src) + o));
+            }
+            const bf16x4 x8 = *(const bf16x4 *)(row + 4 * kg + (2 * k3HX + 2) * 16);
+            __builtin_amdgcn_sched_barrier(0);
+            // every sum takes its taps in the order dz, dy, dx
 #pragma unroll
-        for (int j = 0; j < kB; ++j) {
-            const int k = (int)threadIdx.x + 256 * (i0 + j);
-            const int h = k >> 2, q = k & 3;
-            const int x = T.x0 + h % k3HX, y = T.y0 + (h / k3HX) % k3HY, z = T.z0 + h / (k3HX * k3HY);
-            v[j] = make_uint2(0u, 0u);
-            if (i0 + j < k3StageIters && k < k3StageItems && in_grid3(x, y, z, g.nx, g.ny, g.nz))
-                v[j] = in[4 * (x + (long long)g.nx * (y + (long long)g.ny * z)) + q];
-        }
-#pragma unroll
-        for (int j = 0; j < kB; ++j) {
-            const int k = (int)threadIdx.x + 256 * (i0 + j);
-            if (i0 + j < k3StageIters && k < k3StageItems) *(uint2 *)(sx + (k >> 2) * STRIDE + 4 * (k & 3)) = v[j];
+            for (int q = 0; q < 4; ++q) {
+                d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w2[2][q], x[q], d0, 0, 0, 0);
+                d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w2[1][q], x[q], d1, 0, 0, 0);
+                d2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w2[0][q], x[q], d2, 0, 0, 0);
+            }
+            d0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(W.w1[64 * 2], x8, d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(W.w1[64 * 1], x8, d1, 0, 0, 0);
+            d2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(W.w1[64 * 0], x8, d2, 0, 0, 0);
         }
     }
-}
+    // output plane z - 1, complete with input plane z
+    __device__ __forceinline__ void output(const GridInfo &g, const Column &C, int z, uint2 *__restrict__ out) {
+        const long long nxy = (long long)g.nx * g.ny;
+        if (z - 1 >= C.z0 && i >= 0)
+            out[4 * (nxy * (z - 1) + i) + ((threadIdx.x & 63) >> 4)] = gated4(d0, gate);
+        d0 = d1;
+        d1 = d2;
+    }
+};
 
-// Layer 1: a1[p][co] = g1[p][co] sum_t W1[co][t] r(p + off_t), r = 0 outside
-// the grid (tap t = (dz + 1) 9 + (dy + 1) 3 + (dx + 1)); k3PPT points per
-// thread of an 8 x 8 x 8 tile, r of the tile and its halo staged in LDS.
-__global__ __launch_bounds__(256) void k_net3d_l1(GridInfo g, const float *__restrict__ r,
-                                                  const float *__restrict__ W1,
-                                                  const uint8_t *__restrict__ G8,
-                                                  uint4 *__restrict__ a1,
-                                                  const CgState *__restrict__ st) {
+// Layers 1 and 2.  Layer 1 (1 -> 16, a1[p][co] = g1[p][co] sum_t W1[co][t]
+// r(p + off_t), r = 0 outside the grid, tap t = (dz + 1) 9 + (dy + 1) 3 +
+// (dx + 1)) runs in FP32 on v_mfma_f32_16x16x4_f32, seven for the 27 taps of
+// 16 points, a plane ahead of layer 2 and straight into the LDS that layer 2
+// reads: a1 does not cross HBM, at the price of taking 180 points for 128.
+// r passes through a ring of four planes.
+// 128^3: 45 + 77 us as two kernels in 8^3 tiles, 83 in columns.
+constexpr int k3RX = k3HX + 2, k3RPlane = k3RX * (k3HY + 2);  // 240 points
+__global__ __launch_bounds__(k3BS, 4) void k_net3d_l12(GridInfo g, int chunk,
+                                                       const float *__restrict__ r,
+                                                       const float *__restrict__ W1,
+                                                       const bf16x4 *__restrict__ pk,
+                                                       const uint8_t *__restrict__ G8,
+                                                       uint2 *__restrict__ out,
+                                                       const CgState *__restrict__ st) {
     if (st && (st->done || st->bad)) return;
-    __shared__ float sr[k3Halo];
-    const Tile3 T = tile3(g, blockIdx.x);
+    __shared__ float sr[4 * k3RPlane];
+    __shared__ __attribute__((aligned(16))) short sx[2][k3Plane * 16];
+    const Column C(g, xcd_block(blockIdx.x, gridDim.x), chunk);
+    const long long nxy = (long long)g.nx * g.ny;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, kg = lane >> 4;
+    __shared__ bf16x4 s1[3 * 64];
+    Row16 R;
+    R.init(g, C, pk, s1);
+    // r: one point of a plane per thread
+    const bool rt = threadIdx.x < k3RPlane;
+    const int ri = rt ? C.at<1>(g, threadIdx.x) : -1;
+    auto inr = [&](int z) { return ri >= 0 && z >= 0 && z < g.nz; };
+    auto loadr = [&](int z) { return r[inr(z) ? nxy * z + ri : 0]; };  // dropped by inr where it is stored
+    // layer 1: taps t = 4 j + kg of this lane, its weights in LDS (the
+    // registers are layer 2's); twelve groups of 16 points, two to waves
+    // 0 .. 3, so that each SIMD has three
+    constexpr int kJ = (k3T + 3) / 4;
+    __shared__ float sw[kJ * 64];
+    for (int k = threadIdx.x; k < kJ * 64; k += k3BS) {
+        const int t = 4 * (k / 64) + (k % 64 >> 4);
+        const float v = W1[(k & 15) * k3T + min(t, k3T - 1)];
+        sw[k] = t < k3T ? v : 0.f;
+    }
+    int off[kJ];
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) {
+        const int u = min(4 * j + kg, k3T - 1);
+        off[j] = (u / 3 % 3) * k3RX + u % 3;
+    }
+    int hi[2], hs[2];  // in-plane index, point in sr
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int h = 16 * (wave + 8 * q) + n;
+        hi[q] = h < k3Plane ? C.at<0>(g, h) : -1;
+        hs[q] = h < k3Plane ? h / k3HX * k3RX + h % k3HX : 0;
+    }
+    auto loadg = [&](int z, int q) {
+        return *(const uint32_t *)(G8 + 32 * (nxy * min(max(z, 0), g.nz - 1) + max(hi[q], 0)) + 4 * kg);
+    };
+    uint32_t g0 = loadg(C.z0 - 1, 0), g1 = loadg(C.z0 - 1, 1);
+    auto layer1 = [&](int z) {  // plane z into sx[z & 1]
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (q == 1 && wave >= 4) break;
+            // not the same value to the compiler, which would keep the sum
+            // with every tap's offset in a register of its own
+            asm volatile("" : "+v"(hs[q]));
+            float x[kJ], w[kJ];
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) {
+                const int t = 4 * j + kg;
+                x[j] = sr[((z - 1 + min(t, k3T - 1) / 9) & 3) * k3RPlane + hs[q] + off[j]];
+                if (4 * j + 3 >= k3T) x[j] = t < k3T ? x[j] : 0.f;  // no tap: 0, whatever r holds
+                w[j] = sw[64 * j + lane];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) d = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], x[j], d, 0, 0, 0);
+            uint2 v = gated4(d, q ? g1 : g0);
+            if (hi[q] < 0) v = make_uint2(0u, 0u);  // layer 2's zero padding
+            const int h = 16 * (wave + 8 * q) + n;
+            if (h < k3Plane) *(uint2 *)(&sx[z & 1][h * 16 + 4 * kg]) = v;
+        }
+    };
     {
-        constexpr int kIters = (k3Halo + 255) / 256;
-        float v[kIters];  // all loads first, then the LDS stores
-#pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int h = (int)threadIdx.x + 256 * it;
-            const int x = T.x0 + h % k3HX, y = T.y0 + (h / k3HX) % k3HY, z = T.z0 + h / (k3HX * k3HY);
-            const bool ok = h < k3Halo && in_grid3(x, y, z, g.nx, g.ny, g.nz);
-            const float rv = r[ok ? x + (long long)g.nx * (y + (long long)g.ny * z) : 0];
-            v[it] = ok ? rv : 0.f;  // a load from point 0 and a select: no branch per item
-        }
-#pragma unroll
-        for (int it = 0; it < kIters; ++it)
-            if ((int)threadIdx.x + 256 * it < k3Halo) sr[threadIdx.x + 256 * it] = v[it];
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int k = 0; k < k3PPT; ++k) {
-    const int p = (int)threadIdx.x + 256 * k;
-    const int x = T.x0 + 1 + p % k3X, y = T.y0 + 1 + (p / k3X) % k3Y, z = T.z0 + 1 + p / (k3X * k3Y);
-    if (!in_grid3(x, y, z, g.nx, g.ny, g.nz)) continue;
-    const long long i = x + (long long)g.nx * (y + (long long)g.ny * z);
-    float rv[k3T];
-#pragma unroll
-    for (int t = 0; t < k3T; ++t) rv[t] = sr[halo_idx(p, t)];
-    const uint4 gq = ((const uint4 *)G8)[2 * i];  // g1: bytes 0 .. 15
-    const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w};
-    uint32_t outw[8];
-#pragma unroll
-    for (int co = 0; co < 16; co += 2) {
-        float a0 = 0.f, b0 = 0.f;
-#pragma unroll
-        for (int t = 0; t < k3T; ++t) {  // uniform weights: scalar loads, SGPR operands
-            a0 += W1[co * k3T + t] * rv[t];
-            b0 += W1[(co + 1) * k3T + t] * rv[t];
-        }
-        a0 *= q8((gw[co >> 2] >> (8 * (co & 3))) & 0xffu);
-        b0 *= q8((gw[(co + 1) >> 2] >> (8 * ((co + 1) & 3))) & 0xffu);
-        outw[co >> 1] = (uint32_t)(uint16_t)bfbits(a0) | ((uint32_t)(uint16_t)bfbits(b0) << 16);
-    }
-    a1[2 * i] = make_uint4(outw[0], outw[1], outw[2], outw[3]);
-    a1[2 * i + 1] = make_uint4(outw[4], outw[5], outw[6], outw[7]);
-    }
-}
-
-// Layers 2 and 3 (16 -> 16): out[p][co] = g[p][co] sum_t sum_ci W_t[co][ci]
-// in(p + off_t)[ci], as D = W_t X_t on the matrix cores.  wpack: the layer's
-// 27 A operands, per lane (row co = lane & 15, ci = 4 (lane >> 4) + c);
-// goff: byte offset of the gate in each point's 32 gate bytes (0: g1,
-// 16: g2).
-__global__ __launch_bounds__(256) void k_net3d_mfma(GridInfo g, const uint2 *__restrict__ in,
-                                                    const bf16x4 *__restrict__ wpack,
-                                                    const uint8_t *__restrict__ G8, int goff,
-                                                    uint2 *__restrict__ out,
-                                                    const CgState *__restrict__ st) {
-    if (st && (st->done || st->bad)) return;
-    __shared__ __attribute__((aligned(16))) short sx[k3Halo * kStride];
-    const Tile3 T = tile3(g, blockIdx.x);
-    const int x0 = T.x0, y0 = T.y0, z0 = T.z0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    bf16x4 wb[k3T];
-#pragma unroll
-    for (int t = 0; t < k3T; ++t) wb[t] = wpack[t * 64 + lane];
-    const int n = lane & 15, kq = (lane >> 4) * 4;
-    uint32_t gv[k3GPW];  // the gates of this lane's output points, requested before the matrix work
-#pragma unroll
-    for (int j = 0; j < k3GPW; ++j) {
-        const int p = (wave * k3GPW + j) * 16 + n;
-        const int x = x0 + 1 + p % k3X, y = y0 + 1 + (p / k3X) % k3Y, z = z0 + 1 + p / (k3X * k3Y);
-        const long long i = in_grid3(x, y, z, g.nx, g.ny, g.nz) ? x + (long long)g.nx * (y + (long long)g.ny * z) : 0;
-        gv[j] = *(const uint32_t *)(G8 + 32 * i + goff + kq);
-    }
-    stage3d<kStride, 8>(g, T, in, sx);  // 8 loads in flight: the weights stay in registers
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < k3GPW; ++j) {
-        const int p = (wave * k3GPW + j) * 16 + n;  // this lane's output point in the tile
-        const int px = p % k3X, py = (p / k3X) % k3Y, pz = p / (k3X * k3Y);
-        const short *base = sx + ((pz + 1) * (k3HX * k3HY) + (py + 1) * k3HX + (px + 1)) * kStride + kq;
-        f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < k3T; ++t) {
-            const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-            const bf16x4 b = *(const bf16x4 *)(base + (dz * (k3HX * k3HY) + dy * k3HX + dx) * kStride);
-            d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb[t], b, d, 0, 0, 0);
-        }
-        const int x = x0 + 1 + px, y = y0 + 1 + py, z = z0 + 1 + pz;
-        if (!in_grid3(x, y, z, g.nx, g.ny, g.nz)) continue;
-        const long long i = x + (long long)g.nx * (y + (long long)g.ny * z);
-        const uint32_t g4 = gv[j];
         float v[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = d[c] * q8((g4 >> (8 * c)) & 0xffu);
-        out[4 * i + (kq >> 2)] =
-            make_uint2((uint16_t)bfbits(v[0]) | ((uint32_t)(uint16_t)bfbits(v[1]) << 16),
-                       (uint16_t)bfbits(v[2]) | ((uint32_t)(uint16_t)bfbits(v[3]) << 16));
+        for (int k = 0; k < 4; ++k) v[k] = loadr(C.z0 - 2 + k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (rt) sr[((C.z0 - 2 + k) & 3) * k3RPlane + threadIdx.x] = inr(C.z0 - 2 + k) ? v[k] : 0.f;
+    }
+    float rv = loadr(C.z0 + 2);
+    __syncthreads();
+    if (C.z0 > 0) layer1(C.z0 - 1);
+    g0 = loadg(C.z0, 0);
+    g1 = loadg(C.z0, 1);
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the weights, once
+#pragma unroll 1
+    for (int z = C.z0 - 1; z <= C.z1; ++z) {
+        R.plane(g, z, sx[z & 1]);
+        // what the last step has requested, then the next requests: nothing
+        // waits for a load of its own step
+        if (z + 1 <= C.z1 && z + 1 < g.nz) layer1(z + 1);
+        if (rt) sr[((z + 3) & 3) * k3RPlane + threadIdx.x] = inr(z + 3) ? rv : 0.f;
+        R.output(g, C, z, out);
+        rv = loadr(z + 4);
+        g0 = loadg(z + 2, 0);
+        g1 = loadg(z + 2, 1);
+        R.gates(g, z, G8, 16);
+        __syncthreads();
+    }
+}
+
+// Layer 3: out[p][co] = g1[p][co] sum_t sum_ci W_t[co][ci] in(p + off_t)[ci].
+// 128^3: 77 us in 8^3 tiles, 46 in columns (5.0 TB/s of what it has to move).
+__global__ __launch_bounds__(k3BS, 4) void k_net3d_l3(GridInfo g, int chunk, const uint4 *__restrict__ in,
+                                                      const bf16x4 *__restrict__ pk,
+                                                      const uint8_t *__restrict__ G8,
+                                                      uint2 *__restrict__ out,
+                                                      const CgState *__restrict__ st) {
+    if (st && (st->done || st->bad)) return;
+    __shared__ __attribute__((aligned(16))) short sx[2][k3Plane * 16];
+    const Column C(g, xcd_block(blockIdx.x, gridDim.x), chunk);
+    const long long nxy = (long long)g.nx * g.ny;
+    __shared__ bf16x4 s1[3 * 64];
+    Row16 R;
+    R.init(g, C, pk, s1);
+    // one 16-byte item of a plane per thread, two a point, 0 outside the grid
+    static_assert(2 * k3Plane <= k3BS, "a plane in one item per thread");
+    const bool it = threadIdx.x < 2 * k3Plane;
+    const int hi = it ? C.at<0>(g, threadIdx.x >> 1) : -1;
+    auto load = [&](int z) {
+        return in[hi >= 0 && z >= 0 && z < g.nz ? 2 * (nxy * z + hi) + (threadIdx.x & 1) : 0];
+    };
+    auto store = [&](int z, uint4 q) {  // planes outside the grid are not read
+        const bool ok = hi >= 0;
+        if (it)
+            *(uint4 *)(&sx[z & 1][8 * threadIdx.x]) =
+                make_uint4(ok ? q.x : 0u, ok ? q.y : 0u, ok ? q.z : 0u, ok ? q.w : 0u);
+    };
+    store(C.z0 - 1, load(C.z0 - 1));
+    uint4 v = load(C.z0);
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the weights, once
+#pragma unroll 1
+    for (int z = C.z0 - 1; z <= C.z1; ++z) {
+        R.plane(g, z, sx[z & 1]);
+        store(z + 1, v);
+        R.output(g, C, z, out);
+        v = load(z + 2);
+        R.gates(g, z, G8, 0);
+        __syncthreads();
     }
 }
 
 // Layer 4 (16 -> 1) and the output: z = F0 r + sum_t sum_ci W4[ci][t]
-// a3(p + off_t)[ci], k3PPT points per thread of an 8 x 8 x 8 tile: a3 of the
-// tile and its halo staged in LDS (16 channels, 32 bytes a point), the 16
-// channels of every tap taken as 8 BF16 pairs by v_dot2c_f32_bf16 (FP32
-// accumulation) against the tap's weight pairs, which are uniform (scalar
-// loads).  On the matrix cores this layer would use one row of 16.  With
-// part, the block's FP64 partials of <z, r> in part[blockIdx] and of
-// <z, rp> in part[gridDim + blockIdx].
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+// a3(p + off_t)[ci].  As an implicit GEMM it would use one row in 16 of the
+// matrix instruction; taken the other way round it fills them: the 27 taps
+// are the rows, P[t][p] = sum_ci W4[ci][t] a3(p)[ci] is two instructions for
+// 16 points, and z sums P[t](p + off_t).  A block walks the planes of a
+// 16 x 16 column of k4Z points, P of one plane and its halo in LDS (FP32),
+// each thread one point of the plane with the sums of the three output
+// planes that the input plane reaches; the next plane's a3 is in flight
+// meanwhile.  With part, the block's FP64 partials of <z, r> in
+// part[blockIdx] and of <z, rp> in part[gridDim + blockIdx].
+// 128^3: 66 us as dot products over taps per point, 32 this way.
+constexpr int k4X = 16, k4Y = 16, k4Z = 8, k4HX = k4X + 2, k4Halo = k4HX * (k4Y + 2);
+constexpr int k4Groups = (k4Halo + 15) / 16, k4Per = (k4Groups + 3) / 4;
+constexpr int k4P = 16 * k4Groups;  // 336 = 5 * 64 + 16: taps four apart in different banks
+static_assert(k4P % 64 == 16, "tap planes staggered over the banks");
+struct OutTile {
+    int x0, y0, z0;  // halo origin = tile origin - 1
+    __device__ __forceinline__ OutTile(const GridInfo &g, long long b) {
+        const int ntx = (g.nx + k4X - 1) / k4X, nty = (g.ny + k4Y - 1) / k4Y;
+        x0 = (int)(b % ntx) * k4X - 1;
+        y0 = (int)((b / ntx) % nty) * k4Y - 1;
+        z0 = (int)(b / ((long long)ntx * nty)) * k4Z - 1;
+    }
+};
 __global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, const uint2 *__restrict__ a3,
-                                                  const uint32_t *__restrict__ w4,
+                                                  const bf16x4 *__restrict__ pk4,
                                                   const float *__restrict__ r,
                                                   const float *__restrict__ F0,
                                                   float *__restrict__ zout,
@@ -539,72 +661,110 @@ __global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, const uint2 *__res
                                                   double *__restrict__ part,
                                                   const CgState *__restrict__ st) {
     if (st && (st->done || st->bad)) return;
-    __shared__ __attribute__((aligned(16))) short sx[k3Halo * 16];
-    const Tile3 T = tile3(g, blockIdx.x);
-    // the outputs' inputs, requested before the staging: loads from point 0
-    // for a point outside the grid, dropped below
-    int ip[k3PPT];
-    bool live[k3PPT];
-    float r0[k3PPT], f0[k3PPT], p0[k3PPT];
+    __shared__ float P[k3T * k4P];
+    const OutTile T(g, blockIdx.x);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, kg = lane >> 4;
+    const bf16x4 wa = pk4[lane], wb = pk4[64 + lane];
+    int hi[k4Per];  // in-plane index of this lane's halo points, -1 outside
 #pragma unroll
-    for (int k = 0; k < k3PPT; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
-        const int x = T.x0 + 1 + p % k3X, y = T.y0 + 1 + (p / k3X) % k3Y, z = T.z0 + 1 + p / (k3X * k3Y);
-        live[k] = in_grid3(x, y, z, g.nx, g.ny, g.nz);
-        ip[k] = live[k] ? (int)(x + (long long)g.nx * (y + (long long)g.ny * z)) : 0;  // N < 2^28
-        r0[k] = r[ip[k]];
-        f0[k] = F0[ip[k]];
-        p0[k] = (rp ? rp : r)[ip[k]];
+    for (int j = 0; j < k4Per; ++j) {
+        const int h = 16 * (wave + 4 * j) + n, x = T.x0 + h % k4HX, y = T.y0 + h / k4HX;
+        hi[j] = h < k4Halo && x >= 0 && x < g.nx && y >= 0 && y < g.ny ? x + g.nx * y : -1;
     }
-    stage3d<16>(g, T, a3, sx);
-    __syncthreads();
+    const int nxy = g.nx * g.ny;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int px = T.x0 + 1 + tx, py = T.y0 + 1 + ty;
+    const bool live = px < g.nx && py < g.ny;
+    const int pi = live ? px + g.nx * py : 0;
+    const int z1 = T.z0 + 1, zend = min(z1 + k4Z, g.nz);  // output planes
+    const int zlast = min(zend, g.nz - 1);                // last input plane
+    bf16x4 x[k4Per];
+    auto load = [&](int z) {
+#pragma unroll
+        for (int j = 0; j < k4Per; ++j) {
+            const uint2 q = a3[4 * (long long)((long long)nxy * z + max(hi[j], 0)) + kg];
+            x[j] = __builtin_bit_cast(bf16x4, hi[j] >= 0 ? q : make_uint2(0u, 0u));
+        }
+    };
+    int z = max(T.z0, 0);
+    load(z);
+    float acc0 = 0.f, acc1 = 0.f;  // output planes z - 1, z
+    float r0 = 0.f, f0 = 0.f, p0 = 0.f;  // of output plane z - 1
     double zr = 0.0, zrp = 0.0;
+    const float *src = P + ty * k4HX + tx;
+#pragma unroll 1
+    for (;; ++z) {
+        const bool out = z - 1 >= z1;  // plane z - 1 ends with this one
+        const long long in = (long long)nxy * min(z, g.nz - 1) + pi;
+        const float r1 = r[in], f1 = F0[in], p1 = (rp ? rp : r)[in];
+        if (z <= zlast) {
 #pragma unroll
-    for (int k = 0; k < k3PPT; ++k) {
-        const int p = (int)threadIdx.x + 256 * k;
-        float acc = 0.f;
+            for (int j = 0; j < k4Per; ++j) {
+                const int grp = wave + 4 * j;
+                if (grp >= k4Groups) break;
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                const f32x4 da = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa, x[j], zero, 0, 0, 0);
+                const f32x4 db = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb, x[j], zero, 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < k3T; ++t) {
-            const uint4 *src = (const uint4 *)(sx + halo_idx(p, t) * 16);
-            const uint4 lo = src[0], hi = src[1];
-            const uint32_t v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, v[c]),
-                                                      __builtin_bit_cast(bf16x2v, w4[t * 8 + c]), acc,
-                                                      false);
+                for (int c = 0; c < 4; ++c) {
+                    P[(4 * kg + c) * k4P + 16 * grp + n] = da[c];
+                    if (16 + 4 * kg + c < k3T) P[(16 + 4 * kg + c) * k4P + 16 * grp + n] = db[c];
+                }
+            }
+            if (z < zlast) load(z + 1);
+            __syncthreads();
         }
-        if (live[k]) {
-            const float zi = f0[k] * r0[k] + acc;
-            zout[ip[k]] = zi;
-            zr += (double)zi * (double)r0[k];
-            zrp += rp ? (double)zi * (double)p0[k] : 0.0;
+        float s0 = 0.f, s1 = 0.f, s2 = 0.f;  // to output planes z + 1, z, z - 1
+        if (z <= zlast) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const float *q = src + t * k4P + (t / 3) * k4HX + t % 3;
+                s0 += q[0];
+                s1 += q[9 * k4P];
+                s2 += q[18 * k4P];
+            }
+            __syncthreads();
         }
+        if (out && live) {
+            const float zi = f0 * r0 + (acc0 + s2);
+            zout[(long long)nxy * (z - 1) + pi] = zi;
+            zr += (double)zi * (double)r0;
+            zrp += rp ? (double)zi * (double)p0 : 0.0;
+        }
+        if (z >= zend) break;
+        acc0 = acc1 + s1;
+        acc1 = s0;
+        r0 = r1;
+        f0 = f1;
+        p0 = p1;
     }
     if (part) block_partial_sum2(zr, zrp, part, part + gridDim.x);
 }
 
-// The A operands of layers 2 and 3 (3D), per lane: [layer][tap][lane];
-// then row 0 of layer 4's, [tap][ci / 4] (the only non-zero row).
-constexpr int k3Pack4 = 2 * k3T * 64, k3PackEntries = k3Pack4 + k3T * 4;
+// The A operands of layers 2 and 3 (3D), then layer 4's: two of 16 taps.
+constexpr int k3Pack4 = 2 * k3PackLayer, k3PackEntries = k3Pack4 + 2 * 64;
 __global__ void k_pack_mfma3d(const float *__restrict__ L2, const float *__restrict__ L3,
                               const float *__restrict__ L4, bf16x4 *__restrict__ out) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= k3PackEntries) return;
-    if (e >= k3Pack4) {
-        const int t = (e - k3Pack4) / 4, q = (e - k3Pack4) % 4;
-        bf16x4 v;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = bfbits(L4[(4 * q + c) * k3T + t]);
-        out[e] = v;
-        return;
+    const bool last = e >= k3Pack4;
+    const float *W = e >= k3PackLayer ? L3 : L2;
+    const int k = e % k3PackLayer;
+    int lane = e % 64, ci = 4 * (lane >> 4), t;
+    if (last) {
+        t = (e - k3Pack4) / 64 * 16 + (lane & 15);
+    } else if (k < k3PackPairs) {  // two entries a lane
+        lane = (k / 2) % 64;
+        ci = 8 * ((lane >> 4) & 1) + 4 * (k & 1);
+        t = k / 512 * 9 + 2 * (k / 128 % 4) + (lane >> 5);
+    } else {
+        t = (k - k3PackPairs) / 64 * 9 + 8;
     }
-    const int lane = e % 64, t = (e / 64) % k3T;
-    const float *W = e >= k3T * 64 ? L3 : L2;
-    const int co = lane & 15, k0 = (lane >> 4) * 4;
     bf16x4 v;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = bfbits(W[(co * 16 + k0 + c) * k3T + t]);
+    for (int c = 0; c < 4; ++c)
+        v[c] = !last ? bfbits(W[((lane & 15) * 16 + ci + c) * k3T + t])
+               : t < k3T ? bfbits(L4[(ci + c) * k3T + t]) : (short)0;
     out[e] = v;
 }
 
@@ -622,8 +782,9 @@ int net_pack_mfma(const adlbr_net *net, hipStream_t s) {
     return ADLBR_OK;
 }
 
+// Blocks of the last kernel, so partials of each dot.
 long long net3d_tiles(const GridInfo &g) {
-    return (long long)((g.nx + k3X - 1) / k3X) * ((g.ny + k3Y - 1) / k3Y) * ((g.nz + k3Z - 1) / k3Z);
+    return (long long)((g.nx + k4X - 1) / k4X) * ((g.ny + k4Y - 1) / k4Y) * ((g.nz + k4Z - 1) / k4Z);
 }
 
 // Packed 3D operands sit after the expanded 3D weights (T = 27).
@@ -647,14 +808,17 @@ int net_apply_mfma3d(const adlbr_net *net, const adlbr_operator *op, const float
     const bf16x4 *pk = (const bf16x4 *)(net->layers + kPackOffset3);
     // activations as BF16 [N][16] in the two halves of the FP32 scratch
     uint4 *A = (uint4 *)net->scratch, *B = (uint4 *)(net->scratch + 8 * N);
-    const unsigned nt = (unsigned)net3d_tiles(g);
-    hipLaunchKernelGGL(k_net3d_l1, dim3(nt), dim3(256), 0, s, g, r, L, net->gates8, A, st);
-    hipLaunchKernelGGL(k_net3d_mfma, dim3(nt), dim3(256), 0, s, g, (const uint2 *)A, pk,
-                       net->gates8, 16, (uint2 *)B, st);
-    hipLaunchKernelGGL(k_net3d_mfma, dim3(nt), dim3(256), 0, s, g, (const uint2 *)B, pk + k3T * 64,
-                       net->gates8, 0, (uint2 *)A, st);
-    hipLaunchKernelGGL(k_net3d_l4, dim3(nt), dim3(256), 0, s, g, (const uint2 *)A,
-                       (const uint32_t *)(pk + k3Pack4), r, net->features, z, rp, part, st);
+    // planes a block walks: enough blocks for two on each CU, four planes at
+    // least (two more are read for every block's ends)
+    const long long cols = (long long)((g.nx + k3X - 1) / k3X) * ((g.ny + k3Y - 1) / k3Y);
+    const int chunk = (int)std::max(4ll, (cols * g.nz + 511) / 512);
+    const unsigned nt = (unsigned)(cols * ((g.nz + chunk - 1) / chunk));
+    hipLaunchKernelGGL(k_net3d_l12, dim3(nt), dim3(k3BS), 0, s, g, chunk, r, L, pk, net->gates8,
+                       (uint2 *)B, st);
+    hipLaunchKernelGGL(k_net3d_l3, dim3(nt), dim3(k3BS), 0, s, g, chunk, (const uint4 *)B,
+                       pk + k3PackLayer, net->gates8, (uint2 *)A, st);
+    hipLaunchKernelGGL(k_net3d_l4, dim3((unsigned)net3d_tiles(g)), dim3(256), 0, s, g,
+                       (const uint2 *)A, pk + k3Pack4, r, net->features, z, rp, part, st);
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
 }
