@@ -54,16 +54,14 @@ ALGO_BYTES = {(2, 8): 16 + 3 * 8 + 4, (2, 4): 8 + 3 * 4 + 4, (2, 2): 4 + 3 * 2 +
 # SHA-256 of the kernel sources they were taken on.  A change to those
 # sources makes the figure stale: traffic is then null.
 TRAFFIC = {
-    "c2": {"sha256": "d3676bd68fc79b0d9177c3b6e1408435c139997d6e3b8b38eb5babe7dfa33d52",
-           "bytes_per_launch": 221648474},
-    "c3": {"sha256": "d3676bd68fc79b0d9177c3b6e1408435c139997d6e3b8b38eb5babe7dfa33d52",
-           "bytes_per_launch": 2434507093},
-    "c3-bf16": {"sha256": "d3676bd68fc79b0d9177c3b6e1408435c139997d6e3b8b38eb5babe7dfa33d52",
-                "bytes_per_launch": 1756668075},
-    "c4": {"sha256": "d3676bd68fc79b0d9177c3b6e1408435c139997d6e3b8b38eb5babe7dfa33d52",
-           "bytes_per_launch": 8376006510},
-    "c4-norecords": {"sha256": "d3676bd68fc79b0d9177c3b6e1408435c139997d6e3b8b38eb5babe7dfa33d52",
-                     "bytes_per_launch": 7052699068},
+    "c2": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
+           "bytes_per_launch": 268991923},
+    "c3": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
+           "bytes_per_launch": 1590143744},
+    "c3-bf16": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
+                "bytes_per_launch": 1227395456},
+    "c4": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
+           "bytes_per_launch": 6236442344},
 }
 TRAFFIC_SOURCES = ("paper_1301_3925_amd/csrc/operator.hip", "paper_1301_3925_amd/csrc/common.h")
 
@@ -106,8 +104,9 @@ def parse():
     ap.add_argument("--dtype", default=None, help="storage dtype for c3: f64|f32|bf16|f16")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-records", action="store_true",
-                    help="c4: 2D operators without records (each incoming weight gathered "
-                         "from its source instead of stored with the entry)")
+                    help="c4: 2D operators without the records flag (merged lists keep each "
+                         "weight with its entry either way; the edge ranks then share the "
+                         "records' memory)")
     ap.add_argument("--build-streams", type=int, default=8,
                     help="c4: streams the per-problem stencil builds and assemblies run on")
     ap.add_argument("--batch-variant", type=int, default=9,

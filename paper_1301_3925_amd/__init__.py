@@ -110,9 +110,12 @@ class Operator:
 
     tiled=True asks for the tiled layout (ADLBR_OP_TILED: explicit steps
     with tile + halo staged in LDS, near edges unlisted; Neumann grids,
-    F32/BF16/F16 storage; not for solve).  records=True keeps every 2D
-    incoming entry with its weight (ADLBR_OP_RECORDS), which a Batch of
-    such operators reads instead of gathering the weights.
+    F32/BF16/F16 storage; not for solve).  Every other operator merges
+    pairs of opposite edges (ADLBR_OP_MERGED) and keeps each remaining
+    incoming entry with its weight, unless a 2D workspace of the caller's
+    only holds the plain layout.  records=True (ADLBR_OP_RECORDS) asks for
+    that layout explicitly; a Batch gives such 2D operators a class of
+    their own.
 
     Holds its device workspace (a torch uint8 tensor) for its lifetime.
     With check=True (the default) the constructor synchronizes and raises

@@ -304,7 +304,8 @@ int true_residual(const adlbr_operator *op, double dt, const void *b, const doub
 
 // Reductions are two-phase and atomic-free: every block of a grid-wide
 // kernel writes its partial (block_partial_sum), then a one-block finisher
-// kernel sums the partials in a fixed order (reduce_partials).  Same-address
+// kernel, or every block of the solvers' next kernel, sums the partials in a
+// fixed order (reduce_partials).  Same-address
 // device-scope atomics serialize across the XCDs, so a "last block
 // finishes" ticket costs far more than the extra launch; the fixed order
 // also makes every reduction deterministic.
