@@ -633,26 +633,26 @@ __global__ __launch_bounds__(k3BS, 4) void k_net3d_l3(GridInfo g, int chunk, con
 // matrix instruction; taken the other way round it fills them: the 27 taps
 // are the rows, P[t][p] = sum_ci W4[ci][t] a3(p)[ci] is two instructions for
 // 16 points, and z sums P[t](p + off_t).  A block walks the planes of a
-// 16 x 16 column of k4Z points, P of one plane and its halo in LDS (FP32),
+// 16 x 16 column of points, P of one plane and its halo in LDS (FP32),
 // each thread one point of the plane with the sums of the three output
 // planes that the input plane reaches; the next plane's a3 is in flight
 // meanwhile.  With part, the block's FP64 partials of <z, r> in
 // part[blockIdx] and of <z, rp> in part[gridDim + blockIdx].
 // 128^3: 66 us as dot products over taps per point, 32 this way.
-constexpr int k4X = 16, k4Y = 16, k4Z = 8, k4HX = k4X + 2, k4Halo = k4HX * (k4Y + 2);
+constexpr int k4X = 16, k4Y = 16, k4HX = k4X + 2, k4Halo = k4HX * (k4Y + 2);
 constexpr int k4Groups = (k4Halo + 15) / 16, k4Per = (k4Groups + 3) / 4;
 constexpr int k4P = 16 * k4Groups;  // 336 = 5 * 64 + 16: taps four apart in different banks
 static_assert(k4P % 64 == 16, "tap planes staggered over the banks");
 struct OutTile {
     int x0, y0, z0;  // halo origin = tile origin - 1
-    __device__ __forceinline__ OutTile(const GridInfo &g, long long b) {
+    __device__ __forceinline__ OutTile(const GridInfo &g, long long b, int chunk) {
         const int ntx = (g.nx + k4X - 1) / k4X, nty = (g.ny + k4Y - 1) / k4Y;
         x0 = (int)(b % ntx) * k4X - 1;
         y0 = (int)((b / ntx) % nty) * k4Y - 1;
-        z0 = (int)(b / ((long long)ntx * nty)) * k4Z - 1;
+        z0 = (int)(b / ((long long)ntx * nty)) * chunk - 1;
     }
 };
-__global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, const uint2 *__restrict__ a3,
+__global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, int chunk, const uint2 *__restrict__ a3,
                                                   const bf16x4 *__restrict__ pk4,
                                                   const float *__restrict__ r,
                                                   const float *__restrict__ F0,
@@ -662,7 +662,7 @@ __global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, const uint2 *__res
                                                   const CgState *__restrict__ st) {
     if (st && (st->done || st->bad)) return;
     __shared__ float P[k3T * k4P];
-    const OutTile T(g, blockIdx.x);
+    const OutTile T(g, blockIdx.x, chunk);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, kg = lane >> 4;
     const bf16x4 wa = pk4[lane], wb = pk4[64 + lane];
     int hi[k4Per];  // in-plane index of this lane's halo points, -1 outside
@@ -676,7 +676,7 @@ __global__ __launch_bounds__(256) void k_net3d_l4(GridInfo g, const uint2 *__res
     const int px = T.x0 + 1 + tx, py = T.y0 + 1 + ty;
     const bool live = px < g.nx && py < g.ny;
     const int pi = live ? px + g.nx * py : 0;
-    const int z1 = T.z0 + 1, zend = min(z1 + k4Z, g.nz);  // output planes
+    const int z1 = T.z0 + 1, zend = min(z1 + chunk, g.nz);  // output planes
     const int zlast = min(zend, g.nz - 1);                // last input plane
     bf16x4 x[k4Per];
     auto load = [&](int z) {
@@ -782,9 +782,23 @@ int net_pack_mfma(const adlbr_net *net, hipStream_t s) {
     return ADLBR_OK;
 }
 
+// Planes a block of a 3D kernel walks: as many as leave `blocks` blocks.  Two
+// more are read for its ends, and every plane is a wait of its own when the
+// data are cold, so a grid that leaves CUs idle is cut into single planes
+// (a first pass of 64^3 and less).
+static int net3d_chunk(long long cols, int nz, long long blocks) {
+    return (int)((cols * nz + blocks - 1) / blocks);
+}
+// The last kernel's: up to eight; 384 blocks and one more a column leave at
+// most the 768 partials that the solver always has room for.
+static int net3d_out_chunk(const GridInfo &g) {
+    const long long cols = (long long)((g.nx + k4X - 1) / k4X) * ((g.ny + k4Y - 1) / k4Y);
+    return cols >= 384 ? 8 : std::min(8, net3d_chunk(cols, g.nz, 384));
+}
 // Blocks of the last kernel, so partials of each dot.
 long long net3d_tiles(const GridInfo &g) {
-    return (long long)((g.nx + k4X - 1) / k4X) * ((g.ny + k4Y - 1) / k4Y) * ((g.nz + k4Z - 1) / k4Z);
+    const int chunk = net3d_out_chunk(g);
+    return (long long)((g.nx + k4X - 1) / k4X) * ((g.ny + k4Y - 1) / k4Y) * ((g.nz + chunk - 1) / chunk);
 }
 
 // Packed 3D operands sit after the expanded 3D weights (T = 27).
@@ -808,17 +822,15 @@ int net_apply_mfma3d(const adlbr_net *net, const adlbr_operator *op, const float
     const bf16x4 *pk = (const bf16x4 *)(net->layers + kPackOffset3);
     // activations as BF16 [N][16] in the two halves of the FP32 scratch
     uint4 *A = (uint4 *)net->scratch, *B = (uint4 *)(net->scratch + 8 * N);
-    // planes a block walks: enough blocks for two on each CU, four planes at
-    // least (two more are read for every block's ends)
     const long long cols = (long long)((g.nx + k3X - 1) / k3X) * ((g.ny + k3Y - 1) / k3Y);
-    const int chunk = (int)std::max(4ll, (cols * g.nz + 511) / 512);
+    const int chunk = net3d_chunk(cols, g.nz, 512);  // two blocks a CU
     const unsigned nt = (unsigned)(cols * ((g.nz + chunk - 1) / chunk));
     hipLaunchKernelGGL(k_net3d_l12, dim3(nt), dim3(k3BS), 0, s, g, chunk, r, L, pk, net->gates8,
                        (uint2 *)B, st);
     hipLaunchKernelGGL(k_net3d_l3, dim3(nt), dim3(k3BS), 0, s, g, chunk, (const uint4 *)B,
                        pk + k3PackLayer, net->gates8, (uint2 *)A, st);
     hipLaunchKernelGGL(k_net3d_l4, dim3((unsigned)net3d_tiles(g)), dim3(256), 0, s, g,
-                       (const uint2 *)A, pk + k3Pack4, r, net->features, z, rp, part, st);
+                       net3d_out_chunk(g), (const uint2 *)A, pk + k3Pack4, r, net->features, z, rp, part, st);
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
 }
