@@ -21,6 +21,7 @@
 namespace adlbr {
 
 int apply_K(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s);
+int apply_K_loss(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s);
 int net_apply_mfma(const adlbr_net *net, const adlbr_operator *op, const float *r, float *z,
                    const float *rp, double *part, const CgState *st, hipStream_t s);
 int net_mfma_blocks(int nx, int ny);
@@ -1194,7 +1195,7 @@ extern "C" int adlbr_net_loss_grad(adlbr_operator *op, double dt, const float *r
     const long long nb = nblk(N);
     hipLaunchKernelGGL(k_dot_self, dim3(nb), dim3(kBS), 0, s, N, r, part);
     hipLaunchKernelGGL(k_dot_self_fin, dim3(1), dim3(kFinish), 0, s, ls, (const double *)part, nb);
-    int rc = apply_K(op, z, gz, dt, s);  // gz = K z
+    int rc = apply_K_loss(op, z, gz, dt, s);  // gz = K z
     if (rc) return rc;
     hipLaunchKernelGGL(k_loss_grad, dim3(nb), dim3(kBS), 0, s, N, z, r, gz, (const LossState *)ls,
                        part);

@@ -2504,6 +2504,92 @@ __global__ __launch_bounds__(kBS) void k_residual(
     block_partial_sum(r2, partial);
 }
 
+// out = (I + dt A) u of a merged FP32 operator in the sums of one without
+// merged pairs, bit for bit: the own weights in slot order, a slot's two
+// differences together, and every incoming edge, listed or merged, in the order of (source, slot), each
+// weight by itself.  A thread per row; the partner of a merged edge is looked
+// up among its source's slots.  For results whose rounding is itself seen
+// (the training loss of a small grid, returned in FP64).
+template <int DIM, bool WIDE, bool PER>
+__global__ __launch_bounds__(256) void k_apply_K_ordered(
+    GridInfo g, const float *__restrict__ u, float *__restrict__ out,
+    const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const float *__restrict__ w,
+    const uint8_t *__restrict__ mask, const lmask_t<DIM> *__restrict__ lmask,
+    const int32_t *__restrict__ pos, const int32_t *__restrict__ ent,
+    const EntRec<float> *__restrict__ went, float h) {
+#pragma clang fp contract(off)
+    constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
+    const long long N = g.N, z = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (z >= N) return;
+    const auto mine = sb[z];
+    Slots<DIM, WIDE> sl;
+    sl.load(&mine, 0);
+    const unsigned m = slot_mask<DIM, WIDE>(mine, mask, z), listed = lmask[z];
+    const SlotKeys<DIM, WIDE> own(sl);
+    const Coord p = coords(z, g);
+    const float uz = u[z];
+    float acc = 0.f, part = 0.f, val[E];
+    int key[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        const int q = k >> 1, sg = k & 1 ? 1 : -1;
+        const float wo = w[widx<S>(q, z, N)];
+        long long t = z;
+        const bool ok = edge_target<DIM, PER>(p, z, sl.o[q], sg, g, t) && t != z;
+        const float du = uz - u[ok ? t : z];
+        part = k & 1 ? part + du : du;
+        if (k & 1) acc = __builtin_fmaf(wo, part, acc);
+        key[k] = 0x7fffffff;
+        val[k] = 0.f;
+        if (!ok || !((m >> q) & 1u) || ((listed >> k) & 1u) || z - t >= (1ll << 22) || z - t <= -(1ll << 22))
+            continue;
+        const auto theirs = sb[t];
+        Slots<DIM, WIDE> ts;
+        ts.load(&theirs, 0);
+        const SlotKeys<DIM, WIDE> other(ts);
+        const unsigned mt = slot_mask<DIM, WIDE>(theirs, mask, t);
+        int slot = -1;
+#pragma unroll
+        for (int r = 0; r < S; ++r)
+            if (((mt >> r) & 1u) && other.a[r] == own.a[q]) slot = r;
+        if (slot < 0) continue;  // (every merged edge has its partner)
+        key[k] = (int)((t - z) * 8) + slot;
+        val[k] = w[widx<S>(slot, t, N)] * du;
+    }
+#pragma unroll
+    for (int round = 0; round < E; ++round)  // odd-even transposition by key
+#pragma unroll
+        for (int i = round & 1; i + 1 < E; i += 2) {
+            const bool sw = key[i] > key[i + 1];
+            const int a = key[i], b = key[i + 1];
+            const float x = val[i], y = val[i + 1];
+            key[i] = sw ? b : a;
+            key[i + 1] = sw ? a : b;
+            val[i] = sw ? y : x;
+            val[i + 1] = sw ? x : y;
+        }
+    float in = 0.f;
+    int j = pos[z];
+    const int end = pos[z + 1];
+    int32_t e = 0;
+    float we = 0.f;
+    if (j < end) load_rec<float>(went, ent, j, true, e, we);
+    const auto until = [&](int bound) {  // the listed entries below a key
+#pragma clang fp contract(off)
+        while (j < end && (e >> 6) < bound) {
+            in += we * (uz - u[z + (e >> 9)]);
+            if (++j < end) load_rec<float>(went, ent, j, true, e, we);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        until(key[k]);
+        if (key[k] != 0x7fffffff) in += val[k];
+    }
+    until(0x7fffffff);
+    out[z] = __builtin_fmaf(-h, in + acc, uz);
+}
+
 __global__ __launch_bounds__(kFinish) void k_sum_partials(const double *partial, long long nb,
                                                       double *out) {
     const double t = reduce_partials(partial, nb);
@@ -2956,6 +3042,32 @@ int cg_direction(const adlbr_operator *op, const void *z, void *q, void *p, CgSt
 // out = (I + dt A) u, written as one explicit step with step -dt.
 int apply_K(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s) {
     return dispatch<ApplyF>(op, u, out, true, -dt, (int)ADLBR_DT_ABS, s);
+}
+
+template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struct OrderedF {
+    static int run(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s) {
+        if constexpr (MG && std::is_same_v<TS, float>) {
+            typedef typename Slots<DIM, WIDE>::store_t store_t;
+            const unsigned nb = (unsigned)((op->gi.N + 255) / 256);
+            hipLaunchKernelGGL((k_apply_K_ordered<DIM, WIDE, PER>), dim3(nb), dim3(256), 0, s, op->gi,
+                               (const float *)u, (float *)out, (const store_t *)op->sb,
+                               (const float *)op->w, (const uint8_t *)op->mask,
+                               (const lmask_t<DIM> *)op->lmask, op->pos, op->ent,
+                               (const EntRec<float> *)op->went, (float)-dt);
+            return ADLBR_OK;
+        }
+        return ADLBR_E_UNSUPPORTED;
+    }
+};
+
+// out = (I + dt A) u for the training loss.  The loss is an FP64 sum of FP32
+// rows; below 2^16 points their roundings do not average out of its ninth
+// digit, so those grids take the rows in the order of an operator without
+// merged pairs (64 x 67: the loss differs by 1.8e-9 between the two).
+int apply_K_loss(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s) {
+    if (op->merged && op->storage == ADLBR_F32 && op->gi.N < (1 << 16))
+        return dispatch<OrderedF>(op, u, out, dt, s);
+    return apply_K(op, u, out, dt, s);
 }
 
 int true_residual(const adlbr_operator *op, double dt, const void *b, const double *x,
