@@ -2504,9 +2504,9 @@ __global__ __launch_bounds__(kBS) void k_residual(
     block_partial_sum(r2, partial);
 }
 
-// out = (I + dt A) u of a merged FP32 operator in the sums of one without
-// merged pairs, bit for bit: the own weights in slot order, a slot's two
-// differences together, and every incoming edge, listed or merged, in the order of (source, slot), each
+// out = (I + dt A) u of a merged FP32 operator with every weight by itself, no
+// pair's sum rounded: the own weights in slot order, a slot's two differences
+// together, and every incoming edge, listed or merged, in the order of (source, slot), each
 // weight by itself.  A thread per row; the partner of a merged edge is looked
 // up among its source's slots.  For results whose rounding is itself seen
 // (the training loss of a small grid, returned in FP64).
@@ -3062,8 +3062,8 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
 
 // out = (I + dt A) u for the training loss.  The loss is an FP64 sum of FP32
 // rows; below 2^16 points their roundings do not average out of its ninth
-// digit, so those grids take the rows in the order of an operator without
-// merged pairs (64 x 67: the loss differs by 1.8e-9 between the two).
+// digit, so those grids take every edge by itself, in the order of complete
+// lists (64 x 67: the loss differs by 1.8e-9 between the two).
 int apply_K_loss(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s) {
     if (op->merged && op->storage == ADLBR_F32 && op->gi.N < (1 << 16))
         return dispatch<OrderedF>(op, u, out, dt, s);
