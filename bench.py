@@ -54,14 +54,14 @@ ALGO_BYTES = {(2, 8): 16 + 3 * 8 + 4, (2, 4): 8 + 3 * 4 + 4, (2, 2): 4 + 3 * 2 +
 # SHA-256 of the kernel sources they were taken on.  A change to those
 # sources makes the figure stale: traffic is then null.
 TRAFFIC = {
-    "c2": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
-           "bytes_per_launch": 268991923},
-    "c3": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
-           "bytes_per_launch": 1590143744},
-    "c3-bf16": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
-                "bytes_per_launch": 1227395456},
-    "c4": {"sha256": "f2faf1522aacc833ea33b53673ff2d3f09a688cc9c6a2e7eba2ce630994f2575",
-           "bytes_per_launch": 6236442344},
+    "c2": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
+           "bytes_per_launch": 269012774},
+    "c3": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
+           "bytes_per_launch": 1590070656},
+    "c3-bf16": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
+                "bytes_per_launch": 1227362133},
+    "c4": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
+           "bytes_per_launch": 6236438198},
 }
 TRAFFIC_SOURCES = ("paper_1301_3925_amd/csrc/operator.hip", "paper_1301_3925_amd/csrc/common.h")
 
