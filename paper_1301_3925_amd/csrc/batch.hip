@@ -202,8 +202,13 @@ int enqueue_steps(adlbr_batch *b, long long nsteps, hipStream_t s) {
     return ADLBR_OK;
 }
 
+// A replay of the graph may still be running (the last call has returned): it
+// is waited for, since the runtime's nodes and branches go with the graph.
 void drop_graph(adlbr_batch *b) {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
+    if (b->exec) {
+        (void)hipStreamSynchronize(b->own);
+        (void)hipGraphExecDestroy(b->exec);
+    }
     if (b->graph) (void)hipGraphDestroy(b->graph);
     b->exec = nullptr;
     b->graph = nullptr;
