@@ -1637,6 +1637,85 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
     }
 };
 
+// The own part of a merged FP32 row with every weight as it was given: the
+// own one and, where the edge is merged, its partner's, found again among the
+// target's slots (the stored sum of the two has been rounded to FP32).  For
+// rows summed in FP64, whose result must be that of the given weights: the
+// residual that decides a solve's convergence.  The edges are OwnEdges', the
+// lookup k_merge's, at about the cost of both.
+template <int DIM, bool WIDE, bool PER> struct PairEdges {
+    static constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
+    float wo[S], wp[E];  // own weights; merged partners', 0 without one
+    unsigned ok;
+    unsigned t[E];
+    __device__ __forceinline__ void load(const GridInfo &g, long long z, bool live,
+                                         const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
+                                         const float *__restrict__ w,
+                                         const uint8_t *__restrict__ mask,
+                                         const lmask_t<DIM> *__restrict__ lmask) {
+        typedef typename Slots<DIM, WIDE>::store_t store_t;
+        const int N = (int)g.N, zi = live ? (int)z : 0;
+        const store_t mine = sb[zi];
+        Slots<DIM, WIDE> sl;
+        sl.load(&mine, 0);
+        const unsigned m = slot_mask<DIM, WIDE>(mine, mask, zi), listed = lmask[zi];
+#pragma unroll
+        for (int q = 0; q < S; ++q) wo[q] = w[widx32<S>(q, zi, N)];
+        const SlotKeys<DIM, WIDE> own(sl);
+        const Coord p = coords(zi, g);
+        ok = 0u;
+        unsigned pair = 0u;  // neither listed nor without weight: merged
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            int tk = zi;
+            const bool in = edge_target32<DIM, PER>(p, zi, sl.o[k >> 1], k & 1 ? 1 : -1, g, tk);
+            t[k] = (unsigned)(in ? tk : zi);
+            ok |= (in && tk != zi ? 1u : 0u) << k;
+            pair |= (((m >> (k >> 1)) & 1u) && !((listed >> k) & 1u) && zi - tk < (1 << 22) &&
+                             zi - tk > -(1 << 22)
+                         ? 1u : 0u) << k;
+        }
+        pair &= ok;
+#pragma unroll
+        for (int b = 0; b < E; b += 6) {
+            store_t raw[6];
+            unsigned mt[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                raw[i] = sb[t[b + i]];
+                mt[i] = DIM == 2 ? mask[t[b + i]] : 0u;
+            }
+            bool hit[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                if (DIM == 3) mt[i] = slot_mask<DIM, WIDE>(raw[i], mask, 0);
+                Slots<DIM, WIDE> ts;
+                ts.load(&raw[i], 0);
+                const SlotKeys<DIM, WIDE> other(ts);
+                int slot = -1;
+#pragma unroll
+                for (int r = 0; r < S; ++r)
+                    if (((mt[i] >> r) & 1u) && other.a[r] == own.a[(b + i) >> 1]) slot = r;
+                hit[i] = ((pair >> (b + i)) & 1u) && slot >= 0;
+                wp[b + i] = w[hit[i] ? widx32<S>(slot, (int)t[b + i], N) : widx32<S>(0, zi, N)];
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) wp[b + i] = hit[i] ? wp[b + i] : 0.f;
+        }
+    }
+    __device__ __forceinline__ double weight(int k) const {
+        return (ok >> k) & 1u ? (double)wo[k >> 1] + (double)wp[k] : 0.0;
+    }
+};
+
+// The edges of a row that is summed in FP64: PairEdges where the stored sums
+// are FP32, OwnEdges otherwise.
+template <int DIM, bool WIDE, bool PER, bool MG, typename T> struct Edges64 {
+    static constexpr bool kPairs = MG && std::is_same_v<T, float>;
+    typedef std::conditional_t<kPairs, PairEdges<DIM, WIDE, PER>,
+                               OwnEdges<DIM, WIDE, PER, MG, T, double>> type;
+};
+
 // Chunks of 64 entries whose loads a wave has in flight at once: 8 with
 // 32-bit arithmetic; 4 with FP64, whose wider values would otherwise cost
 // occupancy (109 instead of 81 registers in the 3D step).
@@ -2471,15 +2550,16 @@ __global__ __launch_bounds__(kBS) void k_cg_direction(
     block_sum_to(pqz, partial + blk);
 }
 
-// |b - (x + dt A x)|^2 with FP64 arithmetic (weights promoted); block
-// partials, finished by k_sum_partials.
+// |b - (x + dt A x)|^2 with FP64 arithmetic on the weights as they were given
+// (an FP32 operator's each by itself, Edges64); block partials, finished by
+// k_sum_partials.
 template <int DIM, bool WIDE, bool PER, bool MG, typename T>
 __global__ __launch_bounds__(kBS) void k_residual(
     GridInfo g, const T *__restrict__ b, const double *__restrict__ x,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const void *__restrict__ wp,
     const int32_t *__restrict__ pos, const int32_t *__restrict__ ent,
-    const EntRec<T> *__restrict__ went, double dt, double *partial,
-    T *__restrict__ rout) {
+    const EntRec<T> *__restrict__ went, const T *__restrict__ w, const uint8_t *__restrict__ mask,
+    const lmask_t<DIM> *__restrict__ lmask, double dt, double *partial, T *__restrict__ rout) {
     const long long N = g.N;
     // the apply's block order (XCD bands; 3D strips of planes); the partial
     // stays at blockIdx.x
@@ -2489,8 +2569,10 @@ __global__ __launch_bounds__(kBS) void k_residual(
     double r2 = 0.0;
     const WaveLists L = wave_lists(pos, z, N);
     const double xz = live ? x[z] : 0.0;
-    OwnEdges<DIM, WIDE, PER, MG, T, double> edges;
-    edges.load(g, z, live, sb, wp);
+    typedef Edges64<DIM, WIDE, PER, MG, T> E64;
+    typename E64::type edges;
+    if constexpr (E64::kPairs) edges.load(g, z, live, sb, w, mask, lmask);
+    else edges.load(g, z, live, sb, wp);
     OwnPart<decltype(edges), double, double> own;
     own.issue(edges, x);
     double ax = wave_incoming<MG, DIM == 2 ? 3 : 6, T, double, double>(L, z0, N, xz, x, (const T *)wp,
@@ -2895,7 +2977,9 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
         const GridInfo g = op->gi;
         const unsigned nb = (unsigned)((g.N + kBS - 1) / kBS);
         hipLaunchKernelGGL((k_residual<DIM, WIDE, PER, MG, TS>), dim3(nb), dim3(kBS), 0, s, g,
-                           (const TS *)b, x, (const store_t *)op->sb, op->wp, op->pos, op->ent, (const EntRec<TS> *)op->went, dt, partial, (TS *)rout);
+                           (const TS *)b, x, (const store_t *)op->sb, op->wp, op->pos, op->ent,
+                           (const EntRec<TS> *)op->went, (const TS *)op->w, (const uint8_t *)op->mask,
+                           (const lmask_t<DIM> *)op->lmask, dt, partial, (TS *)rout);
         hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kFinish), 0, s, (const double *)partial,
                            (long long)nb, out);
         return ADLBR_OK;
