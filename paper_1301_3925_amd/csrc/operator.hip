@@ -338,8 +338,9 @@ __global__ __launch_bounds__(256) void k_compact(
 // 1021x767 image 52 -> 25 us.
 //
 // Weights of a point's 2S directed edges, k = 2q + (sign > 0), as the apply
-// reads them: F64/F32 the 2S sums w_q(z) + (merged ? w(t) : 0), 0 for an edge
-// that leaves the grid or folds onto the point; 16-bit storage the S own
+// reads them: F64/F32 the 2S sums w_q(z) + (merged ? w(t) : 0), -0 for an edge
+// that leaves the grid or folds onto the point (no sum is: the partner's term
+// is +0 or more); 16-bit storage the S own
 // weights, then per edge the partner's weight (0 unmerged, -1 for a missing
 // edge): their sum is formed in FP32, so no weight is rounded twice.
 // Layout: groups of 64 points, each group's words in planes of 16 bytes a
@@ -408,11 +409,17 @@ template <int DIM, typename TS> struct MergedW {
             v[i >> 1] = i & 1 ? (v[i >> 1] & 0xffffu) | b << 16 : b;
         }
     }
-    // weight of edge k in the arithmetic type TA
+    // edge k leaves the grid or folds onto the point
+    __device__ __forceinline__ bool missing(int k) const {
+        if constexpr (SPLIT) return (v[(S + k) >> 1] >> (16 * ((S + k) & 1))) & 0x8000u;
+        else if constexpr (sizeof(TS) == 8) return v[2 * k] == 0u && v[2 * k + 1] == 0x80000000u;
+        else return v[k] == 0x80000000u;
+    }
+    // weight of edge k (where it is not missing) in the arithmetic type TA
     template <typename TA> __device__ __forceinline__ TA edge(int k) const {
         if constexpr (SPLIT) {
             const TA p = (TA)Conv<TS, float>::ld(raw(S + k));
-            return p < (TA)0 ? (TA)0 : (TA)Conv<TS, float>::ld(raw(k >> 1)) + p;
+            return (TA)Conv<TS, float>::ld(raw(k >> 1)) + (missing(k) ? (TA)0 : p);
         } else {
             return (TA)raw(k);
         }
@@ -603,7 +610,7 @@ __global__ __launch_bounds__(256) void k_merge(
                 if constexpr (MergedW<DIM, TS>::SPLIT)
                     mw.set(S + k, ok ? (hit ? wp[i] : TS{}) : Conv<TS, float>::st(-1.0f));
                 else
-                    mw.set(k, (TS)(wv + pv));
+                    mw.set(k, ok ? (TS)(wv + pv) : -(TS)0);
             }
         }
         listed &= ~merged;
@@ -1551,7 +1558,9 @@ __device__ __forceinline__ int fold_in(int v, int n, int mode) {
 
 // Own part of row z: sum over its 2S directed edges (z, s o) in the grid of
 // W (u(z) - u(z + s o)).  Merged operators (MG): W is the edge's weight with
-// its partner's (MergedW; 0 for a missing edge); others: w_o(z).  Split so
+// its partner's (MergedW); others: w_o(z).  The term of a missing edge has
+// u(z) - u(z) in it, that of an edge of weight 0 its own difference: both are 0
+// unless u is not finite there, which the row then shows.  Split so
 // that a kernel can issue these loads before the dependent loads of the
 // incoming part, and use a row's edges for several components: load() loads
 // the slots and weights and forms the targets, issue() loads the neighbour
@@ -1611,10 +1620,13 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
             }
         }
     }
-    // weight of edge k, 0 where it is missing
     __device__ __forceinline__ TA weight(int k) const {
         if constexpr (MG) return mw.template edge<TA>(k);
-        else return (ok >> k) & 1u ? (TA)Conv<TS, TA>::ld(wo[k >> 1]) : (TA)0;
+        else return (TA)Conv<TS, TA>::ld(wo[k >> 1]);
+    }
+    __device__ __forceinline__ bool missing(int k) const {
+        if constexpr (MG) return mw.missing(k);
+        else return !((ok >> k) & 1u);
     }
 };
 
@@ -1627,12 +1639,10 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
     // the own part of a live row (a dead lane's sum is not used)
     __device__ __forceinline__ TA sum(const Edges &e, TA uz) const {
         TA acc = (TA)0;
+        const TA none = uz - uz;
 #pragma unroll
-        for (int k = 0; k < Edges::E; ++k) {
-            const TA w = e.weight(k);
-            const TA du = uz - Conv<TU, TA>::ld(ur[k]);
-            acc += w * (w != (TA)0 ? du : (TA)0);
-        }
+        for (int k = 0; k < Edges::E; ++k)
+            acc += e.weight(k) * (e.missing(k) ? none : uz - Conv<TU, TA>::ld(ur[k]));
         return acc;
     }
 };
@@ -1704,8 +1714,9 @@ template <int DIM, bool WIDE, bool PER> struct PairEdges {
         }
     }
     __device__ __forceinline__ double weight(int k) const {
-        return (ok >> k) & 1u ? (double)wo[k >> 1] + (double)wp[k] : 0.0;
+        return (double)wo[k >> 1] + (double)wp[k];
     }
+    __device__ __forceinline__ bool missing(int k) const { return !((ok >> k) & 1u); }
 };
 
 // The edges of a row that is summed in FP64: PairEdges where the stored sums
