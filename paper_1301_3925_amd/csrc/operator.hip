@@ -1572,6 +1572,7 @@ __device__ __forceinline__ int fold_in(int v, int n, int mode) {
 // branch around a load, and the wave issues them all before it waits.
 template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struct OwnEdges {
     static constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
+    static constexpr bool kSlots = !MG;  // a slot's two edges have one weight
     MergedW<DIM, TS> mw;  // MG
     TS wo[S];             // otherwise, with the edges that exist
     unsigned ok;
@@ -1636,13 +1637,16 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
 #pragma unroll
         for (int k = 0; k < Edges::E; ++k) ur[k] = u[e.t[k]];
     }
-    // the own part of a live row (a dead lane's sum is not used)
+    // the own part of a live row (a dead lane's sum is not used); without
+    // merging a slot's two differences are added first, so that opposite ones
+    // cancel before they are multiplied
     __device__ __forceinline__ TA sum(const Edges &e, TA uz) const {
         TA acc = (TA)0;
         const TA none = uz - uz;
+        const auto du = [&](int k) { return e.missing(k) ? none : uz - Conv<TU, TA>::ld(ur[k]); };
 #pragma unroll
-        for (int k = 0; k < Edges::E; ++k)
-            acc += e.weight(k) * (e.missing(k) ? none : uz - Conv<TU, TA>::ld(ur[k]));
+        for (int k = 0; k < Edges::E; k += Edges::kSlots ? 2 : 1)
+            acc += e.weight(k) * (Edges::kSlots ? du(k) + du(k + (Edges::kSlots ? 1 : 0)) : du(k));
         return acc;
     }
 };
@@ -1655,6 +1659,7 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
 // lookup k_merge's, at about the cost of both.
 template <int DIM, bool WIDE, bool PER> struct PairEdges {
     static constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
+    static constexpr bool kSlots = false;
     float wo[S], wp[E];  // own weights; merged partners', 0 without one
     unsigned ok;
     unsigned t[E];
