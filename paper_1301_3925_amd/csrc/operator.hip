@@ -1654,13 +1654,14 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
 // The own part of a merged FP32 row with every weight as it was given: the
 // own one and, where the edge is merged, its partner's, found again among the
 // target's slots (the stored sum of the two has been rounded to FP32).  For
-// rows summed in FP64, whose result must be that of the given weights: the
-// residual that decides a solve's convergence.  The edges are OwnEdges', the
+// results that must be those of the given weights: the FP64 residual that
+// decides a solve's convergence, and the training loss.  The edges are OwnEdges', the
 // lookup k_merge's, at about the cost of both.
 template <int DIM, bool WIDE, bool PER> struct PairEdges {
     static constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
     static constexpr bool kSlots = false;
     float wo[S], wp[E];  // own weights; merged partners', 0 without one
+    int slot[E];         // partner's slot at the target, -1 without one
     unsigned ok;
     unsigned t[E];
     __device__ __forceinline__ void load(const GridInfo &g, long long z, bool live,
@@ -1700,22 +1701,23 @@ template <int DIM, bool WIDE, bool PER> struct PairEdges {
                 raw[i] = sb[t[b + i]];
                 mt[i] = DIM == 2 ? mask[t[b + i]] : 0u;
             }
-            bool hit[6];
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
                 if (DIM == 3) mt[i] = slot_mask<DIM, WIDE>(raw[i], mask, 0);
                 Slots<DIM, WIDE> ts;
                 ts.load(&raw[i], 0);
                 const SlotKeys<DIM, WIDE> other(ts);
-                int slot = -1;
+                slot[b + i] = -1;
 #pragma unroll
                 for (int r = 0; r < S; ++r)
-                    if (((mt[i] >> r) & 1u) && other.a[r] == own.a[(b + i) >> 1]) slot = r;
-                hit[i] = ((pair >> (b + i)) & 1u) && slot >= 0;
-                wp[b + i] = w[hit[i] ? widx32<S>(slot, (int)t[b + i], N) : widx32<S>(0, zi, N)];
+                    if (((pair >> (b + i)) & 1u) && ((mt[i] >> r) & 1u) &&
+                        other.a[r] == own.a[(b + i) >> 1])
+                        slot[b + i] = r;
+                const bool hit = slot[b + i] >= 0;
+                wp[b + i] = w[hit ? widx32<S>(slot[b + i], (int)t[b + i], N) : widx32<S>(0, zi, N)];
             }
 #pragma unroll
-            for (int i = 0; i < 6; ++i) wp[b + i] = hit[i] ? wp[b + i] : 0.f;
+            for (int i = 0; i < 6; ++i) wp[b + i] = slot[b + i] >= 0 ? wp[b + i] : 0.f;
         }
     }
     __device__ __forceinline__ double weight(int k) const {
@@ -2602,57 +2604,50 @@ __global__ __launch_bounds__(kBS) void k_residual(
     block_partial_sum(r2, partial);
 }
 
-// out = (I + dt A) u of a merged FP32 operator with every weight by itself, no
-// pair's sum rounded: the own weights in slot order, a slot's two differences
-// together, and every incoming edge, listed or merged, in the order of (source, slot), each
-// weight by itself.  A thread per row; the partner of a merged edge is looked
-// up among its source's slots.  For results whose rounding is itself seen
-// (the training loss of a small grid, returned in FP64).
+// out = (I + dt A) u of a merged FP32 operator with every weight by itself, in
+// the sums of an operator without merged pairs, bit for bit: the own weights in
+// slot order, a slot's two differences together, and every incoming edge,
+// listed or merged, in the order of (source, slot).  The partner of a merged
+// edge is looked up among its source's slots.  For a result whose rounding is
+// itself seen: the training loss, an FP64 sum of FP32 rows.
+// The listed values pass through LDS in windows as in wave_incoming; the
+// merged ones, sorted in registers, wait there for their places.  Bound by the
+// lookups' gathers (a loss and its gradient at 1024^2 and 128^3: 63 and 293 us
+// with a row's list walked from memory by its lane, 56 and 200 this
+// way, 35 and 74 on the rounded pair sums).
 template <int DIM, bool WIDE, bool PER>
-__global__ __launch_bounds__(256) void k_apply_K_ordered(
+__global__ __launch_bounds__(kBS) void k_apply_K_ordered(
     GridInfo g, const float *__restrict__ u, float *__restrict__ out,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const float *__restrict__ w,
     const uint8_t *__restrict__ mask, const lmask_t<DIM> *__restrict__ lmask,
     const int32_t *__restrict__ pos, const int32_t *__restrict__ ent,
     const EntRec<float> *__restrict__ went, float h) {
 #pragma clang fp contract(off)
-    constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
-    const long long N = g.N, z = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (z >= N) return;
-    const auto mine = sb[z];
-    Slots<DIM, WIDE> sl;
-    sl.load(&mine, 0);
-    const unsigned m = slot_mask<DIM, WIDE>(mine, mask, z), listed = lmask[z];
-    const SlotKeys<DIM, WIDE> own(sl);
-    const Coord p = coords(z, g);
-    const float uz = u[z];
+    constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S, KP = 4;
+    constexpr int kNone = 0x7fffffff;
+    __shared__ int mkey[kBS / 64][E][64], lkey[kBS / 64][64 * KP];
+    __shared__ float mval[kBS / 64][E][64], lval[kBS / 64][64 * KP];
+    const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+    const long long N = g.N;
+    const long long blk = strip_block(xcd_block(blockIdx.x, gridDim.x), g, kApplyPoints);
+    const long long z0 = wave_group(g, blk), z = z0 + lane;
+    const bool live = z < N;
+    const WaveLists L = wave_lists(pos, z, N);
+    const float uz = live ? u[z] : 0.f;
+    PairEdges<DIM, WIDE, PER> edges;
+    edges.load(g, z, live, sb, w, mask, lmask);
+    OwnPart<decltype(edges), float, float> own;
+    own.issue(edges, u);
     float acc = 0.f, part = 0.f, val[E];
     int key[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        const int q = k >> 1, sg = k & 1 ? 1 : -1;
-        const float wo = w[widx<S>(q, z, N)];
-        long long t = z;
-        const bool ok = edge_target<DIM, PER>(p, z, sl.o[q], sg, g, t) && t != z;
-        const float du = uz - u[ok ? t : z];
+        const float du = edges.missing(k) ? uz - uz : uz - own.ur[k];
         part = k & 1 ? part + du : du;
-        if (k & 1) acc = __builtin_fmaf(wo, part, acc);
-        key[k] = 0x7fffffff;
-        val[k] = 0.f;
-        if (!ok || !((m >> q) & 1u) || ((listed >> k) & 1u) || z - t >= (1ll << 22) || z - t <= -(1ll << 22))
-            continue;
-        const auto theirs = sb[t];
-        Slots<DIM, WIDE> ts;
-        ts.load(&theirs, 0);
-        const SlotKeys<DIM, WIDE> other(ts);
-        const unsigned mt = slot_mask<DIM, WIDE>(theirs, mask, t);
-        int slot = -1;
-#pragma unroll
-        for (int r = 0; r < S; ++r)
-            if (((mt >> r) & 1u) && other.a[r] == own.a[q]) slot = r;
-        if (slot < 0) continue;  // (every merged edge has its partner)
-        key[k] = (int)((t - z) * 8) + slot;
-        val[k] = w[widx<S>(slot, t, N)] * du;
+        if (k & 1) acc = __builtin_fmaf(edges.wo[k >> 1], part, acc);
+        const bool on = edges.slot[k] >= 0;
+        key[k] = on ? ((int)edges.t[k] - (int)z) * 8 + edges.slot[k] : kNone;
+        val[k] = edges.wp[k] * du;
     }
 #pragma unroll
     for (int round = 0; round < E; ++round)  // odd-even transposition by key
@@ -2666,26 +2661,47 @@ __global__ __launch_bounds__(256) void k_apply_K_ordered(
             val[i] = sw ? y : x;
             val[i + 1] = sw ? x : y;
         }
-    float in = 0.f;
-    int j = pos[z];
-    const int end = pos[z + 1];
-    int32_t e = 0;
-    float we = 0.f;
-    if (j < end) load_rec<float>(went, ent, j, true, e, we);
-    const auto until = [&](int bound) {  // the listed entries below a key
-#pragma clang fp contract(off)
-        while (j < end && (e >> 6) < bound) {
-            in += we * (uz - u[z + (e >> 9)]);
-            if (++j < end) load_rec<float>(went, ent, j, true, e, we);
-        }
-    };
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        until(key[k]);
-        if (key[k] != 0x7fffffff) in += val[k];
+        mkey[wave][k][lane] = key[k];
+        mval[wave][k][lane] = val[k];
     }
-    until(0x7fffffff);
-    out[z] = __builtin_fmaf(-h, in + acc, uz);
+    __builtin_amdgcn_wave_barrier();
+    float in = 0.f;
+    int m = 0, next = key[0];  // the first merged value not yet added, and its key
+    const auto merged_below = [&](int bound) {
+#pragma clang fp contract(off)
+        while (next < bound) {
+            in += mval[wave][m][lane];
+            next = ++m < E ? mkey[wave][m][lane] : kNone;
+        }
+    };
+    for (unsigned eb = 0; eb < L.total; eb += 64 * KP) {
+        int32_t v[KP];
+        float wv[KP];
+#pragma unroll
+        for (int j = 0; j < KP; ++j) {
+            const unsigned e = eb + 64 * j + lane;
+            load_rec<float>(went, ent, L.start + e, e < L.total, v[j], wv[j]);
+        }
+        InEdge<true, S, float, float, float> ie[KP];
+#pragma unroll
+        for (int j = 0; j < KP; ++j) ie[j].issue(L, z0, N, uz, v[j], wv[j], eb + 64 * j, u, w);
+#pragma unroll
+        for (int j = 0; j < KP; ++j) {
+            lkey[wave][64 * j + lane] = v[j] >> 6;
+            lval[wave][64 * j + lane] = ie[j].value();
+        }
+        __builtin_amdgcn_wave_barrier();
+        const unsigned end = eb + 64u * KP, hi = L.hi < end ? L.hi : end;
+        for (unsigned e = L.lo > eb ? L.lo : eb; e < hi; ++e) {
+            merged_below(lkey[wave][e - eb]);
+            in += lval[wave][e - eb];
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    merged_below(kNone);
+    if (live) out[z] = __builtin_fmaf(-h, in + acc, uz);
 }
 
 __global__ __launch_bounds__(kFinish) void k_sum_partials(const double *partial, long long nb,
@@ -3160,12 +3176,13 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
     }
 };
 
-// out = (I + dt A) u for the training loss.  The loss is an FP64 sum of FP32
-// rows; below 2^16 points their roundings do not average out of its ninth
-// digit, so those grids take every edge by itself, in the order of complete
-// lists (64 x 67: the loss differs by 1.8e-9 between the two).
+// out = (I + dt A) u for the training loss, an FP64 sum of FP32 rows in which
+// the rounding of pair sums shows: every edge by itself, in the order of
+// complete lists, so that a merged operator has the loss of one that is not
+// (with pair sums it moves by 1.8e-9 at 64 x 67, 1.6e-9 at 256^2, 4e-10 at
+// 1024^2).
 int apply_K_loss(const adlbr_operator *op, const void *u, void *out, double dt, hipStream_t s) {
-    if (op->merged && op->storage == ADLBR_F32 && op->gi.N < (1 << 16))
+    if (op->merged && op->storage == ADLBR_F32)
         return dispatch<OrderedF>(op, u, out, dt, s);
     return apply_K(op, u, out, dt, s);
 }
