@@ -415,7 +415,8 @@ __global__ __launch_bounds__(256) void k_stencil3d(const TD *__restrict__ D, lon
     for (int k = 0; k < 6; ++k) {
 #pragma unroll
         for (int c2 = 0; c2 < 3; ++c2) off[(3 * k + c2) * N + z] = (int16_t)cs[k][c2];
-        w[k * N + z] = (TW)g[k];
+        // the weights may take the tensor's place, which the 64-bit pass reads
+        if (red != -2) w[k * N + z] = (TW)g[k];
     }
     report(status, z, st);
 }
