@@ -255,7 +255,9 @@ int adlbr_batch_create(int nprob, adlbr_operator *const *ops, void *const *u,
  * arrays) stay within the budget, and each chunk takes all its steps before
  * the next one starts, so that it runs out of the 256 MB last-level cache
  * (with bit 3, two chunks share it); 0 keeps the class whole.  Every choice
- * computes the same bits.  Synchronizes `stream`. */
+ * computes the same bits.  Synchronizes `stream`, after the batch's last
+ * run, whatever stream that was given (one that the caller captured into a
+ * graph of its own must not be running, nor be replayed afterwards). */
 int adlbr_batch_tune(adlbr_batch *batch, int steps, int use_cache, void *stream);
 /* The tuner's cache on disk (a JSON file, so that one process's timings
  * serve later ones):
@@ -276,8 +278,8 @@ int adlbr_batch_tune_lookup(int class_key, int64_t points, int nprob, int *found
                             size_t *chunk_bytes);
 /* Force launch variant (0..15) and chunk budget (bytes, 0 = no chunks; a
  * problem larger than the budget gets a chunk of its own) for class cls
- * instead of tuning.  Synchronizes `stream`; ADLBR_E_INVALID for a bad
- * class or variant. */
+ * instead of tuning.  Synchronizes `stream`, after the batch's last run (as
+ * adlbr_batch_tune); ADLBR_E_INVALID for a bad class or variant. */
 int adlbr_batch_set_variant(adlbr_batch *batch, int cls, int variant, size_t chunk_bytes,
                             void *stream);
 /* Class cls (0-based, in order of first appearance): its class key

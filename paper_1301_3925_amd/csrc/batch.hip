@@ -46,7 +46,8 @@ struct adlbr_batch {
     std::vector<Class> classes;
     hipStream_t own;
     hipStream_t side;  // the second chain of two chunks in flight (variant bit 3)
-    hipEvent_t ev_in, ev_out;
+    hipEvent_t ev_in, ev_out;  // ev_out: the end of the last run
+    bool ran;                  // ev_out has been recorded
     std::vector<hipEvent_t> forks, joins;  // one pair per two-chunk group
     hipGraph_t graph;
     hipGraphExec_t exec;
@@ -202,6 +203,15 @@ int enqueue_steps(adlbr_batch *b, long long nsteps, hipStream_t s) {
     return ADLBR_OK;
 }
 
+// The last run reads the descriptors, and steps between u and u_tmp, on the
+// stream that it was given or on the batch's own: it is waited for before
+// either is touched on another.  (A run that the caller has captured into a
+// graph of its own is the caller's to order.)
+int wait_for_runs(adlbr_batch *b) {
+    if (b->ran) ADLBR_CHECK_HIP(hipEventSynchronize(b->ev_out));
+    return ADLBR_OK;
+}
+
 // A replay of the graph may still be running (the last call has returned): it
 // is waited for, since the runtime's nodes and branches go with the graph.
 void drop_graph(adlbr_batch *b) {
@@ -271,6 +281,7 @@ extern "C" int adlbr_batch_create(int nprob, adlbr_operator *const *ops, void *c
     b->graph = nullptr;
     b->exec = nullptr;
     b->graph_steps = -1;
+    b->ran = false;
     std::map<int, int> idx;
     for (int i = 0; i < nprob; ++i) {
         const int key = batch_class(ops[i]), kern = batch_kernels(ops[i]);
@@ -349,7 +360,8 @@ extern "C" int adlbr_batch_tune(adlbr_batch *b, int steps, int use_cache, void *
     EventPair ev;
     ADLBR_CHECK_HIP(ev.create());
     const hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
-    int rc = ADLBR_OK;
+    int rc = wait_for_runs(b);
+    if (rc) return rc;
     for (auto &c : b->classes) {
         const long long key = cache_key(c);
         if (use_cache) {
@@ -412,7 +424,9 @@ extern "C" int adlbr_batch_set_variant(adlbr_batch *b, int cls, int variant, siz
         set_error("adlbr_batch_set_variant: bad class or variant");
         return ADLBR_E_INVALID;
     }
-    int rc = upload(b->classes[cls], variant, chunk_bytes, as_stream(stream));
+    int rc = wait_for_runs(b);
+    if (rc) return rc;
+    rc = upload(b->classes[cls], variant, chunk_bytes, as_stream(stream));
     drop_graph(b);
     return rc;
 }
@@ -445,6 +459,12 @@ extern "C" int adlbr_batch_run(adlbr_batch *b, int64_t nsteps, int use_graph, vo
         int rc = enqueue_steps(b, nsteps, s);
         if (rc) return rc;
         ADLBR_LAUNCH_CHECK();
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        ADLBR_CHECK_HIP(hipStreamIsCapturing(s, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            ADLBR_CHECK_HIP(hipEventRecord(b->ev_out, s));
+            b->ran = true;
+        }
         return ADLBR_OK;
     }
     if (!b->exec || b->graph_steps != nsteps) {
@@ -474,6 +494,7 @@ extern "C" int adlbr_batch_run(adlbr_batch *b, int64_t nsteps, int use_graph, vo
     ADLBR_CHECK_HIP(hipStreamWaitEvent(b->own, b->ev_in, 0));
     ADLBR_CHECK_HIP(hipGraphLaunch(b->exec, b->own));
     ADLBR_CHECK_HIP(hipEventRecord(b->ev_out, b->own));
+    b->ran = true;
     ADLBR_CHECK_HIP(hipStreamWaitEvent(s, b->ev_out, 0));
     return ADLBR_OK;
 }
