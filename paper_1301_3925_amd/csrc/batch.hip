@@ -1,6 +1,6 @@
 // Batched explicit stepping of many operators of uneven sizes.
 //
-// Problems are grouped by class (dim, offset width, boundary, storage); one
+// Problems are grouped by class (layout, dim, offset width, boundary, storage); one
 // grouped launch advances every problem of a class by one step (blocks laid
 // out problem after problem, each block finds its problem by binary search
 // over a small device descriptor table).  The problems are independent, so
@@ -284,10 +284,10 @@ extern "C" int adlbr_batch_create(int nprob, adlbr_operator *const *ops, void *c
     b->ran = false;
     std::map<int, int> idx;
     for (int i = 0; i < nprob; ++i) {
-        const int key = batch_class(ops[i]), kern = batch_kernels(ops[i]);
-        auto it = idx.find(kern);
+        const int key = batch_class(ops[i]);
+        auto it = idx.find(key);
         if (it == idx.end()) {
-            it = idx.emplace(kern, (int)b->classes.size()).first;
+            it = idx.emplace(key, (int)b->classes.size()).first;
             adlbr_batch::Class c;
             c.key = key;
             c.rep = ops[i];

@@ -272,11 +272,9 @@ struct BatchProb {
 };
 // Blocks of one explicit step of op, and the points each covers.
 long long batch_blocks(const adlbr_operator *op, int *block_points);
-// Class of an operator for batching (dim, offset width, boundary, storage):
-// problems of one class share a kernel instance.
+// Class of an operator for batching (layout, dim, offset width, boundary,
+// storage): problems of one class share a kernel instance.
 int batch_class(const adlbr_operator *op);
-// What separates kernel instances: the class, and whether edges are merged.
-int batch_kernels(const adlbr_operator *op);
 // Fill the operator part of a descriptor.
 void batch_describe(const adlbr_operator *op, BatchProb *d);
 // Device bytes one explicit step of op reads or writes (u, its successor and

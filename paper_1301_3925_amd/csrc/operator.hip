@@ -3099,11 +3099,10 @@ int merged_flag(const GridInfo &g, int flags) {
 
 }  // namespace
 
-int batch_kernels(const adlbr_operator *op) { return 2 * batch_class(op) + op->merged; }
-
 int batch_class(const adlbr_operator *op) {
     const int rec2d = op->gi.dim == 2 && op->records ? 1 : 0;
-    return rec2d * 100000 + op->tiled * 10000 + op->gi.dim * 1000 + op->wide * 100 +
+    const int lay = op->tiled ? 1 : op->merged ? 2 : 0;
+    return rec2d * 100000 + lay * 10000 + op->gi.dim * 1000 + op->wide * 100 +
            op->gi.periodic * 10 + op->storage;
 }
 
