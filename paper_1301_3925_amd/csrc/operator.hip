@@ -69,7 +69,7 @@ struct adlbr_operator {
     uint32_t *bincnt;  // 3D: edges per bin of targets; 2D: cnt sums per 1024-point chunk
     uint32_t *bincur;  // 3D: placement cursor per bin
     uint32_t *binoff;  // 3D: exclusive scan of bincnt
-    int2 *binbuf;      // 3D: (target, entry) grouped by bin
+    int2 *binbuf;      // 3D: (target, entry) grouped by bin (F64, F32: in went's place)
 };
 
 namespace adlbr {
@@ -861,15 +861,19 @@ __global__ __launch_bounds__(kFillBS) void k_bin_fill(GridInfo g, const typename
 // ranks in registers.  ent is written back only where it is read later (not
 // with FP32's packed records).  Bound by the gathers of the entries' weights
 // and the sorts: 160^3 247 us (385 us with the rows placed in ent).
+// binbuf and went may be the same memory (8 bytes an entry in both), as may
+// dsum and diag: a block reads its own bin's part of the one before it writes
+// that part of the other, and a point's dsum is read by the thread that
+// writes its diag.
 constexpr int kStage = 6144;  // entries a bin holds in LDS (24 KB): twice a usual bin's
 template <int DIM, bool WIDE, bool PER, typename TS, typename TA, typename TD>
 __global__ __launch_bounds__(256) void k_bin_build(
     GridInfo g, const uint32_t *__restrict__ bincnt, const uint32_t *__restrict__ binoff,
-    const int2 *__restrict__ binbuf, const TS *__restrict__ w, const double *__restrict__ dsum,
+    const int2 *binbuf, const TS *__restrict__ w, const double *dsum,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const uint8_t *__restrict__ mask,
     const lmask_t<DIM> *__restrict__ lmask, int merged, int32_t *__restrict__ pos,
-    int32_t *__restrict__ ent, EntRec<TS> *__restrict__ went, TD *__restrict__ diag,
-    double *__restrict__ dpart, int32_t *status) {
+    int32_t *__restrict__ ent, EntRec<TS> *went, TD *diag, double *__restrict__ dpart,
+    int32_t *status) {
     constexpr int kKeep = 24;  // kStage / 256
     __shared__ int32_t lcnt[kBin];
     __shared__ int32_t loff[kBin];
@@ -954,6 +958,7 @@ __global__ __launch_bounds__(256) void k_bin_build(
             const int k = atomicAdd(&lcnt[tl], 1);
             if (k < 255) ent[base + loff[tl] + k] = v.y;
         }
+        __syncthreads();  // binbuf has been read
     }
     // Rows clamped at 255 entries (flagged above) leave the bin's region
     // [base + clamped total, base + E) unwritten, and the apply reads it as
@@ -1410,16 +1415,16 @@ __device__ inline double own_diag(const GridInfo &g, long long z,
 // the diagonal A_zz and the block's largest diagonal (dpart), one thread per
 // target.  The rows of a block's 256 consecutive targets are one run of ent;
 // when it fits, it is staged in LDS with coalesced loads around the
-// per-thread sort.  dsum: the own and merged weights (with MG).
+// per-thread sort.  dsum: the own and merged weights (with MG; may be diag).
 template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA, typename TD>
 __global__ __launch_bounds__(256) void k_rows(GridInfo g,
                                               const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
                                               const TS *__restrict__ w,
-                                              const double *__restrict__ dsum,
+                                              const double *dsum,
                                               const uint8_t *__restrict__ cnt,
                                               const int32_t *__restrict__ pos,
                                               int32_t *__restrict__ ent, EntRec<TS> *__restrict__ went,
-                                              TD *__restrict__ diag, double *__restrict__ dpart) {
+                                              TD *diag, double *__restrict__ dpart) {
     constexpr int kCap = 16 * 256;
     __shared__ int32_t rows[kCap];
     const long long N = g.N;
@@ -3080,7 +3085,9 @@ Layout layout(const GridInfo &g, int storage, int wide, int merged, int records)
     // without merging the listed edges of a 2D point replace its mask in place
     L.lmask = full ? o : L.mask;
     o += full ? align_up((g.dim == 2 ? 1 : 2) * (size_t)N) : 0;
-    L.dsum = o; o += full ? align_up(8 * (size_t)N) : 0;
+    // in FP64 the diagonal's first part is summed where the diagonal will be
+    L.dsum = storage == ADLBR_F64 ? L.diag : o;
+    o += full && storage != ADLBR_F64 ? align_up(8 * (size_t)N) : 0;
     // partials: one per 256-point block, per 3D bin or per tile of the
     // tiled layout
     const size_t ntiles = g.dim == 2 ? (size_t)((g.nx + kTile - 1) / kTile) * ((g.ny + kTile - 1) / kTile) : 0;
@@ -3100,7 +3107,11 @@ Layout layout(const GridInfo &g, int storage, int wide, int merged, int records)
     const bool bins = g.dim == 3;  // the 2D tile assembly needs no bins
     L.bincur = o; o += bins ? align_up(4 * nbins + 4) : 0;
     L.binoff = o; o += bins ? align_up(4 * nbins + 4) : 0;
-    L.binbuf = o; o += bins ? align_up(8 * (size_t)(2 * S) * N) : 0;
+    // the assembly's 8-byte edges, where the entries' weights of 8 bytes
+    // follow (k_bin_build)
+    const bool bins_apart = bins && dtype_size(storage) == 2;
+    L.binbuf = bins_apart ? o : L.went;
+    o += bins_apart ? align_up(8 * (size_t)(2 * S) * N) : 0;
     L.total = o;
     return L;
 }
