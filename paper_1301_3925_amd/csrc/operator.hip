@@ -1390,25 +1390,34 @@ __global__ __launch_bounds__(256) void k_place2d(GridInfo g,
                 (int32_t)(((z - tt[e]) << 9) | ((e >> 1) << 6) | (tt[e] & 63));
 }
 
-// Own part of A_zz: the row's weights over its edges in the grid.
-template <int DIM, bool WIDE, bool PER, typename TS, typename TA>
-__device__ inline double own_diag(const GridInfo &g, long long z,
-                                  const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
-                                  const TS *__restrict__ w) {
-    constexpr int S = DIM == 2 ? 3 : 6;
-    double d = 0.0;
+// Own part of A_zz: the row's weights over its edges in the grid.  Loaded and
+// summed apart, so that a row's other loads are requested in between.
+template <int DIM, bool WIDE, bool PER, typename TS, typename TA> struct OwnDiag {
+    static constexpr int S = DIM == 2 ? 3 : 6;
     Slots<DIM, WIDE> sl;
-    sl.load(sb, z);
-    const Coord p = coords(z, g);
-    for (int q = 0; q < S; ++q) {
-        const double wv = (double)Conv<TS, TA>::ld(w[widx<S>(q, z, g.N)]);
-        for (int sg = -1; sg <= 1; sg += 2) {
-            long long t;
-            if (edge_target<DIM, PER>(p, z, sl.o[q], sg, g, t)) d += wv;
-        }
+    TS wo[S];
+    __device__ __forceinline__ void load(const GridInfo &g, long long z,
+                                         const typename Slots<DIM, WIDE>::store_t *__restrict__ sb,
+                                         const TS *__restrict__ w) {
+        sl.load(sb, z);
+#pragma unroll
+        for (int q = 0; q < S; ++q) wo[q] = w[widx<S>(q, z, g.N)];
     }
-    return d;
-}
+    __device__ __forceinline__ double sum(const GridInfo &g, long long z) const {
+        double d = 0.0;
+        const Coord p = coords(z, g);
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const double wv = (double)Conv<TS, TA>::ld(wo[q]);
+#pragma unroll
+            for (int sg = -1; sg <= 1; sg += 2) {
+                long long t;
+                if (edge_target<DIM, PER>(p, z, sl.o[q], sg, g, t)) d += wv;
+            }
+        }
+        return d;
+    }
+};
 
 // Pass 3: sort every row, store the weight of each entry beside it (in went, if
 // given; with MG in FP32 the record holds both, and ent is not read again), take
@@ -1431,7 +1440,10 @@ __global__ __launch_bounds__(256) void k_rows(GridInfo g,
     const long long t0 = (long long)blockIdx.x * blockDim.x, t = t0 + threadIdx.x;
     const int p0 = pos[t0], p1 = pos[t0 + 256 < N ? t0 + 256 : N];
     const int c = t < N ? (int)cnt[t] : 0, p = t < N ? pos[t] : 0;  // requested with the staging
-    const double d0 = t >= N ? 0.0 : MG ? dsum[t] : own_diag<DIM, WIDE, PER, TS, TA>(g, t, sb, w);
+    OwnDiag<DIM, WIDE, PER, TS, TA> own;
+    double d0 = 0.0;
+    if constexpr (MG) d0 = t < N ? dsum[t] : 0.0;
+    else own.load(g, t < N ? t : 0, sb, w);
     EntRec<TS> *we = went ? went + p : nullptr;
     const bool staged = p1 - p0 <= kCap;  // block-uniform
     if (staged) {  // all of a thread's loads first, then its LDS stores
@@ -1453,6 +1465,7 @@ __global__ __launch_bounds__(256) void k_rows(GridInfo g,
     const int cw = wave_max_i(c);  // all lanes
     double dmax = 0.0;
     if (t < N) {
+        if constexpr (!MG) d0 = own.sum(g, t);
         // two calls, so that the staged one addresses LDS directly (not
         // through flat addressing)
         const double d = staged ? sort_row_diag<DIM, TS, TA>(g, t, rows + (p - p0), c, cw, d0, w, we)
