@@ -966,6 +966,12 @@ int net_apply_dots(const adlbr_net *net, const adlbr_operator *op, const float *
     return ADLBR_OK;
 }
 
+long long net_dot_parts(const GridInfo &g) {
+    const long long fused = g.dim == 2 ? (long long)net_mfma_blocks(g.nx, g.ny) : net3d_tiles(g);
+    const long long nb = nblk(g.N);
+    return fused > nb ? fused : nb;
+}
+
 }  // namespace adlbr
 
 using namespace adlbr;

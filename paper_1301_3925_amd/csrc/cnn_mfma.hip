@@ -789,8 +789,7 @@ int net_pack_mfma(const adlbr_net *net, hipStream_t s) {
 static int net3d_chunk(long long cols, int nz, long long blocks) {
     return (int)((cols * nz + blocks - 1) / blocks);
 }
-// The last kernel's: up to eight; 384 blocks and one more a column leave at
-// most the 768 partials that the solver always has room for.
+// The last kernel's: up to eight; 384 blocks and one more a column.
 static int net3d_out_chunk(const GridInfo &g) {
     const long long cols = (long long)((g.nx + k4X - 1) / k4X) * ((g.ny + k4Y - 1) / k4Y);
     return cols >= 384 ? 8 : std::min(8, net3d_chunk(cols, g.nz, 384));

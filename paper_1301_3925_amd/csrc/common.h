@@ -242,6 +242,8 @@ int net_apply(const adlbr_net *net, const adlbr_operator *op, double dt, const v
 int net_apply_dots(const adlbr_net *net, const adlbr_operator *op, const float *r,
                    const float *rp, float *z, double *part, long long *nparts,
                    const CgState *st, hipStream_t s);
+// The most that nparts can be on this grid, whatever the path.
+long long net_dot_parts(const GridInfo &g);
 
 // Rows per block of the explicit-step kernels: every wave of a 256-thread
 // block takes 64 consecutive rows.

@@ -258,17 +258,11 @@ template <typename TA, typename TB> __global__ void k_convert(long long N, const
     if (i < N) b[i] = (TB)a[i];
 }
 
-// Most dot partials the inference leaves: the 2D fused kernel's persistent
-// grid has at most 3 blocks per CU on 256 CUs; the 3D path leaves one per
-// 8 x 8 x 4 tile.
-constexpr size_t kDotParts = 768;
-
+// Room for the partials of one dot: the direction's, one per 256 points, the
+// update's, and what the inference leaves on this grid.
 size_t dot_parts(const GridInfo &g) {
     const size_t nb = (size_t)((g.N + kBS - 1) / kBS);
-    size_t m = std::max(nb, kDotParts);
-    if (g.dim == 3)
-        m = std::max(m, (size_t)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * ((g.nz + 3) / 4));
-    return m;
+    return std::max(std::max(nb, (size_t)kUpdBlocks), (size_t)net_dot_parts(g));
 }
 
 // Blocks of the update: one per CU from 1024 points a block, then two once
@@ -318,7 +312,6 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
     double *prr = part + 2 * (long long)dot_parts(g);
     // those of <z, r> of the Jacobi-PCG update, out of the direction's way
     double *prz = part + (long long)dot_parts(g);
-    static_assert(kUpdBlocks <= kDotParts, "in the second region");
     T *r = (T *)(ws + L.vec[0]);
     T *r2 = (T *)(ws + L.vec[1]);
     T *z = (T *)(ws + L.vec[2]);
