@@ -48,3 +48,28 @@ def test_settings_change_behind_a_run(change, graph):
     for got, ref in zip(seen, refs):
         for u, r in zip(got, ref):
             assert torch.equal(u, r)
+
+
+@pytest.mark.parametrize("variant,chunk", [(1, 0), (9, 1)])
+def test_direct_run_in_the_callers_graph(variant, chunk):
+    """A direct run captured by the caller steps at every replay; direct runs
+    and changes of the settings before and after it are ordered as ever."""
+    import torch
+    b, us, refs = _batch(7, 5)
+    b.set_variant(0, variant, chunk)
+    s = torch.cuda.Stream()
+    b.run(7, graph=False, stream=s)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        b.run(7, graph=False)
+    for ref in refs[1:4]:
+        g.replay()
+        torch.cuda.synchronize()
+        for u, r in zip(us, ref):
+            assert torch.equal(u, r)
+    b.set_variant(0, 3, 0)
+    b.run(7, graph=False)
+    torch.cuda.synchronize()
+    for u, r in zip(us, refs[4]):
+        assert torch.equal(u, r)
