@@ -357,40 +357,69 @@ __device__ inline void block_partial_max(double v, double *partial) {
     __syncthreads();
 }
 
-// Sum (or max, when take_max) of partial[0 .. n) by a single block of
-// kFinish threads in a fixed order; every thread gets the result.  One block
-// runs at the latency of its loads: kFinish threads with eight loads in
-// flight each take 8192 partials (2 M points) in one round trip.
+// Sums (or maxima, when take_max) of K arrays partial[k][0 .. n[k]) by a single
+// block of BS threads in a fixed order; every thread gets the results.  One
+// block runs at the latency of its loads: kFinish threads with eight loads in
+// flight each take 8192 partials (2 M points) in one round trip, and the K
+// arrays' first ones are requested together.
 constexpr int kFinish = 1024;
-__device__ inline double reduce_partials(const double *partial, long long n, bool take_max = false) {
-    __shared__ double red[kFinish / 64];
+template <int K, int BS = kFinish>
+__device__ inline void reduce_partials(const double *const (&partial)[K], const long long (&n)[K],
+                                       double (&out)[K], bool take_max = false) {
+    __shared__ double red[K][BS / 64];
     const double none = take_max ? -1.0e308 : 0.0;
-    double acc = none;
-    for (long long b0 = threadIdx.x; b0 - threadIdx.x < n; b0 += 8 * kFinish) {
-        double v[8];
+    double acc[K], v[K][8];
+    const auto load = [&](int k, long long b0) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const long long b = b0 + kFinish * j;
-            v[j] = partial[b < n ? b : 0];
+            const long long b = b0 + BS * j;
+            v[k][j] = partial[k][b < n[k] ? b : 0];
         }
+    };
+    const auto add = [&](int k, long long b0) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const double w = b0 + kFinish * j < n ? v[j] : none;
-            acc = take_max ? fmax(acc, w) : acc + w;
+            const double w = b0 + BS * j < n[k] ? v[k][j] : none;
+            acc[k] = take_max ? fmax(acc[k], w) : acc[k] + w;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < K; ++k) load(k, threadIdx.x);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        acc[k] = none;
+        add(k, threadIdx.x);
+        for (long long b0 = threadIdx.x + 8 * BS; b0 - threadIdx.x < n[k]; b0 += 8 * BS) {
+            load(k, b0);
+            add(k, b0);
         }
     }
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const double o = __shfl_xor(acc, d, 64);
-        acc = take_max ? fmax(acc, o) : acc + o;
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const double o = __shfl_xor(acc[k], d, 64);
+            acc[k] = take_max ? fmax(acc[k], o) : acc[k] + o;
+        }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = acc[k];
     __syncthreads();
-    double t = red[0];
 #pragma unroll
-    for (int j = 1; j < kFinish / 64; ++j) t = take_max ? fmax(t, red[j]) : t + red[j];
+    for (int k = 0; k < K; ++k) {
+        double t = red[k][0];
+#pragma unroll
+        for (int j = 1; j < BS / 64; ++j) t = take_max ? fmax(t, red[k][j]) : t + red[k][j];
+        out[k] = t;
+    }
     __syncthreads();  // red[] may be reused by a second call
-    return t;
+}
+__device__ inline double reduce_partials(const double *partial, long long n, bool take_max = false) {
+    const double *const p[1] = {partial};
+    const long long m[1] = {n};
+    double t[1];
+    reduce_partials<1>(p, m, t, take_max);
+    return t[0];
 }
 
 const GridInfo &operator_grid(const adlbr_operator *op);

@@ -96,6 +96,7 @@ __global__ __launch_bounds__(kFinish, 8) void k_update(long long N, double *__re
                                                     const double *__restrict__ dpart, long long nd,
                                                     double *__restrict__ prz, double *__restrict__ prr) {
     constexpr int U = sizeof(T) == 8 ? kUpd / 2 : kUpd;  // 64 registers: two blocks a CU
+    const double rz_old = st->rz[slot], dt = st->dt;  // requested with the flags
     if (st->done || st->bad) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->halt = 1;
         return;
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(kFinish, 8) void k_update(long long N, double *__re
     const double pq = reduce_partials(dpart, nd);
     if (blockIdx.x == 0 && threadIdx.x == 0) st->pq = pq;
     if (cg_breakdown(pq)) return;
-    const double al = st->rz[slot] / pq, dt = st->dt;
+    const double al = rz_old / pq;
     const T a = (T)al;
     double rz = 0.0, rr = 0.0;
     for (;;) {
@@ -177,18 +178,25 @@ __global__ __launch_bounds__(kFinish) void k_breakdown(CgState *st, const double
 // |r|^2 from its partials prr (iteration count, history, breakdown and
 // convergence flags); then, from the dot partials part (nparts each),
 // beta = (<z, r> - <z, r_prev>) / <z_prev, r_prev> (first: beta = 0).
-__global__ __launch_bounds__(kFinish) void k_fcg_scalars(SolveState *st, const double *part,
+__global__ __launch_bounds__(kBS) void k_fcg_scalars(SolveState *st, const double *part,
                                                      long long nparts, const double *prr,
                                                      long long nb, double *hist, int max_hist,
                                                      int first) {
-    if (cg_stopped(&st->cg)) {
-        if (threadIdx.x == 0 && !st->cg.done) st->cg.bad = 1;
+    // the three sums in one round trip, in a finished batch too; the update and
+    // the fused inference leave at most 768 partials in 2D, a few thousand in
+    // 3D, for which 256 threads start sooner than 1024: 4.0 us at 64^2 (5.6 with
+    // 1024, 6.4 with these one after the other behind the flags)
+    const double *const p[3] = {first ? part : prr, part, part + nparts};
+    const long long np[3] = {first ? 0 : nb, nparts, nparts};
+    double t[3];
+    const bool stop = cg_stopped(&st->cg), done = st->cg.done;
+    reduce_partials<3, kBS>(p, np, t);
+    const double rr = t[0], zr = t[1], zrp = t[2];
+    if (threadIdx.x != 0) return;
+    if (stop) {
+        if (!done) st->cg.bad = 1;
         return;
     }
-    const double rr = first ? 0.0 : reduce_partials(prr, nb);
-    const double zr = reduce_partials(part, nparts);
-    const double zrp = reduce_partials(part + nparts, nparts);
-    if (threadIdx.x != 0) return;
     if (!first) {
         st->cg.rr = rr;
         const int it = st->cg.iter + 1;
@@ -352,7 +360,7 @@ int solve_impl(adlbr_operator *op, double dt, const T *b, T *x, const adlbr_solv
                                    first ? nullptr : (const float *)ro, (float *)z, part, &np, cg,
                                    s);
             if (e) return e;
-            hipLaunchKernelGGL(k_fcg_scalars, dim3(1), dim3(kFinish), 0, s, st, (const double *)part,
+            hipLaunchKernelGGL(k_fcg_scalars, dim3(1), dim3(kBS), 0, s, st, (const double *)part,
                                np, (const double *)prr, (long long)nbu, hist, kMaxHist, first);
         }
         const CgTail tail = {use_net || first ? nullptr : prz, prr, (int)nbu, slot, hist,
