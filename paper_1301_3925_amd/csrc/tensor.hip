@@ -58,69 +58,88 @@ __device__ __forceinline__ int mirror(int i, int n) {
     return i < n ? i : p - 1 - i;
 }
 
-// The kBO consecutive outputs along an axis from position p0 of one line (src:
-// its first value, `stride` apart, len values, mirrored past its ends): the
-// line's values are read once, not once per output, and every output sums its
-// taps in the order j = 0 .. 2 r.
-constexpr int kBO = 4;
-template <typename T>
+// BO consecutive outputs along an axis from position p0 of one line (src: its
+// first value, `stride` apart, len values, mirrored past its ends): the line's
+// values are read once, not once per output, and every output sums its taps in
+// the order j = 0 .. 2 r.
+template <typename T, int BO>
 __device__ __forceinline__ void blur_line(const T *__restrict__ src, long long stride, int p0, int len,
-                                          const Taps &t, T (&acc)[kBO]) {
+                                          const Taps &t, T (&acc)[BO]) {
 #pragma unroll
-    for (int o = 0; o < kBO; ++o) acc[o] = (T)0;
-    const int n = 2 * t.r + kBO;  // values p0 - r .. p0 + r + kBO - 1
-    const bool inside = p0 - t.r >= 0 && p0 + t.r + kBO - 1 < len;
-    constexpr int B = 8;
+    for (int o = 0; o < BO; ++o) acc[o] = (T)0;
+    const int n = 2 * t.r + BO;  // values p0 - r .. p0 + r + BO - 1
+    // the position in the line's even extension, of period 2 len, one on from
+    // load to load: a division a line, not one a value
+    const int period = 2 * len;
+    int q = (p0 - t.r) % period;
+    q += q < 0 ? period : 0;
+    constexpr int B = BO == 1 ? 16 : 8;
     for (int k0 = 0; k0 < n; k0 += B) {  // uniform; B loads in flight
         T v[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            const int p = p0 - t.r + min(k0 + b, n - 1);
-            v[b] = src[(long long)(inside ? p : mirror(p, len)) * stride];
+            v[b] = src[(long long)(q < len ? q : period - 1 - q) * stride];
+            const int next = q + 1 < period ? q + 1 : 0;
+            q = k0 + b + 1 < n ? next : q;
         }
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
-            for (int o = 0; o < kBO; ++o) {
+            for (int o = 0; o < BO; ++o) {
                 const int j = k0 + b - o;  // uniform
                 if (j >= 0 && j <= 2 * t.r) acc[o] += tap<T>(t, j) * v[b];
             }
     }
 }
 
-// Blur planes along axis AX, kBO consecutive outputs of a line per thread;
+// Outputs of a line per thread: four where the grid fills the card even so,
+// one on small grids, whose passes run at the latency of a thread's loads; the
+// sums are the same.  A tensor with one and with four, sigma 1 and rho 4 in
+// FP32: 16^3 31 and 73 us, 40^3 45 and 79, 64^3 94 and 96, 80^3 156 and 124;
+// FP64 in 2D: 256^2 26 and 31 us, 512^2 56 and 45.
+constexpr int kBO = 4;
+constexpr long long kSmallGrid = 200000;
+
+// Blur planes along axis AX, BO consecutive outputs of a line per thread;
 // blockIdx.y selects the plane.  Threads run along x, then y, then z of the
-// grid shortened kBO-fold along AX.
-template <typename T, int AX>
+// grid shortened BO-fold along AX.
+template <typename T, int AX, int BO>
 __global__ __launch_bounds__(256) void k_blur(GridInfo g, const T *__restrict__ in,
                                               T *__restrict__ out, Taps t) {
-    const unsigned cx = AX == 0 ? (unsigned)(g.nx + kBO - 1) / kBO : (unsigned)g.nx;
-    const unsigned cy = AX == 1 ? (unsigned)(g.ny + kBO - 1) / kBO : (unsigned)g.ny;
-    const unsigned cz = AX == 2 ? (unsigned)(g.nz + kBO - 1) / kBO : (unsigned)g.nz;
+    const unsigned cx = AX == 0 ? (unsigned)(g.nx + BO - 1) / BO : (unsigned)g.nx;
+    const unsigned cy = AX == 1 ? (unsigned)(g.ny + BO - 1) / BO : (unsigned)g.ny;
+    const unsigned cz = AX == 2 ? (unsigned)(g.nz + BO - 1) / BO : (unsigned)g.nz;
     const unsigned i = blockIdx.x * 256u + threadIdx.x;  // N < 2^28
     const unsigned r = i / cx, x0 = i - r * cx, z0 = r / cy, y0 = r - z0 * cy;
     if (z0 >= cz) return;
-    const int x = (int)x0 * (AX == 0 ? kBO : 1), y = (int)y0 * (AX == 1 ? kBO : 1);
-    const int z = (int)z0 * (AX == 2 ? kBO : 1);
+    const int x = (int)x0 * (AX == 0 ? BO : 1), y = (int)y0 * (AX == 1 ? BO : 1);
+    const int z = (int)z0 * (AX == 2 ? BO : 1);
     const int p0 = AX == 0 ? x : AX == 1 ? y : z, len = AX == 0 ? g.nx : AX == 1 ? g.ny : g.nz;
     const long long stride = AX == 0 ? 1 : AX == 1 ? g.nx : (long long)g.nx * g.ny;
     const long long at = (long long)blockIdx.y * g.N + x + (long long)g.nx * (y + (long long)g.ny * z);
-    T acc[kBO];
-    blur_line<T>(in + at - p0 * stride, stride, p0, len, t, acc);
+    T acc[BO];
+    blur_line<T, BO>(in + at - p0 * stride, stride, p0, len, t, acc);
 #pragma unroll
-    for (int o = 0; o < kBO; ++o)
+    for (int o = 0; o < BO; ++o)
         if (p0 + o < len) out[at + o * stride] = acc[o];
+}
+
+template <typename T, int BO>
+void launch_blur_of(const GridInfo &g, int planes, const T *in, T *out, int ax, const Taps &t,
+                    hipStream_t s) {
+    const auto cut = [&](int n, int a) { return (long long)(a == ax ? (n + BO - 1) / BO : n); };
+    const long long n = cut(g.nx, 0) * cut(g.ny, 1) * cut(g.nz, 2);
+    const dim3 grid((unsigned)((n + 255) / 256), planes);
+    if (ax == 0) hipLaunchKernelGGL((k_blur<T, 0, BO>), grid, dim3(256), 0, s, g, in, out, t);
+    else if (ax == 1) hipLaunchKernelGGL((k_blur<T, 1, BO>), grid, dim3(256), 0, s, g, in, out, t);
+    else hipLaunchKernelGGL((k_blur<T, 2, BO>), grid, dim3(256), 0, s, g, in, out, t);
 }
 
 template <typename T>
 void launch_blur(const GridInfo &g, int planes, const T *in, T *out, int ax, const Taps &t,
                  hipStream_t s) {
-    const auto cut = [&](int n, int a) { return (long long)(a == ax ? (n + kBO - 1) / kBO : n); };
-    const long long n = cut(g.nx, 0) * cut(g.ny, 1) * cut(g.nz, 2);
-    const dim3 grid((unsigned)((n + 255) / 256), planes);
-    if (ax == 0) hipLaunchKernelGGL((k_blur<T, 0>), grid, dim3(256), 0, s, g, in, out, t);
-    else if (ax == 1) hipLaunchKernelGGL((k_blur<T, 1>), grid, dim3(256), 0, s, g, in, out, t);
-    else hipLaunchKernelGGL((k_blur<T, 2>), grid, dim3(256), 0, s, g, in, out, t);
+    if (g.N < kSmallGrid) launch_blur_of<T, 1>(g, planes, in, out, ax, t, s);
+    else launch_blur_of<T, kBO>(g, planes, in, out, ax, t, s);
 }
 
 // grad u_sigma by central differences (mirror boundary), outer products.
@@ -281,6 +300,20 @@ __device__ __forceinline__ void eigmap3(const T J[6], T D[6], T alpha, T C, int 
     }
 }
 
+// The eigen map alone, of a J blurred along z by k_blur (small grids).
+template <typename T>
+__global__ __launch_bounds__(256) void k_eigmap3(long long N, const T *__restrict__ J,
+                                                 T *__restrict__ D, T alpha, T C, int map) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= N) return;
+    T j[6], d[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) j[c] = J[c * N + i];
+    eigmap3<T>(j, d, alpha, C, map);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) D[c * N + i] = d[c];
+}
+
 // The last blur of J (along z) with the eigen map behind it: kBO points of a
 // column per thread, so that the blurred J does not cross HBM.  100^3, radius
 // 6: the blurs and the map of a tensor took 244 + 64 us as passes of one
@@ -295,7 +328,7 @@ __global__ __launch_bounds__(256) void k_blur_eigmap3(GridInfo g, const T *__res
     if (z >= g.nz) return;
     T v[6][kBO];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) blur_line<T>(J + c * g.N + xy, plane, z, g.nz, t, v[c]);
+    for (int c = 0; c < 6; ++c) blur_line<T, kBO>(J + c * g.N + xy, plane, z, g.nz, t, v[c]);
 #pragma unroll
     for (int o = 0; o < kBO; ++o) {
         if (z + o >= g.nz) break;
@@ -566,9 +599,15 @@ int run_tensor(const GridInfo &g, const T *u, int ncomp, const adlbr_tensor_para
         }
         launch_blur<T>(g, nj, wb, wa, 0, tr, s);
         launch_blur<T>(g, nj, wa, wb, 1, tr, s);
-        const long long nc = (long long)((g.nz + kBO - 1) / kBO) * g.nx * g.ny;
-        hipLaunchKernelGGL(k_blur_eigmap3<T>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, g,
-                           (const T *)wb, D, tr, (T)p->alpha, (T)p->C, p->eig_map);
+        if (N < kSmallGrid) {
+            launch_blur<T>(g, nj, wb, wa, 2, tr, s);
+            hipLaunchKernelGGL(k_eigmap3<T>, dim3(nb), dim3(256), 0, s, N, (const T *)wa, D,
+                               (T)p->alpha, (T)p->C, p->eig_map);
+        } else {
+            const long long nc = (long long)((g.nz + kBO - 1) / kBO) * g.nx * g.ny;
+            hipLaunchKernelGGL(k_blur_eigmap3<T>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, g,
+                               (const T *)wb, D, tr, (T)p->alpha, (T)p->C, p->eig_map);
+        }
     }
     ADLBR_LAUNCH_CHECK();
     return ADLBR_OK;
