@@ -176,8 +176,10 @@ int adlbr_build_stencils(const adlbr_grid *g, const void *D, int D_dtype,
  * FP32 from both for 16-bit storage), and only the unpaired edges are listed,
  * each with its weight.  Every apply, step and solve reads about half the
  * neighbours; the workspace grows by the edge weights and records (2D F32:
- * from about 56 to 136 bytes a point).  Results agree with those without the flag
- * to rounding.  With ADLBR_OP_TILED: ADLBR_E_UNSUPPORTED. */
+ * from about 56 to 131 bytes a point, F64 from 72 to 163; 3D: 246 and 314).
+ * Results agree with those without the flag to rounding; the true residual of
+ * adlbr_solve and the loss of adlbr_net_loss_grad take every weight by itself.
+ * With ADLBR_OP_TILED: ADLBR_E_UNSUPPORTED. */
 #define ADLBR_OP_MERGED 8
 
 int adlbr_operator_workspace(const adlbr_grid *g, int storage, int flags,
@@ -299,7 +301,9 @@ int adlbr_batch_variant(const adlbr_batch *batch, int cls, int *key, int *varian
                         int *nchunks, size_t *chunk_bytes);
 /* nsteps explicit steps of every problem; use_graph = 0 launches directly
  * on `stream` instead of through the captured graph.  The results land in
- * u (an odd nsteps ends with a grouped copy). */
+ * u (an odd nsteps ends with a grouped copy).  A run with another nsteps than
+ * the last captured one captures anew, after the host has waited for the
+ * batch's last replay to end. */
 int adlbr_batch_run(adlbr_batch *batch, int64_t nsteps, int use_graph, void *stream);
 int adlbr_batch_destroy(adlbr_batch *batch);
 
@@ -412,7 +416,7 @@ int adlbr_structure_tensor_noalloc(const adlbr_grid *g, const void *u, int dtype
  *   layers   [2W(W+1)T + 7168] FP32  weights of the four-layer stack, [W1,
  *                              W2, flip(W2)^T, flip(W1)^T], then the BF16
  *                              MFMA operands packed per lane (2D: all four
- *                              layers; 3D: the two W -> W layers)
+ *                              layers; 3D: all but the first)
  *                              (adlbr_net_gates)
  * adlbr_net_gates must run again after params change.
  * ------------------------------------------------------------------ */

@@ -11,8 +11,8 @@
 // incoming edges are listed once per operator (count -> scan -> fill ->
 // per-row sort), so every apply is a deterministic gather with no atomics.
 // 2D grids are assembled by target tiles that gather their edges from a window
-// of sources (LDS atomics only); 3D grids by bins of targets (wave-aggregated
-// LDS atomics, then one block per bin).
+// of sources (LDS atomics only); 3D grids by bins of targets (LDS atomics, one
+// global atomic per bin and block, then one block per bin).
 //
 // Data layout in the workspace (N points, S = 3 or 6 slots):
 //   sb     compact slots: 2D (o0, o1) as 4 x int8 (or int16), o2 = -o0-o1;
@@ -1672,10 +1672,12 @@ template <typename Edges, typename TA, typename TU> struct OwnPart {
 
 // The own part of a merged FP32 row with every weight as it was given: the
 // own one and, where the edge is merged, its partner's, found again among the
-// target's slots (the stored sum of the two has been rounded to FP32).  For
+// target's slots (the stored sum of the two has been rounded to FP32, which
+// moves a residual by up to some 1e-8 of |b|).  For
 // results that must be those of the given weights: the FP64 residual that
-// decides a solve's convergence, and the training loss.  The edges are OwnEdges', the
-// lookup k_merge's, at about the cost of both.
+// decides a solve's convergence, and the training loss.  The edges are
+// OwnEdges', the lookup k_merge's, at about the cost of both: a solve's residual
+// takes 29 us more at 1024^2, 130 us at 128^3.
 template <int DIM, bool WIDE, bool PER> struct PairEdges {
     static constexpr int S = DIM == 2 ? 3 : 6, E = 2 * S;
     static constexpr bool kSlots = false;
@@ -2458,8 +2460,7 @@ __global__ __launch_bounds__(256) void k_reach_wmax(GridInfo g,
     block_partial_max(wm, wpart);
 }
 
-// hnear = min(hmax, reach) (0 for the list layout: every edge is listed)
-// and the largest weight.
+// hnear = min(hmax, reach) and the largest weight (tiled layout).
 __global__ __launch_bounds__(kFinish) void k_tile_params(const double *rpart, const double *wpart,
                                                      long long nb, int hmax, int32_t *hnear,
                                                      double *wmax) {

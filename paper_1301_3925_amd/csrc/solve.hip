@@ -274,8 +274,13 @@ size_t dot_parts(const GridInfo &g) {
 }
 
 // Blocks of the update: one per CU from 1024 points a block, then two once
-// each has a whole step of its threads (1024^2: 11.1 us with one per CU, 13.1
-// with two; 128^3: 17.1 and 15.9).
+// each has 4096 points, a whole step of its threads in FP32 and two in FP64
+// (1024^2: 11.1 us with one per CU, 13.1 with two; 128^3: 17.1 and 15.9).
+// Every block sums the direction's partials, one round trip up to 2 M points,
+// eight at 16 M.  32 iterations with a one-block kernel for each sum and this
+// way: 1024^2 FP64 2.13 and 1.50 ms, 2048^2 FP32 5.74 and 3.83, FP64 8.20 and
+// 5.65, 4096^2 FP32 21.4 and 14.1, 256^3 FP32 38.7 and 22.7, 192^3 FP64 23.4
+// and 15.5 (with the merged pairs' share).
 unsigned update_blocks(long long N) {
     const long long a = (N + kFinish - 1) / kFinish, b = (N + kUpd * kFinish - 1) / (kUpd * kFinish);
     return (unsigned)std::max(std::min<long long>(a, kUpdBlocks / 2), std::min<long long>(b, kUpdBlocks));
