@@ -160,15 +160,9 @@ int adlbr_build_stencils(const adlbr_grid *g, const void *D, int D_dtype,
 #define ADLBR_OP_TILED 2
 /* Records (list layout; 2D, since 3D operators always keep them): every
  * incoming entry is also stored with its edge's weight (8 bytes per edge
- * for F32 storage, entry and weight side by side), and a batch of such 2D
- * operators reads the weight from there instead of gathering it from the
- * source's weights; the assembly writes the extra records per rebuild and
- * the workspace grows by them.  Single-operator calls (apply, step, solve)
- * read what they read without the flag, and results are bit-identical
- * either way.  Operators with and without records fall in different batch
- * classes.  Beside ADLBR_OP_MERGED, which keeps such records for its unpaired
- * edges, the flag changes nothing but the class.
- * With ADLBR_OP_TILED: ADLBR_E_UNSUPPORTED. */
+ * for F32 storage, entry and weight side by side).  Implies ADLBR_OP_MERGED,
+ * whose results it shares bit for bit.  Operators with and without records
+ * fall in different batch classes.  With ADLBR_OP_TILED: ADLBR_E_UNSUPPORTED. */
 #define ADLBR_OP_RECORDS 4
 /* Merged pairs (list layout; 2D, since 3D operators always merge): where the
  * edge (z, o) and the edge (z + o, -o) both exist, row z keeps one edge with

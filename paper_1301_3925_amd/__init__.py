@@ -113,9 +113,9 @@ class Operator:
     F32/BF16/F16 storage; not for solve).  Every other operator merges
     pairs of opposite edges (ADLBR_OP_MERGED) and keeps each remaining
     incoming entry with its weight, unless a 2D workspace of the caller's
-    only holds the plain layout.  records=True (ADLBR_OP_RECORDS) gives 2D
-    operators a class of their own in a Batch, and those in a workspace of
-    the plain layout with records their entries' weights too.
+    only holds the plain layout.  records=True (ADLBR_OP_RECORDS) asks for
+    that layout explicitly; a Batch gives such 2D operators a class of
+    their own.
 
     Holds its device workspace (a torch uint8 tensor) for its lifetime.
     With check=True (the default) the constructor synchronizes and raises

@@ -28,8 +28,7 @@
 //   went   every listed entry's weight (FP32: entry and weight in one record).
 //   diag   [N] A_zz (double for FP64 storage, float otherwise).
 // 2D operators created without the memory for it (no ADLBR_OP_MERGED) list
-// every edge, read their own weights from w and gather the listed ones there;
-// with ADLBR_OP_RECORDS they have went too, which a batch reads instead.
+// every edge, read their own weights from w and gather the listed ones there.
 #include <algorithm>
 #include <cstddef>
 #include <type_traits>
@@ -43,7 +42,7 @@ struct adlbr_operator {
     int storage;  // adlbr_dtype
     int wide;     // int16 compact offsets
     int tiled;    // tiled layout: near edges from LDS tiles, far edges listed
-    int records;  // 2D: weights beside the entries (ADLBR_OP_RECORDS; a batch class of its own)
+    int records;  // 2D: asked for with ADLBR_OP_RECORDS (a batch class of its own)
     int merged;   // pairs of opposite edges merged (lists in 3D; 2D on request)
     void *sb;
     void *w;
@@ -51,7 +50,7 @@ struct adlbr_operator {
     uint8_t *cnt;      // 2D: listed edges of every target
     int32_t *pos;
     int32_t *ent;
-    void *went;        // merged, 3D, records: [entries] every incoming entry's weight (EntRec)
+    void *went;        // merged, 3D: [entries] the weight of every incoming entry (EntRec)
     void *diag;
     double *maxdiag;
     double *dtcfl;
@@ -1419,8 +1418,8 @@ template <int DIM, bool WIDE, bool PER, typename TS, typename TA> struct OwnDiag
     }
 };
 
-// Pass 3: sort every row, store the weight of each entry beside it (in went, if
-// given; with MG in FP32 the record holds both, and ent is not read again), take
+// Pass 3: sort every row, store the weight of each entry beside it (went,
+// with MG; in FP32 the record holds both, and ent is not read again), take
 // the diagonal A_zz and the block's largest diagonal (dpart), one thread per
 // target.  The rows of a block's 256 consecutive targets are one run of ent;
 // when it fits, it is staged in LDS with coalesced loads around the
@@ -1444,7 +1443,7 @@ __global__ __launch_bounds__(256) void k_rows(GridInfo g,
     double d0 = 0.0;
     if constexpr (MG) d0 = t < N ? dsum[t] : 0.0;
     else own.load(g, t < N ? t : 0, sb, w);
-    EntRec<TS> *we = went ? went + p : nullptr;
+    EntRec<TS> *we = MG ? went + p : nullptr;
     const bool staged = p1 - p0 <= kCap;  // block-uniform
     if (staged) {  // all of a thread's loads first, then its LDS stores
         const int n = p1 - p0;
@@ -1876,10 +1875,9 @@ __device__ __forceinline__ TA wave_incoming(const WaveLists &L, long long z0, lo
 
 // One block of out = A u (STEP = false) or u - h A u (STEP = true): every
 // wave takes 64 consecutive rows.  blk is the block's index within its grid.
-// REC: the entries' weights are read beside them.
 // Shared by the single-operator and the batched kernels, so both give
 // bit-identical results.
-template <int DIM, bool WIDE, bool PER, bool MG, bool REC, bool STEP, typename TS, typename TA>
+template <int DIM, bool WIDE, bool PER, bool MG, bool STEP, typename TS, typename TA>
 __device__ __forceinline__ void apply_block(
     const GridInfo &g, long long blk, const TS *__restrict__ u, TS *__restrict__ out,
     const typename Slots<DIM, WIDE>::store_t *__restrict__ sb, const void *__restrict__ wp,
@@ -1893,8 +1891,8 @@ __device__ __forceinline__ void apply_block(
     const TA uz = live ? Conv<TS, TA>::ld(u[z]) : (TA)0;
     OwnPart<decltype(edges), TA, TS> own;
     own.issue(edges, u);
-    const TA in = wave_incoming<REC, DIM == 2 ? 3 : 6, TS, TA, TS>(L, z0, g.N, uz, u, (const TS *)wp,
-                                                                  ent, went);
+    const TA in = wave_incoming<MG, DIM == 2 ? 3 : 6, TS, TA, TS>(L, z0, g.N, uz, u, (const TS *)wp,
+                                                                 ent, went);
     if (!live) return;
     const TA a = in + own.sum(edges, uz);
     out[z] = Conv<TS, TA>::st(STEP ? uz - h * a : a);
@@ -1908,7 +1906,7 @@ __global__ __launch_bounds__(kBS) void k_apply(
     const EntRec<TS> *__restrict__ went, double dt, const double *__restrict__ dtcfl,
     int dt_mode) {
     const TA h = (TA)(dt_mode == ADLBR_DT_CFL ? dt * dtcfl[0] : dt);
-    apply_block<DIM, WIDE, PER, MG, MG, STEP, TS, TA>(
+    apply_block<DIM, WIDE, PER, MG, STEP, TS, TA>(
         g, strip_block(xcd_block(blockIdx.x, gridDim.x), g, kApplyPoints), u, out, sb, wp, pos,
         ent, went, h);
 }
@@ -2004,14 +2002,14 @@ __device__ __forceinline__ int find_prob(const BatchProb *__restrict__ probs, in
 // a block finds its problem (find_prob), then runs the single-operator block
 // body.  XCD: remap block indices so that each XCD takes a contiguous range
 // (neighbouring blocks share its L2).
-template <int DIM, bool WIDE, bool PER, bool MG, bool REC, typename TS, typename TA, bool XCD>
+template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA, bool XCD>
 __global__ __launch_bounds__(kBS) void k_apply_batch(const BatchProb *__restrict__ probs, int nprob,
                                                      int parity) {
     const long long b = XCD ? xcd_block(blockIdx.x, gridDim.x) : (long long)blockIdx.x;
     const BatchProb &P = probs[find_prob(probs, nprob, b)];
     const GridInfo g = P.g;
     const TA h = (TA)(P.dt_mode == ADLBR_DT_CFL ? P.dt * P.dtcfl[0] : P.dt);
-    apply_block<DIM, WIDE, PER, MG, REC, true, TS, TA>(
+    apply_block<DIM, WIDE, PER, MG, true, TS, TA>(
         g, strip_block(b - P.first_block, g, kApplyPoints), (const TS *)P.u[parity], (TS *)P.u[parity ^ 1],
         (const typename Slots<DIM, WIDE>::store_t *)P.sb, P.wp, P.pos, P.ent,
         (const EntRec<TS> *)P.went, h);
@@ -2972,25 +2970,13 @@ template <int DIM, bool WIDE, bool PER, bool MG, typename TS, typename TA> struc
         if (copy) {
             hipLaunchKernelGGL((k_copy_batch<TS>), dim3((unsigned)nblocks), dim3(kBS), 0, s, probs,
                                nprob);
-            return ADLBR_OK;
-        }
-        if constexpr (!MG) {
-            if (rep->went) {  // records without merged pairs (the class has them all)
-                if (variant & 1)
-                    hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, false, true, TS, TA, true>),
-                                       dim3((unsigned)nblocks), dim3(kBS), 0, s, probs, nprob, parity);
-                else
-                    hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, false, true, TS, TA, false>),
-                                       dim3((unsigned)nblocks), dim3(kBS), 0, s, probs, nprob, parity);
-                return ADLBR_OK;
-            }
-        }
-        if (variant & 1)
-            hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, MG, MG, TS, TA, true>),
+        } else if (variant & 1) {
+            hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, MG, TS, TA, true>), dim3((unsigned)nblocks),
+                               dim3(kBS), 0, s, probs, nprob, parity);
+        } else {
+            hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, MG, TS, TA, false>),
                                dim3((unsigned)nblocks), dim3(kBS), 0, s, probs, nprob, parity);
-        else
-            hipLaunchKernelGGL((k_apply_batch<DIM, WIDE, PER, MG, MG, TS, TA, false>),
-                               dim3((unsigned)nblocks), dim3(kBS), 0, s, probs, nprob, parity);
+        }
         return ADLBR_OK;
     }
 };
@@ -3076,8 +3062,7 @@ size_t merged_bytes(int dim, int storage) {
 }
 
 // merged: pairs of opposite edges merged, the listed ones kept with their
-// weights (3D always, but for the tiled layout's weights).  records: 2D, the
-// listed ones' weights in either case.
+// weights (3D always, but for the tiled layout's weights).
 Layout layout(const GridInfo &g, int storage, int wide, int merged, int records) {
     const long long N = g.N;
     const int S = g.dim == 2 ? 3 : 6;
@@ -3092,7 +3077,7 @@ Layout layout(const GridInfo &g, int storage, int wide, int merged, int records)
     L.cnt = o;  o += g.dim == 2 ? align_up((size_t)N + 64) : 0;
     L.pos = o;  o += align_up(4 * (size_t)N + 256);
     L.ent = o;  o += align_up(4 * (size_t)(2 * S) * N);
-    L.went = o; o += full || records ? align_up((dtype_size(storage) == 4 ? 8 : dtype_size(storage)) * (size_t)(2 * S) * N) : 0;
+    L.went = o; o += full ? align_up((dtype_size(storage) == 4 ? 8 : dtype_size(storage)) * (size_t)(2 * S) * N) : 0;
     L.diag = o; o += align_up((storage == ADLBR_F64 ? 8 : 4) * (size_t)N);
     L.scal = o; o += 256;
     L.mask = o; o += g.dim == 2 ? align_up((size_t)N + 64) : 0;
@@ -3134,7 +3119,7 @@ Layout layout(const GridInfo &g, int storage, int wide, int merged, int records)
 // always, 2D where the flags grant the memory.
 int merged_flag(const GridInfo &g, int flags) {
     if (flags & ADLBR_OP_TILED) return 0;
-    return g.dim == 3 || (flags & ADLBR_OP_MERGED) ? 1 : 0;
+    return g.dim == 3 || (flags & (ADLBR_OP_MERGED | ADLBR_OP_RECORDS)) ? 1 : 0;
 }
 
 }  // namespace
@@ -3179,7 +3164,7 @@ size_t batch_footprint(const adlbr_operator *op) {
     // u and its successor, offsets, edge weights, row start, and the listed
     // entries: about one (with its weight) per slot when merged, two if not
     const size_t w = op->merged ? merged_bytes(op->gi.dim, op->storage) : (size_t)op->slots * ts;
-    const size_t ent = (op->merged ? 1 : 2) * (op->went ? (ts == 8 ? 12 : ts == 4 ? 8 : 6) : 4);
+    const size_t ent = op->merged ? (ts == 8 ? 12 : ts == 4 ? 8 : 6) : 2 * 4;
     return (size_t)op->gi.N * (2 * ts + sbs + w + (size_t)op->slots * ent + 4);
 }
 
@@ -3328,7 +3313,7 @@ extern "C" int adlbr_operator_create(const adlbr_grid *g, const int16_t *offsets
     op->cnt = (uint8_t *)(b + L.cnt);
     op->pos = (int32_t *)(b + L.pos);
     op->ent = (int32_t *)(b + L.ent);
-    op->went = gi.dim == 3 || merged || records ? b + L.went : nullptr;
+    op->went = gi.dim == 3 || merged ? b + L.went : nullptr;
     op->diag = b + L.diag;
     op->maxdiag = (double *)(b + L.scal);
     op->dtcfl = (double *)(b + L.scal + 8);

