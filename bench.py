@@ -54,14 +54,14 @@ ALGO_BYTES = {(2, 8): 16 + 3 * 8 + 4, (2, 4): 8 + 3 * 4 + 4, (2, 2): 4 + 3 * 2 +
 # SHA-256 of the kernel sources they were taken on.  A change to those
 # sources makes the figure stale: traffic is then null.
 TRAFFIC = {
-    "c2": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
-           "bytes_per_launch": 269012774},
-    "c3": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
-           "bytes_per_launch": 1590070656},
-    "c3-bf16": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
-                "bytes_per_launch": 1227362133},
-    "c4": {"sha256": "e7f55e6c4652ee78e11a26cbd0fca8ad7d9bd46839383104db4934279b6b9f67",
-           "bytes_per_launch": 6236438198},
+    "c2": {"sha256": "6d45805b9e07c6fba4be1d0f765e98242689fde6b9d69bd9ec5930d0737164cf",
+           "bytes_per_launch": 269003430},
+    "c3": {"sha256": "6d45805b9e07c6fba4be1d0f765e98242689fde6b9d69bd9ec5930d0737164cf",
+           "bytes_per_launch": 1589945301},
+    "c3-bf16": {"sha256": "6d45805b9e07c6fba4be1d0f765e98242689fde6b9d69bd9ec5930d0737164cf",
+                "bytes_per_launch": 1226727424},
+    "c4": {"sha256": "6d45805b9e07c6fba4be1d0f765e98242689fde6b9d69bd9ec5930d0737164cf",
+           "bytes_per_launch": 6236592786},
 }
 TRAFFIC_SOURCES = ("paper_1301_3925_amd/csrc/operator.hip", "paper_1301_3925_amd/csrc/common.h")
 
