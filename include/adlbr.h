@@ -289,7 +289,8 @@ int adlbr_batch_set_variant(adlbr_batch *batch, int cls, int variant, size_t chu
  * (records*100000 + layout*10000 + dim*1000 + wide*100 + periodic*10 +
  * storage, records = 1 for 2D operators created with ADLBR_OP_RECORDS,
  * layout = 0 for lists of every edge, 1 tiled, 2 merged pairs: 3D lists, and
- * 2D with ADLBR_OP_MERGED), launch variant, number of problems and, where the pointers are not NULL, number of chunks and chunk
+ * 2D with ADLBR_OP_MERGED or ADLBR_OP_RECORDS), launch variant, number of
+ * problems and, where the pointers are not NULL, number of chunks and chunk
  * budget in bytes.  ADLBR_E_INVALID past the last class. */
 int adlbr_batch_variant(const adlbr_batch *batch, int cls, int *key, int *variant, int *nprob,
                         int *nchunks, size_t *chunk_bytes);
